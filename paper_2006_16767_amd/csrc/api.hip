@@ -195,6 +195,9 @@ struct spx_matrix {
     EllMat ell;
     DiaMat dia;
     Csr5Mat c5;
+    // first entry of every column past each row block of the LDS slabs (dX;
+    // allocated on first use)
+    int32_t* slab_part = nullptr;
     // column-sorted copy of the renumbered CSR for the balanced SpMV with
     // 2048-item tiles (kept with the renumbered copy when n <= 2^21)
     TileSorted ts;
@@ -491,7 +494,7 @@ extern "C" spx_status spx_matrix_destroy(spx_matrix* H) {
                     H->part[0][0], H->part[0][1], H->part[1][0], H->part[1][1], H->dev_sel, H->bws,
                     H->units, H->split_rows, H->bfs_front[0], H->bfs_front[1], H->bfs_y, H->drv_count,
                     H->bfs_bits[0], H->bfs_bits[1], H->pr_W, H->pr_r, H->pr_y, H->pr_xidx, H->pr_xval,
-                    H->pr_xd[0], H->pr_xd[1], H->pr_p, H->pr_bad, H->cnt_dev};
+                    H->pr_xd[0], H->pr_xd[1], H->pr_p, H->pr_bad, H->cnt_dev, H->slab_part};
     for (void* p : ptrs)
         if (p) hipFree(p);
     sell_free(&H->sell);
@@ -1827,12 +1830,48 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
 extern "C" spx_status spmv_csr_batch(spx_matrix* H, int32_t B, const void* X, void* Y, void* stream) {
     if (!H || (B > 0 && (!X || !Y))) return fail(SPX_ERR_ARG, "null argument");
     if (B < 0) return fail(SPX_ERR_SHAPE, "B must be >= 0");
-    const int dt = H->csr.dtype;
-    if (dt != SPX_F32 && dt != SPX_F64) return fail(SPX_ERR_DTYPE, "the fused batch SpMV supports F32 and F64");
-    SPX_TRY(ensure_ws(H, grad_ws_bytes(H->csr.m, H->csr.n, B, dt)));
+    const spx_csr& A = H->csr;
+    if (A.dtype != SPX_F32 && A.dtype != SPX_F64)
+        return fail(SPX_ERR_DTYPE, "the fused batch SpMV supports F32 and F64");
+    if (slab_gather_fits(A.m, A.n, A.nnz, B, A.dtype, nullptr))
+        return slab_gather(A.m, A.n, A.nnz, B, A.dtype, nullptr, A.row_ptr, nullptr, A.col_idx, A.vals, X, Y,
+                           (hipStream_t)stream);
+    SPX_TRY(ensure_ws(H, grad_ws_bytes(A.m, A.n, B, A.dtype)));
     Arena ws(H->ws, H->ws_bytes);
-    return launch_spmv_batch(H->csr.row_ptr, H->csr.col_idx, H->csr.vals, H->csr.m, H->csr.n, dt, B, X, Y, ws,
-                             (hipStream_t)stream);
+    return launch_spmv_batch(A.row_ptr, A.col_idx, A.vals, A.m, A.n, A.dtype, B, X, Y, ws, (hipStream_t)stream);
+}
+
+// dX = G A over the CSC copy (its rows ascend within a column, so G's rows
+// of length m can pass through LDS in blocks)
+static spx_status run_dx(spx_matrix* H, int32_t B, const void* G, void* dX, hipStream_t s) {
+    const spx_csr& A = H->csr;
+    const SlabBlocks blocks = slab_blocks(A.m);
+    if (slab_gather_fits(A.n, A.m, A.nnz, B, A.dtype, &blocks)) {
+        if (blocks.nblk > 1 && !H->slab_part) {
+            int32_t* part = nullptr;
+            if (hipMalloc((void**)&part, (size_t)blocks.nblk * A.n * 4) != hipSuccess)
+                return fail(SPX_ERR_ALLOC, "dX: block table allocation failed");
+            const spx_status st = slab_part_build(A.n, blocks, H->col_ptr, H->row_idx, part, s);
+            if (st != SPX_OK) {
+                hipFree(part);
+                return st;
+            }
+            H->slab_part = part;
+        }
+        return slab_gather(A.n, A.m, A.nnz, B, A.dtype, &blocks, H->col_ptr, H->slab_part, H->row_idx, H->vals_csc, G, dX, s);
+    }
+    SPX_TRY(ensure_ws(H, grad_ws_bytes(A.m, A.n, B, A.dtype)));
+    Arena ws(H->ws, H->ws_bytes);
+    return launch_dx(H->col_ptr, H->row_idx, H->vals_csc, A.m, A.n, A.dtype, B, G, dX, ws, s);
+}
+
+static spx_status run_dvals(spx_matrix* H, int32_t B, const void* G, const void* X, void* dvals, hipStream_t s) {
+    const spx_csr& A = H->csr;
+    if (slab_sddmm_fits(A.m, A.n, A.nnz, B, A.dtype))
+        return slab_sddmm(A.m, A.n, A.nnz, B, A.dtype, A.row_ptr, A.col_idx, G, X, dvals, s);
+    SPX_TRY(ensure_ws(H, grad_ws_bytes(A.m, A.n, B, A.dtype)));
+    Arena ws(H->ws, H->ws_bytes);
+    return launch_dvals(A.row_ptr, A.col_idx, A.m, A.n, A.nnz, A.dtype, B, G, X, dvals, ws, s);
 }
 
 extern "C" spx_status spmv_csr_transpose(spx_matrix* H, int32_t B, const void* G, void* dX, void* stream) {
@@ -1840,10 +1879,7 @@ extern "C" spx_status spmv_csr_transpose(spx_matrix* H, int32_t B, const void* G
     if (B < 0) return fail(SPX_ERR_SHAPE, "B must be >= 0");
     const int dt = H->csr.dtype;
     if (dt != SPX_F32 && dt != SPX_F64) return fail(SPX_ERR_DTYPE, "backward supports F32 and F64");
-    SPX_TRY(ensure_ws(H, grad_ws_bytes(H->csr.m, H->csr.n, B, dt)));
-    Arena ws(H->ws, H->ws_bytes);
-    return launch_dx(H->col_ptr, H->row_idx, H->vals_csc, H->csr.m, H->csr.n, dt, B, G, dX, ws,
-                     (hipStream_t)stream);
+    return run_dx(H, B, G, dX, (hipStream_t)stream);
 }
 
 extern "C" spx_status dvals_pattern(spx_matrix* H, int32_t B, const void* G, const void* X, void* dvals,
@@ -1852,22 +1888,29 @@ extern "C" spx_status dvals_pattern(spx_matrix* H, int32_t B, const void* G, con
     if (B < 0) return fail(SPX_ERR_SHAPE, "B must be >= 0");
     const int dt = H->csr.dtype;
     if (dt != SPX_F32 && dt != SPX_F64) return fail(SPX_ERR_DTYPE, "backward supports F32 and F64");
-    SPX_TRY(ensure_ws(H, grad_ws_bytes(H->csr.m, H->csr.n, B, dt)));
-    Arena ws(H->ws, H->ws_bytes);
-    return launch_dvals(H->csr.row_ptr, H->csr.col_idx, H->csr.m, H->csr.n, H->csr.nnz, dt, B, G, X, dvals, ws,
-                        (hipStream_t)stream);
+    return run_dvals(H, B, G, X, dvals, (hipStream_t)stream);
 }
 
 extern "C" spx_status spx_backward(spx_matrix* H, int32_t B, const void* G, const void* X, void* dX, void* dvals,
                                    void* stream) {
     if (!H || (B > 0 && (!G || (dvals && !X))) || (!dX && !dvals)) return fail(SPX_ERR_ARG, "null argument");
     if (B < 0) return fail(SPX_ERR_SHAPE, "B must be >= 0");
-    const int dt = H->csr.dtype;
+    const spx_csr& A = H->csr;
+    const int dt = A.dtype;
     if (dt != SPX_F32 && dt != SPX_F64) return fail(SPX_ERR_DTYPE, "backward supports F32 and F64");
-    SPX_TRY(ensure_ws(H, grad_ws_bytes(H->csr.m, H->csr.n, B, dt)));
+    hipStream_t s = (hipStream_t)stream;
+    const SlabBlocks blocks = slab_blocks(A.m);
+    const bool dx_slab = dX && slab_gather_fits(A.n, A.m, A.nnz, B, dt, &blocks);
+    const bool dv_slab = dvals && slab_sddmm_fits(A.m, A.n, A.nnz, B, dt);
+    if (dx_slab || dv_slab) {
+        // a gradient that does not go through LDS makes its own B-minor copies
+        if (dX) SPX_TRY(run_dx(H, B, G, dX, s));
+        return dvals ? run_dvals(H, B, G, X, dvals, s) : SPX_OK;
+    }
+    SPX_TRY(ensure_ws(H, grad_ws_bytes(A.m, A.n, B, dt)));
     Arena ws(H->ws, H->ws_bytes);
-    return launch_backward(H->csr.row_ptr, H->csr.col_idx, H->col_ptr, H->row_idx, H->vals_csc, H->csr.m, H->csr.n,
-                           H->csr.nnz, dt, B, G, X, dX, dvals, ws, (hipStream_t)stream);
+    return launch_backward(A.row_ptr, A.col_idx, H->col_ptr, H->row_idx, H->vals_csc, A.m, A.n, A.nnz, dt, B, G, X, dX,
+                           dvals, ws, s);
 }
 
 extern "C" spx_status spx_pack_mask(int32_t m, const uint8_t* rows, uint32_t* words, void* stream) {

@@ -142,6 +142,11 @@ struct SR<SPX_BOOL> {
     }
 };
 
+// a * b + c rounded once, in the operands' own type (__builtin_fma takes
+// float operands through double: three conversions and an FP64 operation)
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // ---------------------------------------------------------------------------
 // Bounded accumulation chains. A kernel that walks a long row (or column)
 // keeps U independent partial sums, one per unrolled load slot, and every

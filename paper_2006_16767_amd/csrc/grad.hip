@@ -95,12 +95,12 @@ __global__ __launch_bounds__(kSegThreads) void k_seg_gather(int32_t nseg, int32_
 #pragma unroll
             for (int u = 0; u < 8; ++u) gv[u] = g[(int64_t)r[u] * B];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc.part[u] = __builtin_fma(v[u], gv[u], acc.part[u]);
+            for (int u = 0; u < 8; ++u) acc.part[u] = fma_t(v[u], gv[u], acc.part[u]);
             acc.end_round();
         }
 #pragma unroll
         for (int u = 0; u < 7; ++u)
-            if (k + u < c1) acc.part[u] = __builtin_fma(vals[k + u], g[(int64_t)idx[k + u] * B], acc.part[u]);
+            if (k + u < c1) acc.part[u] = fma_t(vals[k + u], g[(int64_t)idx[k + u] * B], acc.part[u]);
         tile[w][lane] = acc.total();
     }
     __syncthreads();
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kBlock) void k_sddmm(int32_t m, int32_t B, const in
 #pragma unroll
             for (int u = 0; u < 16; ++u) xv[u] = XT[(int64_t)c[u] * B + b];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) p[u] = __builtin_fma(gv, xv[u], p[u]);
+            for (int u = 0; u < 16; ++u) p[u] = fma_t(gv, xv[u], p[u]);
         }
         const T s = wave_fold16(p);
         const int v = (lane >> 2) & 15;

@@ -1,0 +1,558 @@
+// The pruned layer's products with the dense operand held in LDS: a batch of
+// dense rows times A (or its transpose), and the gradient of A's values.
+//
+//   k_slab_gather  out[b, j]  = sum over the entries k of segment j of
+//                  vals[k] * in[b, idx[k]]: the forward (segments = rows of A,
+//                  in = X) and dX (segments = columns, in = G)
+//   k_slab_sddmm   dvals[k] = sum_b G[b, row k] * X[b, col k]
+//
+// Per stored entry and batch row these need one value of the dense operand,
+// at a random place. Gathering it from L2 (a B-minor copy, a row of B values
+// per entry) moves 4 B bytes per entry through the L2 and the address path:
+// 860 MB for the 16384 x 4096 layer at 5 % and B = 64, 57 us at 15 TB/s. Here
+// a workgroup holds a slab of the operand in LDS, kSlabCols columns of a few
+// batch rows (32 bytes a column: 8 FP32 or 4 FP64 batch rows, one or two
+// 16-byte LDS reads per entry), built from the B-major operand itself (no
+// B-minor copy), and streams the segments' indices and values past it. The
+// matrix is then read once per 8 batch rows instead of once, 64 instead of
+// 264 bytes per entry; the workgroups that read the same segments for the
+// other batch rows are neighbours on one XCD, so those reads meet in its L2.
+//
+// 16 lanes walk a segment, four segments per wave in lockstep, four entries
+// per lane at a time with the next four (of the segment, or the first of the
+// next one) already in flight. The bound is the LDS: random 32-byte columns
+// meet on the same banks about twice as often as they would in order. Odd
+// lanes read the second half of a column first, so that the two reads of a
+// wave use all banks.
+//
+// A segment's part in a slab holds at most kSlabCols entries (a segment's
+// indices are distinct), so a lane's running sum is a chain of at most
+// kSlabCols / 16 additions; the 16 lanes' sums are added as a tree.
+#include <algorithm>
+#include <utility>
+
+#include "common.hpp"
+#include "csr_tile.hpp"
+#include "internal.hpp"
+
+namespace spx {
+
+constexpr int kSlabThreads = 1024;
+constexpr int kSlabLanes = 16;                            // lanes per segment: a DPP row
+constexpr int kSlabGroups = kSlabThreads / kSlabLanes;    // segments in flight per workgroup
+constexpr int kSlabU = 4;                                 // entries per lane and step
+constexpr int kSlabStep = kSlabLanes * kSlabU;
+constexpr int kSlabBytes = 128 * 1024;                    // of the CU's 160 KiB
+constexpr int kSlabMaxSegs = 512;                         // segments per workgroup
+
+// columns of a slab of 16-byte (W = 1) or 32-byte (W = 2) columns
+constexpr int slab_cols(int W) { return kSlabBytes / (16 * W); }
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_word(int v) {
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp(T v) {
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, dpp_word<CTRL>(__builtin_bit_cast(int, v)));
+    } else {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const uint32_t lo = (uint32_t)dpp_word<CTRL>((int)(uint32_t)u);
+        const uint32_t hi = (uint32_t)dpp_word<CTRL>((int)(uint32_t)(u >> 32));
+        return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
+    }
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;      // quad_perm
+constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;    // rotations of a row of 16 lanes
+constexpr int kDppBcast = 0x150;                     // row_newbcast: lane n of the row to all
+
+// row[i] = lane i's value of the row of 16 lanes
+template <typename T, int N, int... I>
+__device__ __forceinline__ void row_bcast(T v, T (&row)[N], std::integer_sequence<int, I...>) {
+    ((row[I] = dpp<kDppBcast + I>(v)), ...);
+}
+
+// Buffer loads: a 32-bit byte offset from a base in scalar registers, and 0
+// for what lies past the size (no branch around the load).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
+}
+template <typename T>
+__device__ __forceinline__ T buffer_value(__amdgpu_buffer_rsrc_t r, int at) {
+    if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, 0));
+}
+
+template <typename T>
+struct SlabVec {
+    static constexpr int E = 16 / sizeof(T);  // values per 16-byte LDS read
+    T v[E];
+};
+
+// One slab: columns [c0, c0 + cb) of batch rows b0 .. b0 + NB - 1 of in (B x
+// N), first into registers (so that the next slab loads while this one is in
+// use), then to LDS; rows past B are zeros. Column cb of the slab is all
+// zeros: the place that lanes without an entry read.
+template <typename T, int W>
+struct SlabLoad {
+    static constexpr int E = SlabVec<T>::E, NB = W * E;
+    static constexpr int kPer = slab_cols(W) / kSlabThreads;
+    T r[kPer][NB];
+    __device__ __forceinline__ void load(const T* __restrict__ in, int64_t N, int32_t B, int32_t b0, int32_t c0,
+                                         int32_t cb) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            // past the columns, and for rows past B, the load returns 0
+            const auto row = buffer_of(in + (int64_t)(b0 + b) * N + c0, b0 + b < B ? cb * (int)sizeof(T) : 0);
+#pragma unroll
+            for (int p = 0; p < kPer; ++p)
+                r[p][b] = buffer_value<T>(row, (p * kSlabThreads + (int)threadIdx.x) * (int)sizeof(T));
+        }
+    }
+    __device__ __forceinline__ void store(char* slab, int32_t cb) const {
+        const int par = threadIdx.x & 1;
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) {
+            const int c = p * kSlabThreads + (int)threadIdx.x;
+            if (c < cb) {
+                if constexpr (W == 2) {
+                    // odd lanes store their second half first (bank use)
+                    SlabVec<T> a, b;
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        a.v[e] = par ? r[p][E + e] : r[p][e];
+                        b.v[e] = par ? r[p][e] : r[p][E + e];
+                    }
+                    *(SlabVec<T>*)(slab + (c << 5) + (par << 4)) = a;
+                    *(SlabVec<T>*)(slab + (c << 5) + ((par ^ 1) << 4)) = b;
+                } else {
+                    SlabVec<T> a;
+#pragma unroll
+                    for (int e = 0; e < E; ++e) a.v[e] = r[p][e];
+                    *(SlabVec<T>*)(slab + (c << 4)) = a;
+                }
+            }
+        }
+        if (threadIdx.x < (unsigned)W) {
+            SlabVec<T> z;
+#pragma unroll
+            for (int e = 0; e < E; ++e) z.v[e] = (T)0;
+            *(SlabVec<T>*)(slab + (int64_t)cb * 16 * W + threadIdx.x * 16) = z;
+        }
+    }
+};
+
+// Byte offset of column c of the slab; for W = 2, of its half of the lane's
+// parity (par16 = 16 for odd lanes), which p[0] then holds, p[1] the other.
+template <int W>
+__device__ __forceinline__ int slab_at(int c, int par16) {
+    return W == 2 ? (c << 5) | par16 : c << 4;
+}
+template <typename T, int W>
+__device__ __forceinline__ void slab_read(const char* slab, int at, SlabVec<T> (&p)[W]) {
+    p[0] = *(const SlabVec<T>*)(slab + at);
+    if constexpr (W == 2) p[1] = *(const SlabVec<T>*)(slab + (at ^ 16));
+}
+
+// The 16 lanes' sums a[w][e] of a segment folded: every lane ends with E / 2
+// full sums, of batch rows slab_fold_row(lane) .. + E / 2 - 1.
+template <typename T, int W>
+__device__ __forceinline__ void slab_fold(const T (&a)[W][SlabVec<T>::E], T (&out)[SlabVec<T>::E / 2]) {
+    constexpr int E = SlabVec<T>::E;
+    const int lane = lane_id();
+    T v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        v[e] = a[0][e];
+        // the neighbour's second half is this lane's first
+        if constexpr (W == 2) v[e] += dpp<kDppXor1>(a[1][e]);
+    }
+    const bool hi = lane & W;  // bit 1 for W = 2, bit 0 for W = 1
+    constexpr int ctrl = W == 2 ? kDppXor2 : kDppXor1;
+#pragma unroll
+    for (int i = 0; i < E / 2; ++i) {
+        T s = (hi ? v[i + E / 2] : v[i]) + dpp<ctrl>(hi ? v[i] : v[i + E / 2]);
+        if constexpr (W == 1) s += dpp<kDppXor2>(s);
+        s += dpp<kDppRor4>(s);
+        out[i] = s + dpp<kDppRor8>(s);
+    }
+}
+template <typename T, int W>
+__device__ __forceinline__ int slab_fold_row(int lane) {
+    constexpr int E = SlabVec<T>::E;
+    return W == 2 ? (lane & 1) * E + ((lane >> 1) & 1) * (E / 2) : (lane & 1) * (E / 2);
+}
+
+// LDS of a gather workgroup: the slab and its zero column, then the sums of
+// the segments, NB + 1 values apart.
+template <typename T, int W>
+static size_t slab_gather_lds(int32_t cb, int32_t segs) {
+    return (size_t)(cb + 1) * 16 * W + (size_t)segs * (W * SlabVec<T>::E + 1) * sizeof(T);
+}
+
+// Workgroup = (segments [tile * st, + st), batch rows [chunk * NB, + NB)).
+// The operand's N columns come as nblk slabs of cb; with nblk > 1 the
+// segments' indices ascend and part[blk * nseg + j] is the first entry of
+// segment j at or past column blk * cb (blk < nblk).
+template <typename T, int W>
+__global__ __launch_bounds__(kSlabThreads) void k_slab_gather(int32_t nseg, int32_t N, int32_t nnz, int32_t B,
+                                                              int32_t st, int32_t nchunk, int32_t nblk, int32_t cb,
+                                                              const int32_t* __restrict__ seg_ptr,
+                                                              const int32_t* __restrict__ part,
+                                                              const int32_t* __restrict__ idx,
+                                                              const T* __restrict__ vals, const T* __restrict__ in,
+                                                              T* __restrict__ out) {
+    constexpr int E = SlabVec<T>::E, NB = W * E, kRow = NB + 1;
+    extern __shared__ __align__(16) char s_raw[];
+    const int64_t t = xcd_tile(blockIdx.x, gridDim.x);
+    const int32_t tile = (int32_t)(t / nchunk), b0 = (int32_t)(t % nchunk) * NB;
+    const int32_t j0 = tile * st;
+    const int32_t ns = min(st, nseg - j0);
+    char* slab = s_raw;
+    T* sums = (T*)(s_raw + (size_t)(cb + 1) * 16 * W);
+    const int lane = lane_id();
+    const int g = lane % kSlabLanes, par16 = (lane & 1) << 4;
+    const int s0 = threadIdx.x / kSlabLanes;
+    const int rounds = (ns + kSlabGroups - 1) / kSlabGroups;
+    const auto bidx = buffer_of(idx, nnz * 4), bval = buffer_of(vals, nnz * (int)sizeof(T));
+    SlabLoad<T, W> next;
+    next.load(in, N, B, b0, 0, min(cb, N));
+    for (int blk = 0; blk < nblk; ++blk) {
+        const int32_t c0 = blk * cb;
+        const int32_t width = min(cb, N - c0);
+        if (blk > 0) __syncthreads();  // the last slab has been read
+        next.store(slab, width);
+        __syncthreads();
+        if (blk + 1 < nblk) next.load(in, N, B, b0, c0 + cb, min(cb, N - c0 - cb));
+        auto bounds = [&](int r, int& k0, int& k1) {
+            const int s = r * kSlabGroups + s0;
+            k0 = k1 = 0;
+            if (s < ns) {
+                const int64_t j = j0 + s;
+                k0 = blk > 0 ? part[(int64_t)blk * nseg + j] : seg_ptr[j];
+                k1 = blk + 1 < nblk ? part[(int64_t)(blk + 1) * nseg + j] : seg_ptr[j + 1];
+            }
+        };
+        auto fetch = [&](int k, int (&c)[kSlabU], T (&v)[kSlabU]) {
+#pragma unroll
+            for (int u = 0; u < kSlabU; ++u) {
+                c[u] = buffer_value<int>(bidx, (k + g + u * kSlabLanes) * 4);
+                v[u] = buffer_value<T>(bval, (k + g + u * kSlabLanes) * (int)sizeof(T));
+            }
+        };
+        int ka, kb, kc, kd;
+        bounds(0, ka, kb);
+        bounds(1, kc, kd);
+        int c[kSlabU];
+        T v[kSlabU];
+        fetch(ka, c, v);
+        for (int r = 0; r < rounds; ++r) {
+            int ke, kf;
+            bounds(r + 2, ke, kf);
+            T acc[W][E];
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[w][e] = (T)0;
+            int k = ka;
+            bool more;
+            do {
+                more = __any(k + kSlabStep < kb);  // uniform over the wave
+                // entries past the end read the zero column with value 0
+                SlabVec<T> p[kSlabU][W];
+                T a[kSlabU];
+#pragma unroll
+                for (int u = 0; u < kSlabU; ++u) {
+                    const bool on = k + g + u * kSlabLanes < kb;
+                    slab_read<T, W>(slab, slab_at<W>(on ? c[u] - c0 : width, par16), p[u]);
+                    a[u] = on ? v[u] : (T)0;
+                }
+                fetch(more ? k + kSlabStep : kc, c, v);
+#pragma unroll
+                for (int u = 0; u < kSlabU; ++u)
+#pragma unroll
+                    for (int w = 0; w < W; ++w)
+#pragma unroll
+                        for (int e = 0; e < E; ++e) acc[w][e] = fma_t(a[u], p[u][w].v[e], acc[w][e]);
+                k += kSlabStep;
+            } while (more);
+            T f[E / 2];
+            slab_fold<T, W>(acc, f);
+            const int s = r * kSlabGroups + s0;
+            if (g < 2 * W && s < ns) {
+                T* o = sums + s * kRow + slab_fold_row<T, W>(lane);
+#pragma unroll
+                for (int i = 0; i < E / 2; ++i) o[i] = blk > 0 ? o[i] + f[i] : f[i];
+            }
+            ka = kc;
+            kb = kd;
+            kc = ke;
+            kd = kf;
+        }
+    }
+    __syncthreads();
+    const int nb = min(NB, B - b0);
+    for (int i = threadIdx.x; i < ns * nb; i += kSlabThreads) {
+        const int b = i / ns, s = i - b * ns;
+        out[(int64_t)(b0 + b) * nseg + j0 + s] = sums[s * kRow + b];
+    }
+}
+
+// Workgroup = rows [tile * st, + st) of A, all batch rows, NB at a time. Each
+// entry's sum over the batch rows stays with one thread, which adds a
+// chunk's part to dvals[k] (its own store of the last chunk, from L2).
+template <typename T, int W>
+__global__ __launch_bounds__(kSlabThreads) void k_slab_sddmm(int32_t m, int32_t n, int32_t nnz, int32_t B,
+                                                             int32_t st,
+                                                             const int32_t* __restrict__ row_ptr,
+                                                             const int32_t* __restrict__ col_idx,
+                                                             const T* __restrict__ G, const T* __restrict__ X,
+                                                             T* __restrict__ dvals) {
+    constexpr int E = SlabVec<T>::E, NB = W * E;
+    extern __shared__ __align__(16) char s_raw[];
+    const int32_t j0 = (int32_t)xcd_tile(blockIdx.x, gridDim.x) * st;
+    const int32_t ns = min(st, m - j0);
+    char* slab = s_raw;
+    const int lane = lane_id();
+    const int g = lane % kSlabLanes, par16 = (lane & 1) << 4;
+    const int s0 = threadIdx.x / kSlabLanes;
+    const int rounds = (ns + kSlabGroups - 1) / kSlabGroups;
+    const auto bidx = buffer_of(col_idx, nnz * 4);
+    SlabLoad<T, W> next;
+    next.load(X, n, B, 0, 0, n);
+    for (int b0 = 0; b0 < B; b0 += NB) {
+        if (b0 > 0) __syncthreads();
+        next.store(slab, n);
+        __syncthreads();
+        if (b0 + NB < B) next.load(X, n, B, b0 + NB, 0, n);
+        // row bounds, and the row's value of G of batch row b0 + g % NB
+        auto bounds = [&](int r, int& k0, int& k1, T& gv) {
+            const int s = r * kSlabGroups + s0;
+            k0 = k1 = 0;
+            gv = (T)0;
+            if (s < ns) {
+                k0 = row_ptr[j0 + s];
+                k1 = row_ptr[j0 + s + 1];
+                const int b = b0 + g % NB;
+                if (b < B) gv = G[(int64_t)b * m + j0 + s];
+            }
+        };
+        const auto bdv = buffer_of(dvals, b0 > 0 ? nnz * (int)sizeof(T) : 0);  // the first chunk adds to 0
+        auto fetch = [&](int k, int (&c)[kSlabU], T (&d)[kSlabU]) {
+#pragma unroll
+            for (int u = 0; u < kSlabU; ++u) {
+                c[u] = buffer_value<int>(bidx, (k + g + u * kSlabLanes) * 4);
+                d[u] = buffer_value<T>(bdv, (k + g + u * kSlabLanes) * (int)sizeof(T));
+            }
+        };
+        int ka, kb, kc, kd;
+        T ga, gc;
+        bounds(0, ka, kb, ga);
+        bounds(1, kc, kd, gc);
+        int c[kSlabU];
+        T d[kSlabU];
+        fetch(ka, c, d);
+        for (int r = 0; r < rounds; ++r) {
+            int ke, kf;
+            T ge;
+            bounds(r + 2, ke, kf, ge);
+            // lane b of the 16 holds batch row b0 + b: all NB to every lane,
+            // the half of the lane's parity first
+            T row[NB];
+            row_bcast(ga, row, std::make_integer_sequence<int, NB>{});
+            T gw[W][E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                if constexpr (W == 2) {
+                    gw[0][e] = par16 ? row[E + e] : row[e];
+                    gw[1][e] = par16 ? row[e] : row[E + e];
+                } else {
+                    gw[0][e] = row[e];
+                }
+            }
+            int k = ka;
+            bool more;
+            do {
+                more = __any(k + kSlabStep < kb);  // uniform over the wave
+                SlabVec<T> p[kSlabU][W];
+                T old[kSlabU];
+#pragma unroll
+                for (int u = 0; u < kSlabU; ++u) {
+                    const bool on = k + g + u * kSlabLanes < kb;
+                    slab_read<T, W>(slab, slab_at<W>(on ? c[u] : n, par16), p[u]);
+                    old[u] = d[u];
+                }
+                fetch(more ? k + kSlabStep : kc, c, d);
+#pragma unroll
+                for (int u = 0; u < kSlabU; ++u) {
+                    T s[W];
+#pragma unroll
+                    for (int w = 0; w < W; ++w) {
+                        s[w] = gw[w][0] * p[u][w].v[0];
+#pragma unroll
+                        for (int e = 1; e < E; ++e) s[w] = fma_t(gw[w][e], p[u][w].v[e], s[w]);
+                    }
+                    T sum = s[0];
+                    if constexpr (W == 2) sum += s[1];
+                    const int q = k + g + u * kSlabLanes;
+                    if (q < kb) dvals[q] = old[u] + sum;
+                }
+                k += kSlabStep;
+            } while (more);
+            ka = kc;
+            kb = kd;
+            ga = gc;
+            kc = ke;
+            kd = kf;
+            gc = ge;
+        }
+    }
+}
+
+// part[blk * n + j] for blk in [1, nblk): the first entry of column j whose
+// row is at or past blk * cb (rows ascend within a column of the CSC copy).
+__global__ __launch_bounds__(kBlock) void k_slab_part(int32_t n, int32_t nblk, int32_t cb,
+                                                      const int32_t* __restrict__ col_ptr,
+                                                      const int32_t* __restrict__ row_idx,
+                                                      int32_t* __restrict__ part) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= (int64_t)n * nblk) return;
+    const int32_t blk = (int32_t)(i / n), j = (int32_t)(i % n);
+    int lo = col_ptr[j], hi = col_ptr[j + 1];
+    while (lo < hi) {
+        const int mid = lo + (hi - lo) / 2;
+        if (row_idx[mid] < blk * cb)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    part[i] = lo;
+}
+
+// ------------------------------------------------------------------ host
+SlabBlocks slab_blocks(int32_t N) {
+    SlabBlocks b;
+    b.nblk = (int32_t)std::max<int64_t>(1, ceil_div(N, slab_cols(2)));
+    b.cb = (int32_t)ceil_div(std::max(N, 1), b.nblk);
+    return b;
+}
+
+spx_status slab_part_build(int32_t n, const SlabBlocks& b, const int32_t* col_ptr, const int32_t* row_idx,
+                           int32_t* part, hipStream_t s) {
+    k_slab_part<<<(unsigned)ceil_div((int64_t)n * b.nblk, kBlock), kBlock, 0, s>>>(n, b.nblk, b.cb, col_ptr, row_idx,
+                                                                                   part);
+    SPX_HIP(hipGetLastError());
+    return SPX_OK;
+}
+
+// Mean entries a segment must have per slab: below it the segment's share of
+// a workgroup is its bounds, its fold and idle lanes, and the gather from L2
+// is the faster one.
+constexpr double kSlabMinEntries = 8.0;
+
+// 16-byte columns for few batch rows, and for operands of up to twice the
+// columns
+template <typename T>
+static int slab_width(int32_t N, int32_t B) {
+    constexpr int E = SlabVec<T>::E;
+    if (N > slab_cols(1)) return 0;
+    return N > slab_cols(2) || B <= E ? 1 : 2;
+}
+
+// the entries' arrays are addressed by 32-bit byte offsets
+static bool slab_addresses(int32_t nnz, int dtype) { return (int64_t)nnz * (dtype == SPX_F64 ? 8 : 4) < (int64_t(1) << 31); }
+
+bool slab_gather_fits(int32_t nseg, int32_t N, int32_t nnz, int32_t B, int dtype, const SlabBlocks* blocks) {
+    if (nseg <= 0 || N <= 0 || B <= 0 || !slab_addresses(nnz, dtype)) return false;
+    if (!blocks && (dtype == SPX_F64 ? slab_width<double>(N, B) : slab_width<float>(N, B)) == 0) return false;
+    const int32_t nblk = blocks ? blocks->nblk : 1;
+    return (double)nnz >= kSlabMinEntries * (double)nseg * nblk;
+}
+
+bool slab_sddmm_fits(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype) {
+    if (m <= 0 || n <= 0 || B <= 0 || !slab_addresses(nnz, dtype)) return false;
+    if ((dtype == SPX_F64 ? slab_width<double>(n, B) : slab_width<float>(n, B)) == 0) return false;
+    return (double)nnz >= kSlabMinEntries * (double)m;
+}
+
+static spx_status slab_cus(int* cus) {
+    int dev = 0;
+    SPX_HIP(hipGetDevice(&dev));
+    SPX_HIP(hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev));
+    *cus = std::max(*cus, 1);
+    return SPX_OK;
+}
+
+template <typename T, int W>
+static spx_status slab_gather_w(int32_t nseg, int32_t N, int32_t nnz, int32_t B, const SlabBlocks& b, const int32_t* seg_ptr,
+                                const int32_t* part, const int32_t* idx, const T* vals, const T* in, T* out,
+                                hipStream_t s) {
+    constexpr int NB = W * SlabVec<T>::E;
+    const int32_t nchunk = (int32_t)ceil_div(B, NB);
+    int cus = 0;
+    SPX_TRY(slab_cus(&cus));
+    // about a workgroup per CU (the slab fills its LDS), and enough segments
+    // in each for its 64 groups
+    const int64_t want = std::max<int64_t>(1, cus / nchunk);
+    const int32_t st = (int32_t)std::min<int64_t>(kSlabMaxSegs, std::max<int64_t>(kSlabGroups, ceil_div(nseg, want)));
+    const int64_t grid = ceil_div(nseg, st) * nchunk;
+    if (grid > 0x7fffffff) return fail(SPX_ERR_SHAPE, "batch gather: too many batch rows");
+    const size_t lds = slab_gather_lds<T, W>(b.cb, st);
+    SPX_HIP(hipFuncSetAttribute((const void*)k_slab_gather<T, W>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds));
+    k_slab_gather<T, W><<<(unsigned)grid, kSlabThreads, lds, s>>>(nseg, N, nnz, B, st, nchunk, b.nblk, b.cb, seg_ptr, part,
+                                                                  idx, vals, in, out);
+    SPX_HIP(hipGetLastError());
+    return SPX_OK;
+}
+
+template <typename T>
+static spx_status slab_gather_t(int32_t nseg, int32_t N, int32_t nnz, int32_t B, const SlabBlocks* blocks, const int32_t* seg_ptr,
+                                const int32_t* part, const int32_t* idx, const void* vals, const void* in, void* out,
+                                hipStream_t s) {
+    const SlabBlocks b = blocks ? *blocks : SlabBlocks{1, N};
+    const int W = b.cb <= slab_cols(2) && B > SlabVec<T>::E ? 2 : 1;
+    if (W == 2)
+        return slab_gather_w<T, 2>(nseg, N, nnz, B, b, seg_ptr, part, idx, (const T*)vals, (const T*)in, (T*)out, s);
+    return slab_gather_w<T, 1>(nseg, N, nnz, B, b, seg_ptr, part, idx, (const T*)vals, (const T*)in, (T*)out, s);
+}
+
+spx_status slab_gather(int32_t nseg, int32_t N, int32_t nnz, int32_t B, int dtype, const SlabBlocks* blocks, const int32_t* seg_ptr,
+                       const int32_t* part, const int32_t* idx, const void* vals, const void* in, void* out,
+                       hipStream_t s) {
+    if (dtype == SPX_F32) return slab_gather_t<float>(nseg, N, nnz, B, blocks, seg_ptr, part, idx, vals, in, out, s);
+    return slab_gather_t<double>(nseg, N, nnz, B, blocks, seg_ptr, part, idx, vals, in, out, s);
+}
+
+template <typename T, int W>
+static spx_status slab_sddmm_w(int32_t m, int32_t n, int32_t nnz, int32_t B, const int32_t* row_ptr, const int32_t* col_idx,
+                               const void* G, const void* X, void* dvals, hipStream_t s) {
+    int cus = 0;
+    SPX_TRY(slab_cus(&cus));
+    const int32_t st = (int32_t)std::max<int64_t>(kSlabGroups, ceil_div(m, cus));
+    const size_t lds = (size_t)(n + 1) * 16 * W;
+    SPX_HIP(hipFuncSetAttribute((const void*)k_slab_sddmm<T, W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    k_slab_sddmm<T, W><<<(unsigned)ceil_div(m, st), kSlabThreads, lds, s>>>(m, n, nnz, B, st, row_ptr, col_idx,
+                                                                            (const T*)G, (const T*)X, (T*)dvals);
+    SPX_HIP(hipGetLastError());
+    return SPX_OK;
+}
+
+template <typename T>
+static spx_status slab_sddmm_t(int32_t m, int32_t n, int32_t nnz, int32_t B, const int32_t* row_ptr, const int32_t* col_idx,
+                               const void* G, const void* X, void* dvals, hipStream_t s) {
+    if (slab_width<T>(n, B) == 2) return slab_sddmm_w<T, 2>(m, n, nnz, B, row_ptr, col_idx, G, X, dvals, s);
+    return slab_sddmm_w<T, 1>(m, n, nnz, B, row_ptr, col_idx, G, X, dvals, s);
+}
+
+spx_status slab_sddmm(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype, const int32_t* row_ptr, const int32_t* col_idx,
+                      const void* G, const void* X, void* dvals, hipStream_t s) {
+    if (dtype == SPX_F32) return slab_sddmm_t<float>(m, n, nnz, B, row_ptr, col_idx, G, X, dvals, s);
+    return slab_sddmm_t<double>(m, n, nnz, B, row_ptr, col_idx, G, X, dvals, s);
+}
+
+}  // namespace spx
