@@ -94,6 +94,18 @@ __global__ __launch_bounds__(kBlock) void k_ptr_from_sorted(const uint32_t* __re
     for (int64_t j = prev + 1; j <= cur; ++j) ptr[j] = (int32_t)p;
 }
 
+// *descends = 1 if some row's column indices do not ascend (rows[k]: the row
+// of entry k)
+__global__ __launch_bounds__(kBlock) void k_ascend(int64_t nnz, const int32_t* __restrict__ rows,
+                                                   const int32_t* __restrict__ col_idx,
+                                                   uint32_t* __restrict__ descends) {
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    bool bad = false;
+    for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k + 1 < nnz; k += stride)
+        bad |= rows[k] == rows[k + 1] && col_idx[k] >= col_idx[k + 1];
+    if (__ballot(bad) && lane_id() == 0) *descends = 1u;
+}
+
 // validation: row_ptr monotone with row_ptr[0] = 0 and row_ptr[m] = nnz,
 // col_idx in range; sets bit 0 / bit 1 of *bad
 __global__ __launch_bounds__(kBlock) void k_validate_csr(const int32_t* __restrict__ row_ptr, int32_t m,
@@ -195,9 +207,11 @@ struct spx_matrix {
     EllMat ell;
     DiaMat dia;
     Csr5Mat c5;
-    // first entry of every column past each row block of the LDS slabs (dX;
-    // allocated on first use)
+    // where each column (row) enters each row (column) block of the LDS slabs
+    // of dX (dvals); allocated on first use
     int32_t* slab_part = nullptr;
+    int32_t* dots_part = nullptr;
+    bool cols_ascend = false;  // the column indices ascend within every row (F32 and F64 handles only)
     // column-sorted copy of the renumbered CSR for the balanced SpMV with
     // 2048-item tiles (kept with the renumbered copy when n <= 2^21)
     TileSorted ts;
@@ -494,7 +508,8 @@ extern "C" spx_status spx_matrix_destroy(spx_matrix* H) {
                     H->part[0][0], H->part[0][1], H->part[1][0], H->part[1][1], H->dev_sel, H->bws,
                     H->units, H->split_rows, H->bfs_front[0], H->bfs_front[1], H->bfs_y, H->drv_count,
                     H->bfs_bits[0], H->bfs_bits[1], H->pr_W, H->pr_r, H->pr_y, H->pr_xidx, H->pr_xval,
-                    H->pr_xd[0], H->pr_xd[1], H->pr_p, H->pr_bad, H->cnt_dev, H->slab_part};
+                    H->pr_xd[0], H->pr_xd[1], H->pr_p, H->pr_bad, H->cnt_dev, H->slab_part,
+                    H->dots_part};
     for (void* p : ptrs)
         if (p) hipFree(p);
     sell_free(&H->sell);
@@ -535,6 +550,7 @@ static spx_status build_csc(spx_matrix* H, hipStream_t s) {
     uint32_t *keys = nullptr, *keys2 = nullptr, *vals2 = nullptr;
     int32_t* rws = nullptr;
     int32_t* rows = nullptr;
+    uint32_t descents = 1;
     const size_t rw = radix_ws_elems(nnz);
     if (hipMalloc((void**)&keys, nnz * 4) != hipSuccess || hipMalloc((void**)&keys2, nnz * 4) != hipSuccess ||
         hipMalloc((void**)&vals2, nnz * 4) != hipSuccess || hipMalloc((void**)&rws, rw * 4) != hipSuccess ||
@@ -561,9 +577,19 @@ static spx_status build_csc(spx_matrix* H, hipStream_t s) {
         if (st) break;
         st = gather_perm(rows, H->perm, H->row_idx, nnz, 4, s);
         if (st) break;
+        if (A.dtype == SPX_F32 || A.dtype == SPX_F64) {
+            st = fill_u32((uint32_t*)rws, 0u, 1, s);
+            if (st) break;
+            k_ascend<<<grid, kBlock, 0, s>>>(nnz, rows, A.col_idx, (uint32_t*)rws);
+            if (hipMemcpyAsync(&descents, rws, 4, hipMemcpyDeviceToHost, s) != hipSuccess) {
+                st = fail(SPX_ERR_HIP, "column order");
+                break;
+            }
+        }
         if (vs > 0) st = gather_perm(A.vals, H->perm, H->vals_csc, nnz, vs, s);
         if (st) break;
         if (hipStreamSynchronize(s) != hipSuccess) st = fail(SPX_ERR_HIP, "transpose sync");
+        H->cols_ascend = descents == 0;
     } while (0);
     hipFree(keys);
     hipFree(keys2);
@@ -1841,34 +1867,55 @@ extern "C" spx_status spmv_csr_batch(spx_matrix* H, int32_t B, const void* X, vo
     return launch_spmv_batch(A.row_ptr, A.col_idx, A.vals, A.m, A.n, A.dtype, B, X, Y, ws, (hipStream_t)stream);
 }
 
+// A table of block bounds, built on first use (the pattern of A is fixed).
+static spx_status ensure_part(int32_t** part, int32_t nseg, const SlabBlocks& b, const int32_t* seg_ptr,
+                              const int32_t* idx, hipStream_t s) {
+    if (*part || b.nblk == 1) return SPX_OK;
+    int32_t* p = nullptr;
+    if (hipMalloc((void**)&p, (size_t)b.nblk * nseg * 4) != hipSuccess)
+        return fail(SPX_ERR_ALLOC, "block bounds: allocation failed");
+    const spx_status st = slab_part_build(nseg, b, seg_ptr, idx, p, s);
+    if (st != SPX_OK) {
+        hipFree(p);
+        return st;
+    }
+    *part = p;
+    return SPX_OK;
+}
+
 // dX = G A over the CSC copy (its rows ascend within a column, so G's rows
 // of length m can pass through LDS in blocks)
+static bool dx_in_slabs(const spx_matrix* H, int32_t B) {
+    const spx_csr& A = H->csr;
+    const SlabBlocks b = slab_blocks(A.m);
+    return slab_gather_fits(A.n, A.m, A.nnz, B, A.dtype, &b);
+}
+
 static spx_status run_dx(spx_matrix* H, int32_t B, const void* G, void* dX, hipStream_t s) {
     const spx_csr& A = H->csr;
-    const SlabBlocks blocks = slab_blocks(A.m);
-    if (slab_gather_fits(A.n, A.m, A.nnz, B, A.dtype, &blocks)) {
-        if (blocks.nblk > 1 && !H->slab_part) {
-            int32_t* part = nullptr;
-            if (hipMalloc((void**)&part, (size_t)blocks.nblk * A.n * 4) != hipSuccess)
-                return fail(SPX_ERR_ALLOC, "dX: block table allocation failed");
-            const spx_status st = slab_part_build(A.n, blocks, H->col_ptr, H->row_idx, part, s);
-            if (st != SPX_OK) {
-                hipFree(part);
-                return st;
-            }
-            H->slab_part = part;
-        }
-        return slab_gather(A.n, A.m, A.nnz, B, A.dtype, &blocks, H->col_ptr, H->slab_part, H->row_idx, H->vals_csc, G, dX, s);
+    if (dx_in_slabs(H, B)) {
+        const SlabBlocks b = slab_blocks(A.m);
+        SPX_TRY(ensure_part(&H->slab_part, A.n, b, H->col_ptr, H->row_idx, s));
+        return slab_gather(A.n, A.m, A.nnz, B, A.dtype, &b, H->col_ptr, H->slab_part, H->row_idx, H->vals_csc, G, dX,
+                           s);
     }
     SPX_TRY(ensure_ws(H, grad_ws_bytes(A.m, A.n, B, A.dtype)));
     Arena ws(H->ws, H->ws_bytes);
     return launch_dx(H->col_ptr, H->row_idx, H->vals_csc, A.m, A.n, A.dtype, B, G, dX, ws, s);
 }
 
+static bool dvals_in_slabs(const spx_matrix* H, int32_t B) {
+    const spx_csr& A = H->csr;
+    return H->cols_ascend && slab_dots_fits(A.m, A.n, A.nnz, B, A.dtype);
+}
+
 static spx_status run_dvals(spx_matrix* H, int32_t B, const void* G, const void* X, void* dvals, hipStream_t s) {
     const spx_csr& A = H->csr;
-    if (slab_sddmm_fits(A.m, A.n, A.nnz, B, A.dtype))
-        return slab_sddmm(A.m, A.n, A.nnz, B, A.dtype, A.row_ptr, A.col_idx, G, X, dvals, s);
+    if (dvals_in_slabs(H, B)) {
+        const SlabBlocks b = dots_blocks(A.n);
+        SPX_TRY(ensure_part(&H->dots_part, A.m, b, A.row_ptr, A.col_idx, s));
+        return slab_dots(A.m, A.n, A.nnz, B, A.dtype, A.row_ptr, H->dots_part, A.col_idx, G, X, dvals, s);
+    }
     SPX_TRY(ensure_ws(H, grad_ws_bytes(A.m, A.n, B, A.dtype)));
     Arena ws(H->ws, H->ws_bytes);
     return launch_dvals(A.row_ptr, A.col_idx, A.m, A.n, A.nnz, A.dtype, B, G, X, dvals, ws, s);
@@ -1899,10 +1946,7 @@ extern "C" spx_status spx_backward(spx_matrix* H, int32_t B, const void* G, cons
     const int dt = A.dtype;
     if (dt != SPX_F32 && dt != SPX_F64) return fail(SPX_ERR_DTYPE, "backward supports F32 and F64");
     hipStream_t s = (hipStream_t)stream;
-    const SlabBlocks blocks = slab_blocks(A.m);
-    const bool dx_slab = dX && slab_gather_fits(A.n, A.m, A.nnz, B, dt, &blocks);
-    const bool dv_slab = dvals && slab_sddmm_fits(A.m, A.n, A.nnz, B, dt);
-    if (dx_slab || dv_slab) {
+    if ((dX && dx_in_slabs(H, B)) || (dvals && dvals_in_slabs(H, B))) {
         // a gradient that does not go through LDS makes its own B-minor copies
         if (dX) SPX_TRY(run_dx(H, B, G, dX, s));
         return dvals ? run_dvals(H, B, G, X, dvals, s) : SPX_OK;

@@ -318,23 +318,27 @@ spx_status launch_dvals(const int32_t* row_ptr, const int32_t* col_idx, int32_t 
                         int32_t nnz, int dtype, int32_t B, const void* G, const void* X,
                         void* dvals, Arena& ws, hipStream_t s);
 // The same products with the dense operand held in LDS, a slab of its
-// columns at a time (slab.hip). blocks (null: one slab of all N columns, any
-// index order) cuts the operand's N columns for segments whose indices
-// ascend, with part[blk * nseg + j] as k_slab_part writes it.
+// columns at a time (slab.hip). SlabBlocks cuts an operand's N columns into
+// nblk blocks of cb for segments whose indices ascend; part (nblk * nseg
+// entries, slab_part_build) holds where each segment enters each block.
+// slab_gather with blocks null: one slab of all columns, any index order.
 struct SlabBlocks {
     int32_t nblk = 1;
-    int32_t cb = 0;  // columns per slab
+    int32_t cb = 0;
 };
-SlabBlocks slab_blocks(int32_t N);
-spx_status slab_part_build(int32_t n, const SlabBlocks& b, const int32_t* col_ptr, const int32_t* row_idx,
+SlabBlocks slab_blocks(int32_t N);  // of slab_gather
+SlabBlocks dots_blocks(int32_t n);  // of slab_dots
+spx_status slab_part_build(int32_t nseg, const SlabBlocks& b, const int32_t* seg_ptr, const int32_t* idx,
                            int32_t* part, hipStream_t s);
 bool slab_gather_fits(int32_t nseg, int32_t N, int32_t nnz, int32_t B, int dtype, const SlabBlocks* blocks);
-spx_status slab_gather(int32_t nseg, int32_t N, int32_t nnz, int32_t B, int dtype, const SlabBlocks* blocks, const int32_t* seg_ptr,
-                       const int32_t* part, const int32_t* idx, const void* vals, const void* in, void* out,
-                       hipStream_t s);
-bool slab_sddmm_fits(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype);
-spx_status slab_sddmm(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype, const int32_t* row_ptr, const int32_t* col_idx,
-                      const void* G, const void* X, void* dvals, hipStream_t s);
+spx_status slab_gather(int32_t nseg, int32_t N, int32_t nnz, int32_t B, int dtype, const SlabBlocks* blocks,
+                       const int32_t* seg_ptr, const int32_t* part, const int32_t* idx, const void* vals,
+                       const void* in, void* out, hipStream_t s);
+// dvals for a CSR whose columns ascend within every row
+bool slab_dots_fits(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype);
+spx_status slab_dots(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype, const int32_t* row_ptr,
+                     const int32_t* part, const int32_t* col_idx, const void* G, const void* X, void* dvals,
+                     hipStream_t s);
 // B dense rows of length n -> CSR-of-vectors (vec_ptr[B+1], idx, val);
 // ws_i32: scan_ws_elems(B + 1) int32
 spx_status dense_rows_to_sparse(int32_t B, int32_t n, int dtype, const void* X, int32_t* vec_ptr,

@@ -4,7 +4,7 @@
 //   k_slab_gather  out[b, j]  = sum over the entries k of segment j of
 //                  vals[k] * in[b, idx[k]]: the forward (segments = rows of A,
 //                  in = X) and dX (segments = columns, in = G)
-//   k_slab_sddmm   dvals[k] = sum_b G[b, row k] * X[b, col k]
+//   k_slab_dots    dvals[k] = sum_b G[b, row k] * X[b, col k]
 //
 // Per stored entry and batch row these need one value of the dense operand,
 // at a random place. Gathering it from L2 (a B-minor copy, a row of B values
@@ -68,12 +68,6 @@ constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;      // quad_perm
 constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;    // rotations of a row of 16 lanes
 constexpr int kDppBcast = 0x150;                     // row_newbcast: lane n of the row to all
 
-// row[i] = lane i's value of the row of 16 lanes
-template <typename T, int N, int... I>
-__device__ __forceinline__ void row_bcast(T v, T (&row)[N], std::integer_sequence<int, I...>) {
-    ((row[I] = dpp<kDppBcast + I>(v)), ...);
-}
-
 // Buffer loads: a 32-bit byte offset from a base in scalar registers, and 0
 // for what lies past the size (no branch around the load).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
@@ -88,7 +82,7 @@ __device__ __forceinline__ T buffer_value(__amdgpu_buffer_rsrc_t r, int at) {
 }
 
 template <typename T>
-struct SlabVec {
+struct alignas(16) SlabVec {
     static constexpr int E = 16 / sizeof(T);  // values per 16-byte LDS read
     T v[E];
 };
@@ -221,6 +215,36 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab_gather(int32_t nseg, int3
     const auto bidx = buffer_of(idx, nnz * 4), bval = buffer_of(vals, nnz * (int)sizeof(T));
     SlabLoad<T, W> next;
     next.load(in, N, B, b0, 0, min(cb, N));
+    // the wave's walk, slab after slab, kSlabGroups segments at a time: the
+    // bounds run two rounds ahead and the entries one step, across slabs too
+    // (only the LDS reads depend on the slab)
+    int pblk = 0, pr = 0;  // the round whose bounds are read next
+    auto advance = [&](int& k0, int& k1) {
+        const int s = pr * kSlabGroups + s0;
+        k0 = k1 = 0;
+        if (pblk < nblk && s < ns) {
+            const int64_t j = j0 + s;
+            k0 = pblk > 0 ? part[(int64_t)pblk * nseg + j] : seg_ptr[j];
+            k1 = pblk + 1 < nblk ? part[(int64_t)(pblk + 1) * nseg + j] : seg_ptr[j + 1];
+        }
+        if (++pr == rounds) {
+            pr = 0;
+            ++pblk;
+        }
+    };
+    auto fetch = [&](int k, int (&c)[kSlabU], T (&v)[kSlabU]) {
+#pragma unroll
+        for (int u = 0; u < kSlabU; ++u) {
+            c[u] = buffer_value<int>(bidx, (k + g + u * kSlabLanes) * 4);
+            v[u] = buffer_value<T>(bval, (k + g + u * kSlabLanes) * (int)sizeof(T));
+        }
+    };
+    int ka, kb, kc, kd;
+    advance(ka, kb);
+    advance(kc, kd);
+    int c[kSlabU];
+    T v[kSlabU];
+    fetch(ka, c, v);
     for (int blk = 0; blk < nblk; ++blk) {
         const int32_t c0 = blk * cb;
         const int32_t width = min(cb, N - c0);
@@ -228,31 +252,9 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab_gather(int32_t nseg, int3
         next.store(slab, width);
         __syncthreads();
         if (blk + 1 < nblk) next.load(in, N, B, b0, c0 + cb, min(cb, N - c0 - cb));
-        auto bounds = [&](int r, int& k0, int& k1) {
-            const int s = r * kSlabGroups + s0;
-            k0 = k1 = 0;
-            if (s < ns) {
-                const int64_t j = j0 + s;
-                k0 = blk > 0 ? part[(int64_t)blk * nseg + j] : seg_ptr[j];
-                k1 = blk + 1 < nblk ? part[(int64_t)(blk + 1) * nseg + j] : seg_ptr[j + 1];
-            }
-        };
-        auto fetch = [&](int k, int (&c)[kSlabU], T (&v)[kSlabU]) {
-#pragma unroll
-            for (int u = 0; u < kSlabU; ++u) {
-                c[u] = buffer_value<int>(bidx, (k + g + u * kSlabLanes) * 4);
-                v[u] = buffer_value<T>(bval, (k + g + u * kSlabLanes) * (int)sizeof(T));
-            }
-        };
-        int ka, kb, kc, kd;
-        bounds(0, ka, kb);
-        bounds(1, kc, kd);
-        int c[kSlabU];
-        T v[kSlabU];
-        fetch(ka, c, v);
         for (int r = 0; r < rounds; ++r) {
             int ke, kf;
-            bounds(r + 2, ke, kf);
+            advance(ke, kf);
             T acc[W][E];
 #pragma unroll
             for (int w = 0; w < W; ++w)
@@ -302,130 +304,192 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab_gather(int32_t nseg, int3
     }
 }
 
-// Workgroup = rows [tile * st, + st) of A, all batch rows, NB at a time. Each
-// entry's sum over the batch rows stays with one thread, which adds a
-// chunk's part to dvals[k] (its own store of the last chunk, from L2).
-template <typename T, int W>
-__global__ __launch_bounds__(kSlabThreads) void k_slab_sddmm(int32_t m, int32_t n, int32_t nnz, int32_t B,
-                                                             int32_t st,
-                                                             const int32_t* __restrict__ row_ptr,
-                                                             const int32_t* __restrict__ col_idx,
-                                                             const T* __restrict__ G, const T* __restrict__ X,
-                                                             T* __restrict__ dvals) {
-    constexpr int E = SlabVec<T>::E, NB = W * E;
-    extern __shared__ __align__(16) char s_raw[];
-    const int32_t j0 = (int32_t)xcd_tile(blockIdx.x, gridDim.x) * st;
-    const int32_t ns = min(st, m - j0);
-    char* slab = s_raw;
+// dvals, the columns cut instead of the batch: a workgroup's slab holds all
+// batch rows of a chunk (LPE lanes of E values: 64, 16 or 4 FP32 ones) for
+// cols = kDotsBytes / (16 LPE) columns, so that every stored entry is read
+// once, by the workgroup (rows [tile * st, + st), its block of columns), and
+// its gradient written once. 16 lanes (a DPP row) take a row's entries of
+// the block, 16 at a time, 16 / LPE per step: entry l of the 16 is loaded by
+// lane l, its LDS address goes to the lanes of its group by a DPP broadcast,
+// each lane multiplies its batch rows' values of G (in registers for the
+// row), and a fold leaves entry l's sum with lane l. The column's 16-byte
+// pieces are permuted by its number (dots_at), so that neither the slab's
+// writes (a wave writes one piece of 64 columns) nor its reads (LPE = 16: the
+// 256 bytes of 4 columns) meet on banks. part[i * m + r] is the first entry
+// of row r at or past column i * kDotsGrain (columns ascend within a row).
+constexpr int kDotsBytes = 128 * 1024;
+constexpr int kDotsGrain = 512;
+
+template <int LPE>
+constexpr int dots_cols() {
+    return kDotsBytes / (16 * LPE);
+}
+
+// byte offset of piece 0 of column c; piece i is at the offset xor i * 16
+template <int LPE>
+__device__ __forceinline__ int dots_at(int c) {
+    return c * (16 * LPE) ^ (((c / (16 / LPE)) & (LPE - 1)) << 4);
+}
+
+// v[t] summed over the LPE lanes of each group, for the 16 / P entries t of
+// every lane's group; lane l of the row ends with entry l's sum.
+template <int LPE, typename T>
+__device__ __forceinline__ T dots_fold(const T (&v)[LPE]) {
     const int lane = lane_id();
-    const int g = lane % kSlabLanes, par16 = (lane & 1) << 4;
+    if constexpr (LPE == 1) {
+        return v[0];
+    } else {
+        const bool h0 = lane & 1, h1 = lane & 2;
+        T out = (T)0;
+#pragma unroll
+        for (int q = 0; q < LPE / 4; ++q) {
+            const T a = (h0 ? v[4 * q + 1] : v[4 * q]) + dpp<kDppXor1>(h0 ? v[4 * q] : v[4 * q + 1]);
+            const T b = (h0 ? v[4 * q + 3] : v[4 * q + 2]) + dpp<kDppXor1>(h0 ? v[4 * q + 2] : v[4 * q + 3]);
+            T s = (h1 ? b : a) + dpp<kDppXor2>(h1 ? a : b);
+            if constexpr (LPE == 16) {
+                s += dpp<kDppRor4>(s);
+                s += dpp<kDppRor8>(s);
+                out = ((lane >> 2) & 3) == q ? s : out;
+            } else {
+                out = s;
+            }
+        }
+        return out;
+    }
+}
+
+// lane t of the group's loaded word, to all its lanes
+template <int LPE, int t>
+__device__ __forceinline__ int dots_bcast(int v) {
+    if constexpr (LPE == 16) return dpp_word<kDppBcast + t>(v);
+    if constexpr (LPE == 4) return dpp_word<0x55 * t>(v);
+    return v;
+}
+
+template <typename T, int LPE, int... t>
+__device__ __forceinline__ T dots_step(const char* slab, int at, int mine, const T (&gv)[SlabVec<T>::E],
+                                       std::integer_sequence<int, t...>) {
+    constexpr int E = SlabVec<T>::E;
+    T v[LPE];
+    auto one = [&](int tt, int a) {
+        const SlabVec<T> x = *(const SlabVec<T>*)(slab + (a ^ mine));
+        T s = gv[0] * x.v[0];
+#pragma unroll
+        for (int e = 1; e < E; ++e) s = fma_t(gv[e], x.v[e], s);
+        v[tt] = s;
+    };
+    (one(t, dots_bcast<LPE, t>(at)), ...);
+    return dots_fold<LPE, T>(v);
+}
+
+template <typename T, int LPE>
+__global__ __launch_bounds__(kSlabThreads) void k_slab_dots(int32_t m, int32_t n, int32_t nnz, int32_t B, int32_t st,
+                                                            int32_t nblk, const int32_t* __restrict__ row_ptr,
+                                                            const int32_t* __restrict__ part,
+                                                            const int32_t* __restrict__ col_idx,
+                                                            const T* __restrict__ G, const T* __restrict__ X,
+                                                            T* __restrict__ dvals) {
+    constexpr int E = SlabVec<T>::E, NB = LPE * E;
+    constexpr int cols = dots_cols<LPE>(), grains = cols / kDotsGrain;
+    extern __shared__ __align__(16) char s_raw[];
+    char* slab = s_raw;
+    const int64_t t = xcd_tile(blockIdx.x, gridDim.x);
+    const int32_t tile = (int32_t)(t / nblk), blk = (int32_t)(t % nblk);
+    const int32_t j0 = tile * st, c0 = blk * cols;
+    const int32_t ns = min(st, m - j0), width = min(cols, n - c0);
+    const int g = lane_id() % kSlabLanes;
+    const int mine = (g % LPE) << 4;
     const int s0 = threadIdx.x / kSlabLanes;
     const int rounds = (ns + kSlabGroups - 1) / kSlabGroups;
     const auto bidx = buffer_of(col_idx, nnz * 4);
-    SlabLoad<T, W> next;
-    next.load(X, n, B, 0, 0, n);
-    for (int b0 = 0; b0 < B; b0 += NB) {
+    for (int32_t b0 = 0; b0 < B; b0 += NB) {
         if (b0 > 0) __syncthreads();
-        next.store(slab, n);
-        __syncthreads();
-        if (b0 + NB < B) next.load(X, n, B, b0 + NB, 0, n);
-        // row bounds, and the row's value of G of batch row b0 + g % NB
-        auto bounds = [&](int r, int& k0, int& k1, T& gv) {
+        // the slab: a thread takes E batch rows of one column at a time (the
+        // lanes of a wave 64 neighbouring columns), all loads before the stores
+        constexpr int kPer = LPE * cols / kSlabThreads;
+        SlabVec<T> x[kPer];
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) {
+            const int q = p * kSlabThreads + (int)threadIdx.x;
+            const int c = q % cols, i = __builtin_amdgcn_readfirstlane(q / cols);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int b = b0 + i * E + e;
+                x[p].v[e] = buffer_value<T>(buffer_of(X + (int64_t)b * n + c0, b < B ? width * (int)sizeof(T) : 0),
+                                            c * (int)sizeof(T));
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) {
+            const int q = p * kSlabThreads + (int)threadIdx.x;
+            const int c = q % cols, i = q / cols;
+            if (c < width) *(SlabVec<T>*)(slab + (dots_at<LPE>(c) ^ (i << 4))) = x[p];
+        }
+        // a row's bounds in the block and its values of G, one round ahead;
+        // its first 16 column indices too
+        auto bounds = [&](int r, int& k0, int& k1, T (&gv)[E]) {
             const int s = r * kSlabGroups + s0;
             k0 = k1 = 0;
-            gv = (T)0;
-            if (s < ns) {
-                k0 = row_ptr[j0 + s];
-                k1 = row_ptr[j0 + s + 1];
-                const int b = b0 + g % NB;
-                if (b < B) gv = G[(int64_t)b * m + j0 + s];
-            }
-        };
-        const auto bdv = buffer_of(dvals, b0 > 0 ? nnz * (int)sizeof(T) : 0);  // the first chunk adds to 0
-        auto fetch = [&](int k, int (&c)[kSlabU], T (&d)[kSlabU]) {
 #pragma unroll
-            for (int u = 0; u < kSlabU; ++u) {
-                c[u] = buffer_value<int>(bidx, (k + g + u * kSlabLanes) * 4);
-                d[u] = buffer_value<T>(bdv, (k + g + u * kSlabLanes) * (int)sizeof(T));
+            for (int e = 0; e < E; ++e) gv[e] = (T)0;
+            if (s < ns) {
+                const int64_t j = j0 + s;
+                const int32_t p = blk * grains;
+                k0 = blk > 0 ? part[p * (int64_t)m + j] : row_ptr[j];
+                k1 = blk + 1 < nblk ? part[(p + grains) * (int64_t)m + j] : row_ptr[j + 1];
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const int b = b0 + (g % LPE) * E + e;
+                    if (b < B) gv[e] = G[(int64_t)b * m + j];
+                }
             }
         };
         int ka, kb, kc, kd;
-        T ga, gc;
+        T ga[E], gc[E];
         bounds(0, ka, kb, ga);
         bounds(1, kc, kd, gc);
-        int c[kSlabU];
-        T d[kSlabU];
-        fetch(ka, c, d);
+        int c = buffer_value<int>(bidx, (ka + g) * 4);
+        __syncthreads();
         for (int r = 0; r < rounds; ++r) {
             int ke, kf;
-            T ge;
+            T ge[E];
             bounds(r + 2, ke, kf, ge);
-            // lane b of the 16 holds batch row b0 + b: all NB to every lane,
-            // the half of the lane's parity first
-            T row[NB];
-            row_bcast(ga, row, std::make_integer_sequence<int, NB>{});
-            T gw[W][E];
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                if constexpr (W == 2) {
-                    gw[0][e] = par16 ? row[E + e] : row[e];
-                    gw[1][e] = par16 ? row[e] : row[E + e];
-                } else {
-                    gw[0][e] = row[e];
-                }
-            }
             int k = ka;
             bool more;
             do {
-                more = __any(k + kSlabStep < kb);  // uniform over the wave
-                SlabVec<T> p[kSlabU][W];
-                T old[kSlabU];
-#pragma unroll
-                for (int u = 0; u < kSlabU; ++u) {
-                    const bool on = k + g + u * kSlabLanes < kb;
-                    slab_read<T, W>(slab, slab_at<W>(on ? c[u] : n, par16), p[u]);
-                    old[u] = d[u];
-                }
-                fetch(more ? k + kSlabStep : kc, c, d);
-#pragma unroll
-                for (int u = 0; u < kSlabU; ++u) {
-                    T s[W];
-#pragma unroll
-                    for (int w = 0; w < W; ++w) {
-                        s[w] = gw[w][0] * p[u][w].v[0];
-#pragma unroll
-                        for (int e = 1; e < E; ++e) s[w] = fma_t(gw[w][e], p[u][w].v[e], s[w]);
-                    }
-                    T sum = s[0];
-                    if constexpr (W == 2) sum += s[1];
-                    const int q = k + g + u * kSlabLanes;
-                    if (q < kb) dvals[q] = old[u] + sum;
-                }
-                k += kSlabStep;
+                more = __any(k + kSlabLanes < kb);  // uniform over the wave
+                const bool on = k + g < kb;
+                const int at = on ? dots_at<LPE>(c - c0) : 0;
+                c = buffer_value<int>(bidx, ((more ? k + kSlabLanes : kc) + g) * 4);
+                const T s = dots_step<T, LPE>(slab, at, mine, ga, std::make_integer_sequence<int, LPE>{});
+                if (on) dvals[k + g] = b0 > 0 ? dvals[k + g] + s : s;
+                k += kSlabLanes;
             } while (more);
             ka = kc;
             kb = kd;
-            ga = gc;
             kc = ke;
             kd = kf;
-            gc = ge;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                ga[e] = gc[e];
+                gc[e] = ge[e];
+            }
         }
     }
 }
 
-// part[blk * n + j] for blk in [1, nblk): the first entry of column j whose
-// row is at or past blk * cb (rows ascend within a column of the CSC copy).
-__global__ __launch_bounds__(kBlock) void k_slab_part(int32_t n, int32_t nblk, int32_t cb,
-                                                      const int32_t* __restrict__ col_ptr,
-                                                      const int32_t* __restrict__ row_idx,
-                                                      int32_t* __restrict__ part) {
+// part[blk * nseg + j]: the first entry of segment j whose index is at or
+// past blk * cb (the indices ascend within a segment).
+__global__ __launch_bounds__(kBlock) void k_slab_part(int32_t nseg, int32_t nblk, int32_t cb,
+                                                      const int32_t* __restrict__ seg_ptr,
+                                                      const int32_t* __restrict__ idx, int32_t* __restrict__ part) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= (int64_t)n * nblk) return;
-    const int32_t blk = (int32_t)(i / n), j = (int32_t)(i % n);
-    int lo = col_ptr[j], hi = col_ptr[j + 1];
+    if (i >= (int64_t)nseg * nblk) return;
+    const int32_t blk = (int32_t)(i / nseg), j = (int32_t)(i % nseg);
+    int lo = seg_ptr[j], hi = seg_ptr[j + 1];
     while (lo < hi) {
         const int mid = lo + (hi - lo) / 2;
-        if (row_idx[mid] < blk * cb)
+        if (idx[mid] < blk * cb)
             lo = mid + 1;
         else
             hi = mid;
@@ -441,10 +505,17 @@ SlabBlocks slab_blocks(int32_t N) {
     return b;
 }
 
-spx_status slab_part_build(int32_t n, const SlabBlocks& b, const int32_t* col_ptr, const int32_t* row_idx,
+SlabBlocks dots_blocks(int32_t n) {
+    SlabBlocks b;
+    b.nblk = (int32_t)std::max<int64_t>(1, ceil_div(n, kDotsGrain));
+    b.cb = kDotsGrain;
+    return b;
+}
+
+spx_status slab_part_build(int32_t nseg, const SlabBlocks& b, const int32_t* seg_ptr, const int32_t* idx,
                            int32_t* part, hipStream_t s) {
-    k_slab_part<<<(unsigned)ceil_div((int64_t)n * b.nblk, kBlock), kBlock, 0, s>>>(n, b.nblk, b.cb, col_ptr, row_idx,
-                                                                                   part);
+    k_slab_part<<<(unsigned)ceil_div((int64_t)nseg * b.nblk, kBlock), kBlock, 0, s>>>(nseg, b.nblk, b.cb, seg_ptr,
+                                                                                      idx, part);
     SPX_HIP(hipGetLastError());
     return SPX_OK;
 }
@@ -473,10 +544,17 @@ bool slab_gather_fits(int32_t nseg, int32_t N, int32_t nnz, int32_t B, int dtype
     return (double)nnz >= kSlabMinEntries * (double)nseg * nblk;
 }
 
-bool slab_sddmm_fits(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype) {
+// lanes that hold an entry's batch rows
+static int dots_lanes(int32_t B, int dtype) {
+    const int E = dtype == SPX_F64 ? 2 : 4;
+    return B <= E ? 1 : B <= 4 * E ? 4 : 16;
+}
+
+bool slab_dots_fits(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype) {
     if (m <= 0 || n <= 0 || B <= 0 || !slab_addresses(nnz, dtype)) return false;
-    if ((dtype == SPX_F64 ? slab_width<double>(n, B) : slab_width<float>(n, B)) == 0) return false;
-    return (double)nnz >= kSlabMinEntries * (double)m;
+    const int64_t nblk = ceil_div(n, kDotsBytes / (16 * dots_lanes(B, dtype)));
+    // and the table of bounds stays below the index array
+    return (double)nnz >= kSlabMinEntries * (double)m * nblk && nnz >= (int64_t)m * ceil_div(n, kDotsGrain);
 }
 
 static spx_status slab_cus(int* cus) {
@@ -528,31 +606,42 @@ spx_status slab_gather(int32_t nseg, int32_t N, int32_t nnz, int32_t B, int dtyp
     return slab_gather_t<double>(nseg, N, nnz, B, blocks, seg_ptr, part, idx, vals, in, out, s);
 }
 
-template <typename T, int W>
-static spx_status slab_sddmm_w(int32_t m, int32_t n, int32_t nnz, int32_t B, const int32_t* row_ptr, const int32_t* col_idx,
-                               const void* G, const void* X, void* dvals, hipStream_t s) {
+template <typename T, int LPE>
+static spx_status slab_dots_l(int32_t m, int32_t n, int32_t nnz, int32_t B, const int32_t* row_ptr,
+                              const int32_t* part, const int32_t* col_idx, const void* G, const void* X, void* dvals,
+                              hipStream_t s) {
     int cus = 0;
     SPX_TRY(slab_cus(&cus));
-    const int32_t st = (int32_t)std::max<int64_t>(kSlabGroups, ceil_div(m, cus));
-    const size_t lds = (size_t)(n + 1) * 16 * W;
-    SPX_HIP(hipFuncSetAttribute((const void*)k_slab_sddmm<T, W>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    k_slab_sddmm<T, W><<<(unsigned)ceil_div(m, st), kSlabThreads, lds, s>>>(m, n, nnz, B, st, row_ptr, col_idx,
-                                                                            (const T*)G, (const T*)X, (T*)dvals);
+    const int32_t nblk = (int32_t)ceil_div(n, dots_cols<LPE>());
+    const int32_t st = (int32_t)std::max<int64_t>(kSlabGroups, ceil_div(m, std::max(1, cus / nblk)));
+    const int64_t grid = ceil_div(m, st) * nblk;
+    if (grid > 0x7fffffff) return fail(SPX_ERR_SHAPE, "dvals: too many blocks");
+    const size_t lds = (size_t)std::min(n, dots_cols<LPE>()) * 16 * LPE;
+    SPX_HIP(hipFuncSetAttribute((const void*)k_slab_dots<T, LPE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kDotsBytes));
+    // the permuted pieces of the last columns stay within their column
+    k_slab_dots<T, LPE><<<(unsigned)grid, kSlabThreads, lds, s>>>(m, n, nnz, B, st, nblk, row_ptr, part, col_idx,
+                                                                  (const T*)G, (const T*)X, (T*)dvals);
     SPX_HIP(hipGetLastError());
     return SPX_OK;
 }
 
 template <typename T>
-static spx_status slab_sddmm_t(int32_t m, int32_t n, int32_t nnz, int32_t B, const int32_t* row_ptr, const int32_t* col_idx,
-                               const void* G, const void* X, void* dvals, hipStream_t s) {
-    if (slab_width<T>(n, B) == 2) return slab_sddmm_w<T, 2>(m, n, nnz, B, row_ptr, col_idx, G, X, dvals, s);
-    return slab_sddmm_w<T, 1>(m, n, nnz, B, row_ptr, col_idx, G, X, dvals, s);
+static spx_status slab_dots_t(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype, const int32_t* row_ptr,
+                              const int32_t* part, const int32_t* col_idx, const void* G, const void* X, void* dvals,
+                              hipStream_t s) {
+    switch (dots_lanes(B, dtype)) {
+        case 1: return slab_dots_l<T, 1>(m, n, nnz, B, row_ptr, part, col_idx, G, X, dvals, s);
+        case 4: return slab_dots_l<T, 4>(m, n, nnz, B, row_ptr, part, col_idx, G, X, dvals, s);
+        default: return slab_dots_l<T, 16>(m, n, nnz, B, row_ptr, part, col_idx, G, X, dvals, s);
+    }
 }
 
-spx_status slab_sddmm(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype, const int32_t* row_ptr, const int32_t* col_idx,
-                      const void* G, const void* X, void* dvals, hipStream_t s) {
-    if (dtype == SPX_F32) return slab_sddmm_t<float>(m, n, nnz, B, row_ptr, col_idx, G, X, dvals, s);
-    return slab_sddmm_t<double>(m, n, nnz, B, row_ptr, col_idx, G, X, dvals, s);
+spx_status slab_dots(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype, const int32_t* row_ptr,
+                     const int32_t* part, const int32_t* col_idx, const void* G, const void* X, void* dvals,
+                     hipStream_t s) {
+    if (dtype == SPX_F32) return slab_dots_t<float>(m, n, nnz, B, dtype, row_ptr, part, col_idx, G, X, dvals, s);
+    return slab_dots_t<double>(m, n, nnz, B, dtype, row_ptr, part, col_idx, G, X, dvals, s);
 }
 
 }  // namespace spx

@@ -2,10 +2,13 @@
 wrong: operands of exactly one slab, one column more (several row blocks for
 dX, 16-byte columns for the forward), batch rows around a column's 8 FP32 or 4
 FP64 values, segments around the 64 groups and the 64-entry step, rows longer
-than several steps, empty rows, and unsorted column indices. Bounds: a result
+than several steps, empty rows, ascending and shuffled column indices (dvals
+blocks of 512, 2048 and 8192 columns). Bounds: a result
 is a chain of at most ceil(length / 16) + 4 fused additions per slab (1,100
 entries in a column here: 75 roundings of 2^-24, 4.5e-6 of sum |a x|), dvals
-one of B / 8 + 8, so the library's 1e-5 and 1e-12 hold."""
+one of at most 4 per 64 batch rows and a fold of 4, so the library's 1e-5 and
+1e-12 hold. dvals takes the slab path only where the columns ascend within
+every row: both kinds run."""
 import numpy as np
 import pytest
 
@@ -24,19 +27,20 @@ SHAPES = [
     (70, 8192, 150),   # one whole slab of 16-byte columns, rows of three steps
     (8195, 65, 9),     # dX over three row blocks of G
     (513, 300, 40),
+    (200, 1025, 100),  # dvals over three blocks of columns, the last of one
     (1, 9, 9),
 ]
 
 
-def _matrix(m, n, per_row, dtype, seed):
+def _matrix(m, n, per_row, dtype, seed, ascend=False):
     rng = np.random.default_rng(seed)
     A = synth.uniform_rows(m, n, per_row, seed, dtype=dtype) if per_row < n else synth.random_csr(m, n, 1.0, seed)
-    # some rows emptied, and the columns of every row shuffled
+    # some rows emptied, and the columns of every row shuffled or ascending
     keep = np.ones(A.nnz, bool)
     rows = np.repeat(np.arange(m), np.diff(A.row_ptr))
     if m > 4:
         keep[np.isin(rows, rng.choice(m, m // 20, replace=False))] = False
-    order = np.lexsort((rng.random(A.nnz), rows))
+    order = np.lexsort((np.asarray(A.col_idx) if ascend else rng.random(A.nnz), rows))
     order = order[keep[order]]
     rows = rows[order]
     ptr = np.zeros(m + 1, np.int32)
@@ -46,14 +50,15 @@ def _matrix(m, n, per_row, dtype, seed):
 
 @pytest.mark.parametrize("kind", ["f32", "f64"])
 @pytest.mark.parametrize("shape", range(len(SHAPES)))
-@pytest.mark.parametrize("B", [1, 4, 5, 9, 64])
-def test_slab_products_match_oracle(kind, shape, B):
+@pytest.mark.parametrize("B", [1, 4, 5, 9, 64, 70])
+@pytest.mark.parametrize("ascend", [False, True])
+def test_slab_products_match_oracle(kind, shape, B, ascend):
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     dt = np.float32 if kind == "f32" else np.float64
     m, n, per_row = SHAPES[shape]
-    A = _matrix(m, n, per_row, dt, 900 + shape)
+    A = _matrix(m, n, per_row, dt, 900 + shape, ascend)
     M = spx.Matrix.from_host(A)
     rng = np.random.default_rng(B)
     X = rng.standard_normal((B, n)).astype(dt)
