@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "csr_tile.hpp"
 #include "internal.hpp"
 
 namespace spx {
@@ -345,19 +346,36 @@ spx_status expand_rows(const int32_t* row_ptr, int32_t m, int32_t* rows_out, hip
     return SPX_OK;
 }
 
+// out[p] = in[perm[p]]. A workgroup takes kGatherTile consecutive positions
+// (its loads of a phase all in flight) and every XCD one contiguous range of
+// them: where the permutation transposes a matrix, a range of positions is a
+// range of columns and reads the same eighth of every row, which stays in the
+// XCD's L2 (3.3M entries of a 16384 x 4096 matrix: 23 us against 28 us when
+// the ranges went round the XCDs and every L2 saw all of in).
+constexpr int kGatherPer = 8;
+constexpr int kGatherTile = kBlock * kGatherPer;
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_gather_perm(const T* __restrict__ in,
                                                         const int32_t* __restrict__ perm,
                                                         T* __restrict__ out, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (; i < n; i += stride) out[i] = in[perm[i]];
+    const int64_t base = xcd_tile(blockIdx.x, gridDim.x) * kGatherTile + threadIdx.x;
+    int32_t q[kGatherPer];
+    T v[kGatherPer];
+#pragma unroll
+    for (int u = 0; u < kGatherPer; ++u) q[u] = base + u * kBlock < n ? __builtin_nontemporal_load(perm + base + u * kBlock) : 0;
+#pragma unroll
+    for (int u = 0; u < kGatherPer; ++u)
+        if (base + u * kBlock < n) v[u] = in[q[u]];
+#pragma unroll
+    for (int u = 0; u < kGatherPer; ++u)
+        if (base + u * kBlock < n) out[base + u * kBlock] = v[u];
 }
 
 spx_status gather_perm(const void* in, const int32_t* perm, void* out, int64_t n, int esize,
                        hipStream_t s) {
     if (n <= 0) return SPX_OK;
-    const int grid = (int)std::min<int64_t>(ceil_div(n, kBlock), 8192);
+    const unsigned grid = (unsigned)ceil_div(n, kGatherTile);
     if (esize == 4)
         k_gather_perm<uint32_t><<<grid, kBlock, 0, s>>>((const uint32_t*)in, perm, (uint32_t*)out, n);
     else if (esize == 8)
