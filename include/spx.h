@@ -403,14 +403,14 @@ spx_status spx_run_times(spx_matrix *H, double *out, int32_t cap, int32_t *count
  * column lengths) is computed on the device when its plan is column-major,
  * or for every vector when the loaded trees test nnz_s. Vectors whose plan
  * is row-major, or that hold at least 2 % of n, share passes over A in
- * groups of 64 (not for BOOL). The calls are a plan kernel, a queue scan,
- * three persistent phase kernels and, on a parallel branch beside the
- * second, the groups' walk of A, captured once into a HIP graph and
- * replayed while the arrays and B stay the same; nothing synchronizes
- * except a workspace reallocation.
+ * groups of 32 (16 for 8-byte values; not for BOOL); the others run
+ * column-major, a block of rows of Y at a time in LDS, or with device
+ * atomics for BOOL and where A has too few entries for that. The calls
+ * are kernels on the given stream; nothing synchronizes except the first
+ * call on a handle and a workspace reallocation.
  * total_nnz_x (host) is an upper bound of vec_ptr[B] used to size the
- * workspace. Column-major plans write back with device atomics in this
- * path. Vector indices must be unique within a vector.
+ * workspace. Vector indices must be unique within a vector; they may
+ * come in any order.
  * ------------------------------------------------------------------- */
 spx_status run_batch(spx_matrix *H, int32_t B, int64_t total_nnz_x, const int32_t *vec_ptr,
                      const int32_t *idx, const void *val, void *Y, void *stream);

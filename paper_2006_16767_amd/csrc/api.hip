@@ -230,7 +230,7 @@ struct spx_matrix {
     void* ws = nullptr;
     size_t ws_bytes = 0;
     spx_plan last_plan{};
-    // batched path: device copy of the trees, workspace, captured graph
+    // batched path: device copy of the trees, workspace
     DevSelector* dev_sel = nullptr;
     void* bws = nullptr;
     size_t bws_bytes = 0;
@@ -239,6 +239,8 @@ struct spx_matrix {
     int32_t* berr = nullptr;
     int32_t* units = nullptr;  // fused-group work units of A (4 ints each)
     int32_t nunits = 0;
+    int32_t* segs = nullptr;  // the columns' segments in blocks of rows, for run_batch
+    int32_t nblk = 0;
     int32_t* split_rows = nullptr;
     int32_t nsplit = 0;
     // breadth-first search buffers (allocated on first use)
@@ -267,13 +269,9 @@ struct spx_matrix {
     void* pr_p = nullptr;  // rank, copied to the caller's array at the end
     uint32_t* pr_bad = nullptr;
     bool pr_W_valid = false;
-    hipStream_t cap_stream = nullptr;
-    hipStream_t cap_side = nullptr;  // a second branch of the captured graph (the fused walk)
-    hipEvent_t cap_fork = nullptr, cap_join = nullptr;
-    hipGraphExec_t gexec = nullptr;
-    hipGraph_t graph = nullptr;
-    const void* gkey[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-    int32_t gkey_B = -1;
+    // batched path: a second stream for the fused groups' walk, and the events
+    // that fork to it and join it
+    int32_t fused_per_cu = 0;
     // profiling
     int profiling = 0;
     double host_ms[2] = {0, 0};
@@ -496,17 +494,11 @@ extern "C" spx_status spx_matrix_destroy(spx_matrix* H) {
     int cur = 0;
     hipGetDevice(&cur);
     hipSetDevice(H->device);
-    if (H->gexec) hipGraphExecDestroy(H->gexec);
-    if (H->graph) hipGraphDestroy(H->graph);
-    if (H->cap_stream) hipStreamDestroy(H->cap_stream);
-    if (H->cap_side) hipStreamDestroy(H->cap_side);
-    if (H->cap_fork) hipEventDestroy(H->cap_fork);
-    if (H->cap_join) hipEventDestroy(H->cap_join);
     void* ptrs[] = {H->col_ptr, H->row_idx, H->perm, H->vals_csc, H->gorder, H->grank, H->gcol, H->gsrc,
                     H->gvals, H->bits, H->xd, H->sp_idx,
                     H->sp_val, H->scratch_i32, H->dev_scalars, H->scan_counter, H->ws,
                     H->part[0][0], H->part[0][1], H->part[1][0], H->part[1][1], H->dev_sel, H->bws,
-                    H->units, H->split_rows, H->bfs_front[0], H->bfs_front[1], H->bfs_y, H->drv_count,
+                    H->units, H->split_rows, H->segs, H->bfs_front[0], H->bfs_front[1], H->bfs_y, H->drv_count,
                     H->bfs_bits[0], H->bfs_bits[1], H->pr_W, H->pr_r, H->pr_y, H->pr_xidx, H->pr_xval,
                     H->pr_xd[0], H->pr_xd[1], H->pr_p, H->pr_bad, H->cnt_dev, H->slab_part,
                     H->dots_part};
@@ -1446,6 +1438,16 @@ extern "C" spx_status run_batch(spx_matrix* H, int32_t B, int64_t total_nnz_x, c
     SPX_TRY(cached_part(H, A, 0, &bal, s, &part));
     const int64_t tiles_mat = ceil_div((int64_t)A.m + A.nnz, 2048);
     if (!H->units && A.dtype != SPX_BOOL && A.m > 0) SPX_TRY(build_units(H, s));
+    if (!H->segs) {
+        H->nblk = batch_row_blocks(A.m, A.n, A.nnz, A.dtype);
+        if (H->nblk) {
+            if (hipMalloc((void**)&H->segs, ((size_t)A.n * H->nblk + 1) * 4) != hipSuccess) {
+                H->segs = nullptr;
+                return fail(SPX_ERR_ALLOC, "run_batch: column segments allocation failed");
+            }
+            SPX_TRY(batch_build_segs(A, H->col_ptr, H->row_idx, H->nblk, H->segs, s));
+        }
+    }
     // capacity-bounded workspace, zeroed at allocation (the per-vector
     // bitvector and value slots and the group slabs are self-cleaning
     // afterwards)
@@ -1453,7 +1455,7 @@ extern "C" spx_status run_batch(spx_matrix* H, int32_t B, int64_t total_nnz_x, c
         const int32_t nb = std::max(B, H->bcap_B);
         const int64_t nn = std::max(total_nnz_x, H->bcap_nnz);
         size_t zf = 0, zb = 0;
-        const size_t bytes = batch_ws_size(A.m, A.n, A.dtype, nb, nn, tiles_mat, &zf, &zb);
+        const size_t bytes = batch_ws_size(A.m, A.n, A.dtype, nb, nn, tiles_mat, H->segs != nullptr, &zf, &zb);
         SPX_HIP(hipStreamSynchronize(s));
         if (H->bws) SPX_HIP(hipFree(H->bws));
         H->bws = nullptr;
@@ -1467,7 +1469,6 @@ extern "C" spx_status run_batch(spx_matrix* H, int32_t B, int64_t total_nnz_x, c
         H->bws_bytes = bytes;
         H->bcap_B = nb;
         H->bcap_nnz = nn;
-        H->gkey_B = -1;  // the captured graph points at the old workspace
     }
     BatchLaunch L{};
     L.csr = A;
@@ -1477,6 +1478,7 @@ extern "C" spx_status run_batch(spx_matrix* H, int32_t B, int64_t total_nnz_x, c
     L.part = part;
     L.tiles_mat = tiles_mat;
     L.B = B;
+    L.cap_B = H->bcap_B;
     L.cap_nnz_x = H->bcap_nnz;
     L.vec_ptr = vec_ptr;
     L.idx = idx;
@@ -1492,41 +1494,10 @@ extern "C" spx_status run_batch(spx_matrix* H, int32_t B, int64_t total_nnz_x, c
     L.nunits = H->nunits;
     L.split_rows = H->split_rows;
     L.nsplit = H->nsplit;
-    // the graph is keyed by everything its kernel arguments capture
-    const void* key[5] = {vec_ptr, idx, val, Y, H->bws};
-    const bool same = H->gexec && H->gkey_B == B && std::equal(key, key + 5, H->gkey);
-    if (!same) {
-        if (H->gexec) hipGraphExecDestroy(H->gexec);
-        if (H->graph) hipGraphDestroy(H->graph);
-        H->gexec = nullptr;
-        H->graph = nullptr;
-        if (!H->cap_stream) SPX_HIP(hipStreamCreateWithFlags(&H->cap_stream, hipStreamNonBlocking));
-        if (!H->cap_side) SPX_HIP(hipStreamCreateWithFlags(&H->cap_side, hipStreamNonBlocking));
-        if (!H->cap_fork) SPX_HIP(hipEventCreateWithFlags(&H->cap_fork, hipEventDisableTiming));
-        if (!H->cap_join) SPX_HIP(hipEventCreateWithFlags(&H->cap_join, hipEventDisableTiming));
-        L.side = H->cap_side;
-        L.fork = H->cap_fork;
-        L.join = H->cap_join;
-        SPX_HIP(hipStreamBeginCapture(H->cap_stream, hipStreamCaptureModeThreadLocal));
-        spx_status st = launch_batch(L, H->bws, H->bws_bytes, H->cap_stream, &H->berr);
-        hipGraph_t g = nullptr;
-        hipError_t e = hipStreamEndCapture(H->cap_stream, &g);
-        if (st != SPX_OK) {
-            if (g) hipGraphDestroy(g);
-            return st;
-        }
-        if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
-        e = hipGraphInstantiate(&H->gexec, g, nullptr, nullptr, 0);
-        if (e != hipSuccess) {
-            hipGraphDestroy(g);
-            return hip_fail(e, "hipGraphInstantiate");
-        }
-        H->graph = g;
-        std::copy(key, key + 5, H->gkey);
-        H->gkey_B = B;
-    }
-    SPX_HIP(hipGraphLaunch(H->gexec, s));
-    return SPX_OK;
+    L.segs = H->segs;
+    L.nblk = H->nblk;
+    L.fused_per_cu = &H->fused_per_cu;
+    return launch_batch(L, H->bws, H->bws_bytes, s, &H->berr);
 }
 
 extern "C" spx_status spx_batch_status(spx_matrix* H, int32_t* flags, void* stream) {

@@ -1,52 +1,47 @@
-// Batched SpMSpV: B sparse vectors of uneven sparsity in one graph launch,
-// the plan of every vector chosen on the device.
+// Batched SpMSpV: B sparse vectors of uneven sparsity, the plan of every
+// vector chosen on the device.
 //
-//  k_batch_plan        one workgroup per vector: prefix sum of the lengths of
-//                      the columns it selects (its nnz_s falls out), then the
-//                      three decision trees evaluated on the Table 1 features
-//                      (matrix features + nnz_x, x_sparsity, nnz_s,
-//                      m_sparsity), and the vector's work-item counts for
-//                      the three phases of its plan.
-//  k_batch_scan        prefix sums of the counts: one ordered queue per
-//                      phase; resets the queue heads.
-//  k_batch_phase<A|B|C>  #CUs x 4 persistent workgroups pop the items of one
-//                      phase until its queue is drained (every workgroup
-//                      exits once the queue head passes the item count);
-//                      beside B, on a branch of the graph of its own,
-//                      k_batch_fused walks the work units of the fused
-//                      groups (a queue per width, a wave per unit):
-//                        A: row-major plans scatter x into the vector's
-//                           bitvector / value slots; column-major plans zero
-//                           the vector's row of Y
-//                        B: one merge-path tile (or one row/entry chunk of the
-//                           direct distribution) of the vector's kernel
-//                        C: row-major balanced fix-up of tile carries, and the
-//                           self-cleaning of the bitvector / value slots
-//                      Items of one phase never wait for each other: the
-//                      ordering between phases is the kernel boundary.
+//  k_batch_plan        one workgroup per vector: the decision trees evaluated on
+//                      the Table 1 features (matrix features + nnz_x,
+//                      x_sparsity, and where a tree reads them nnz_s and
+//                      m_sparsity, from the lengths of the columns it selects)
+//  k_batch_scan        deals the vectors that share passes over A out to groups
+//  k_batch_slabs       the groups' vectors as dense slabs X^T (n rows = columns
+//                      of A, one slot per vector, a cache line per row)
+//  k_batch_stray       vectors whose indices do not ascend, into their slots
+//  k_batch_fused       walks A once per group
+//  k_batch_rows        every other vector, column-major by blocks of rows: a
+//                      block of its Y in LDS, the selected columns' entries
+//                      added there
 //
-// Fused row-major groups: a vector whose plan is row-major (SpMV or CSR
-// SpMSpV, any value type but BOOL), or whose entries reach
-// kFusedMinXSparsity of n, joins a group that shares one pass over A: 128
-// vectors of 4-byte values (two per lane), 64 of 8-byte ones. Its phase-A
-// items scatter x into the group's dense slab X^T (n rows = columns of A,
-// one slot per vector) and its phase-C items clear it again. k_batch_fused
-// walks work units of A for each group (at most kFusedUnitNnz entries of at
-// most kFusedUnitRows whole rows, or a piece of a longer row), a wave per
-// unit; a last group of at most 64 vectors is walked one per lane. It is a
-// kernel of its own (one per width) so that its registers set its
-// occupancy, not those of the tile kernels. Pieces of split rows are added
-// to Y with atomics (their rows of Y are zeroed by phase-A items of the
-// group); every other row is written once. Non-support entries meet zeros
-// in the slab, so the bitvector validation of CSR SpMSpV becomes a product
-// with zero.
+// Groups: a vector whose plan is row-major (SpMV or CSR SpMSpV, any value type
+// but BOOL), or whose entries reach kFusedMinXSparsity of n, joins a group that
+// shares one pass over A: 32 vectors of 4-byte values, 16 of 8-byte ones.
+// k_batch_fused walks work units of A for each group (at most kFusedUnitNnz
+// entries of at most kFusedUnitRows whole rows, or a piece of a longer row), a
+// wave per unit. Pieces of split rows are added to Y with atomics (their rows
+// of Y are zeroed beforehand); every other row is written once. Non-support
+// entries meet zeros in the slab, so the bitvector validation of CSR SpMSpV
+// becomes a product with zero.
 //
-// The launches are captured once into a HIP graph by the caller and
-// replayed. The per-vector bitvector and value slots are zero when a run
-// starts and are cleared again by phase C, so no fill is recorded in the
-// graph. Column-major plans write back with device atomics (the sort and
-// bucket write-backs need per-vector pair buffers sized by nnz_s, which the
-// host does not know without a sync).
+// Where the table of column segments would be too large (batch_row_blocks),
+// and for BOOL, k_batch_phase<A|B|C> runs the vectors of no group instead:
+// persistent workgroups pop the items of one phase until its queue is drained
+// (every workgroup exits once the queue head passes the item count):
+//   A: row-major plans scatter x into the vector's bitvector / value slots;
+//      column-major plans zero the vector's row of Y
+//   B: one merge-path tile (or one row/entry chunk of the direct
+//      distribution) of the vector's kernel
+//   C: row-major balanced fix-up of tile carries, and the self-cleaning of
+//      the bitvector / value slots (they are zero when a run starts)
+// Items of one phase never wait for each other: the ordering between phases
+// is the kernel boundary. Column-major plans write back with device atomics
+// (the sort and bucket write-backs need per-vector pair buffers sized by
+// nnz_s, which the host does not know without a sync).
+//
+// The kernels follow each other on the caller's stream. (The groups' walk on a
+// stream of its own beside the other vectors': 1186 against 1035 us for 512
+// vectors on R-MAT 2^18, since each starves the other of wave slots.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -63,27 +58,24 @@ constexpr int kFillChunk = 65536;    // rows of Y zeroed per phase-A item
 constexpr int kScatterChunk = 2048;  // x entries scattered / cleared per item
 constexpr int kCscDirectEntries = 64;
 constexpr int kCscDirectLanes = 4;
-constexpr int kGroup = 64;                 // lanes of a fused group's wave
-
-// vectors per lane of a full fused group: two 4-byte values (an 8-byte slab
-// load per lane, 128 vectors per group and slab rows of 128 slots), one
-// 8-byte value (64 per group). A last group of at most 64 vectors is walked
-// one value per lane (32 entries per step instead of 16) over the first half
-// of its slab rows.
+// A fused group: the vectors whose values fill a 128-byte slab row (one cache
+// line), 32 of 4-byte values, 16 of 8-byte ones.
+constexpr int kSlabRow = 128;
 template <int DT>
-constexpr int group_vpl() {
-    return sizeof(typename SR<DT>::X) == 4 ? 2 : 1;
+constexpr int group_size() {
+    return kSlabRow / (int)sizeof(typename SR<DT>::X);
 }
-// a column-major vector this dense joins a fused group: at 1 % two vectors
-// could cost a whole pass over A, at 3 % too many products went to atomics
+// a column-major vector this dense joins a fused group
 constexpr double kFusedMinXSparsity = 0.02;
-constexpr int kSplitZeroRows = 64;  // split rows of Y zeroed per phase-A group item
+constexpr int kSplitZeroRows = 64;  // split rows of Y zeroed per item
+
+constexpr int32_t kJoins = -2;  // BatchPlan::gslot until k_batch_scan deals the slots
 
 struct BatchPlan {
     int32_t pattern, dist, wb, lanes;
     int32_t nnz_x, base;
     int32_t nA, nB, nC;
-    int32_t gslot;  // slot in the fused row-major groups, or -1
+    int32_t gslot;  // slot in the fused groups, -1 if in none
     int64_t nnz_s;
 };
 
@@ -109,8 +101,8 @@ struct BatchDev {
     BatchPlan* plans;
     int32_t* offs;    // 3 x (B + 1)
     int32_t* totals;  // 4
-    int32_t* queue;   // queue heads: one per phase, [3] = err, [4, 5] and [6, 7] = the two fused walks' (64-bit)
-    int32_t* err;
+    int32_t* queue;   // queue heads of the phases, [3] = err of the last run
+    int32_t* err;     // of this run, cleared by k_batch_scan
     int32_t* excl_all;  // cap_nnz_x + B
     uint32_t* bits_all;  // B x nwords
     void* xd_all;        // B x n values
@@ -122,10 +114,14 @@ struct BatchDev {
     int32_t nunits;
     const int32_t* split_rows;  // rows cut into several units
     int32_t nsplit;
-    int32_t* gcount;  // vectors in groups (reset per run)
+    const int32_t* segs;  // the columns' first entries in each block of rows (null: k_batch_phase runs the rest)
+    int32_t nblk;
+    int32_t* gcount;  // vectors in groups
+    int32_t* heads;   // of the queues of work units, 128 bytes apart
+    int32_t* stray;   // a flag per vector: k_batch_slabs met an entry outside its tile
     int32_t* gvec;    // slot -> vector
-    void* xt_all;     // ceil(B / gsize) slabs of n x gsize values (self-cleaning)
-    int32_t gsize;    // vectors per fused group and slots per slab row: 64 x group_vpl
+    void* xt_all;     // ceil(B / gsize) slabs of (n + 1) x gsize values, row n zero
+    int32_t gsize;    // vectors per fused group and slots per slab row
 };
 
 __device__ __forceinline__ int dev_tree_eval(const DevTree& t, const double* f) {
@@ -154,15 +150,18 @@ __global__ __launch_bounds__(kBlock) void k_batch_plan(BatchDev a) {
         }
         return;
     }
-    int32_t* excl = a.excl_all + base + b;
+    int32_t* excl = a.segs ? nullptr : a.excl_all + base + b;
     const int32_t* idx = a.idx + base;
     const DevSelector& S = *a.sel;
     __shared__ int s_fuse;
-    // host-known features first: a vector that joins a fused group needs no
-    // prefix of its column lengths (unless the trees read nnz_s)
+    // host-known features first: a vector that joins a fused group or runs by
+    // blocks of rows needs no prefix of its column lengths (unless the trees
+    // read nnz_s)
     if (threadIdx.x == 0) {
         int fuse = 0;
-        if (DT != SPX_BOOL && a.units != nullptr && nx > 0 && !S.needs_nnz_s) {
+        if (a.segs && nx == 0) {
+            fuse = 2;
+        } else if (DT != SPX_BOOL && a.units != nullptr && nx > 0 && !S.needs_nnz_s) {
             double f[F_COUNT];
             for (int i = 0; i < 9; ++i) f[i] = S.mfeat[i];
             f[9] = nx;
@@ -171,7 +170,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_plan(BatchDev a) {
             f[F_COUNTED] = 0.0;
             int pat = dev_tree_eval(S.t[0], f);
             if (pat < 0 || pat > 2) pat = 0;
-            fuse = pat != SPX_PAT_CSC_SPMSPV || f[10] >= kFusedMinXSparsity;
+            fuse = pat != SPX_PAT_CSC_SPMSPV || f[10] >= kFusedMinXSparsity ? 1 : (a.segs ? 2 : 0);
         }
         s_fuse = fuse;
     }
@@ -179,18 +178,14 @@ __global__ __launch_bounds__(kBlock) void k_batch_plan(BatchDev a) {
     if (s_fuse) {
         if (threadIdx.x == 0) {
             BatchPlan p{};
-            p.pattern = SPX_PAT_SPMV;
+            p.pattern = s_fuse == 1 ? SPX_PAT_SPMV : SPX_PAT_CSC_SPMSPV;
             p.dist = SPX_DIST_BALANCED;
             p.wb = SPX_WB_NONE;
             p.lanes = a.row_lanes;
             p.nnz_x = nx;
             p.base = base;
             p.nnz_s = -1;
-            p.gslot = atomicAdd(a.gcount, 1);
-            a.gvec[p.gslot] = b;
-            p.nA = (int32_t)ceil_div(nx, kScatterChunk);
-            p.nB = 0;
-            p.nC = (int32_t)ceil_div(nx, kScatterChunk);
+            p.gslot = s_fuse == 1 ? kJoins : -1;
             a.plans[b] = p;
         }
         return;
@@ -216,13 +211,13 @@ __global__ __launch_bounds__(kBlock) void k_batch_plan(BatchDev a) {
 #pragma unroll
         for (int i = 0; i < kIpt; ++i) {
             const int e = c0 + threadIdx.x * kIpt + i;
-            if (e < nx) excl[e] = run;
+            if (excl && e < nx) excl[e] = run;
             run += len[i];
         }
         carry += tot;
     }
     if (threadIdx.x != 0) return;
-    excl[nx] = carry;
+    if (excl) excl[nx] = carry;
     double f[F_COUNT];
     for (int i = 0; i < 9; ++i) f[i] = S.mfeat[i];
     f[9] = nx;
@@ -238,8 +233,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_plan(BatchDev a) {
     const bool fusable = DT != SPX_BOOL && a.units != nullptr && nx > 0;
     if (fusable && (p.pattern != SPX_PAT_CSC_SPMSPV || f[10] >= kFusedMinXSparsity)) {
         if (p.pattern == SPX_PAT_CSC_SPMSPV) p.pattern = SPX_PAT_SPMV;
-        p.gslot = atomicAdd(a.gcount, 1);
-        a.gvec[p.gslot] = b;
+        p.gslot = kJoins;
     }
     p.dist = dev_tree_eval(S.t[1 + p.pattern], f) == SPX_DIST_BALANCED ? SPX_DIST_BALANCED : SPX_DIST_DIRECT;
     p.wb = p.pattern == SPX_PAT_CSC_SPMSPV ? SPX_WB_ATOMIC : SPX_WB_NONE;
@@ -247,10 +241,8 @@ __global__ __launch_bounds__(kBlock) void k_batch_plan(BatchDev a) {
     p.nnz_x = nx;
     p.base = base;
     p.nnz_s = carry;
-    if (p.gslot >= 0) {
-        p.nA = (int32_t)ceil_div(nx, kScatterChunk);
-        p.nB = 0;
-        p.nC = (int32_t)ceil_div(nx, kScatterChunk);
+    if (p.gslot == kJoins || a.segs) {
+        p.nA = p.nB = p.nC = 0;
     } else if (p.pattern == SPX_PAT_CSC_SPMSPV) {
         p.nA = (int32_t)ceil_div(a.m, kFillChunk);
         p.nB = p.dist == SPX_DIST_BALANCED ? (int32_t)ceil_div((int64_t)nx + carry, kBatchTile)
@@ -265,23 +257,32 @@ __global__ __launch_bounds__(kBlock) void k_batch_plan(BatchDev a) {
     a.plans[b] = p;
 }
 
-__global__ void k_batch_reset(int32_t* err, int32_t* gcount) {
-    *err = 0;
-    *gcount = 0;
-}
-
-// group items appended after the per-vector items of a phase (the groups'
-// walk of A is k_batch_fused): phase A zeroes the split rows of the groups'
-// vectors in Y, kSplitZeroRows rows per item (one item for all of them left
-// a single workgroup with some 10^5 scattered stores, the tail of the phase)
-__device__ __forceinline__ int32_t group_items(const BatchDev& a, int ph, int32_t G) {
-    if (ph == 0) return G * (int32_t)ceil_div(a.nsplit, kSplitZeroRows);
-    return 0;
-}
-
 // ------------------------------------------------------------------ queue
+// One ordered queue per phase, and the vectors of the fused groups in their
+// order in the batch.
 __global__ __launch_bounds__(kBlock) void k_batch_scan(BatchDev a) {
     __shared__ int32_t s_tmp[kWavesPerBlock];
+    if (threadIdx.x == 0) {
+        a.queue[3] = *a.err;
+        *a.err = 0;
+    }
+    int32_t count = 0;
+    for (int c0 = 0; c0 < a.B; c0 += kBlock) {
+        const int b = c0 + threadIdx.x;
+        const bool joins = b < a.B && a.plans[b].gslot == kJoins;
+        int32_t tot;
+        const int32_t incl = block_incl_scan(joins ? 1 : 0, s_tmp, &tot);
+        if (joins) {
+            const int slot = count + incl - 1;
+            a.plans[b].gslot = slot;
+            a.gvec[slot] = b;
+            a.stray[b] = 0;
+        }
+        count += tot;
+    }
+    if (threadIdx.x == 0) *a.gcount = count;
+    if (threadIdx.x < 8) a.heads[threadIdx.x * 32] = 0;
+    if (a.segs) return;  // no queues
     for (int ph = 0; ph < 3; ++ph) {
         int32_t* off = a.offs + ph * (a.B + 1);
         int32_t carry = 0;
@@ -296,12 +297,11 @@ __global__ __launch_bounds__(kBlock) void k_batch_scan(BatchDev a) {
         }
         if (threadIdx.x == 0) {
             off[a.B] = carry;
-            const int32_t G = (int32_t)ceil_div(*a.gcount, a.gsize);
-            a.totals[ph] = carry + group_items(a, ph, G);
+            a.totals[ph] = carry;
         }
         __syncthreads();
     }
-    if (threadIdx.x < 3 || (threadIdx.x >= 4 && threadIdx.x < 8)) a.queue[threadIdx.x] = 0;
+    if (threadIdx.x < 3) a.queue[threadIdx.x] = 0;
 }
 
 // ------------------------------------------------------------------ persistent
@@ -372,194 +372,462 @@ __device__ __forceinline__ T lane_value(T v, int q) {
     }
 }
 
-// Slab row `row` of a group (kSlots values), this lane's V slots (V
-// consecutive values: one 4- or 8-byte load per lane). BUF: a buffer load with the row's byte
-// offset in a scalar register and the lane's in a vector one (no 64-bit
-// address per load); the group's slab is below 2 GiB then.
-template <typename X, int V>
-struct SlotVals {
-    X v[V];
+// 16 bytes of a slab row: the values of a lane's vectors.
+template <typename X>
+struct alignas(16) SlotVals {
+    static constexpr int E = 16 / sizeof(X);
+    X v[E];
 };
 
-template <typename X, bool BUF, int V, int kSlots>
-struct SlabRows {
-    const X* base;  // the group's slab
-    __amdgpu_buffer_rsrc_t rsrc;
-    __device__ SlabRows(const X* b, int64_t n) : base(b) {
-        if constexpr (BUF)
-            rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)b, (short)0, (int)(n * kSlots * (int64_t)sizeof(X)),
-                                                     0x00020000);
-    }
-    __device__ __forceinline__ SlotVals<X, V> load(int row, int lane) const {
-        static_assert(sizeof(X) * V == 4 || sizeof(X) * V == 8, "a lane loads 4 or 8 bytes");
-        if constexpr (!BUF) {
-            return *(const SlotVals<X, V>*)(base + (int64_t)row * kSlots + lane * V);
-        } else if constexpr (sizeof(X) * V == 4) {
-            return __builtin_bit_cast(SlotVals<X, V>, __builtin_amdgcn_raw_buffer_load_b32(
-                                                          rsrc, lane * 4, row * (kSlots * (int)sizeof(X)), 0));
-        } else {
-            return __builtin_bit_cast(SlotVals<X, V>, __builtin_amdgcn_raw_buffer_load_b64(
-                                                          rsrc, lane * 8, row * (kSlots * (int)sizeof(X)), 0));
+// The groups' slabs, a tile of kSlabCols slab rows per step of a workgroup:
+// where the tile's columns begin and end in each vector by search, its entries
+// into LDS, whole lines out. Entries that are not where an ascending index
+// list would have them flag their vector: every entry lies in the range of at
+// least one tile (a tile ends where the next one begins), so k_batch_stray can
+// put the flagged vectors right. Past the tiles: items that zero
+// kSplitZeroRows split rows of Y for a group's vectors.
+//
+// Bound by the slab's bytes: 120 us (2.9 TB/s) for the 217
+// vectors of density 2 % and more (14M entries) on R-MAT 2^18. Scattered
+// stores to slabs kept zero between runs took 240 us with the zeroing of the
+// other vectors' Y, and 112 us for clearing them again: a 4-byte store per
+// entry and pass is an L2 request each, and neither pass can run beside the
+// products.
+constexpr int kSlabCols = 256;
+
+template <int DT>
+__global__ __launch_bounds__(kBlock) void k_batch_slabs(BatchDev a) {
+    if constexpr (DT != SPX_BOOL) {  // BOOL vectors never join a group
+        using X = typename SR<DT>::X;
+        constexpr int GS = group_size<DT>(), E = SlotVals<X>::E;
+        constexpr int kPitch = GS + 1;  // rows on different banks
+        __shared__ X s_x[kSlabCols * kPitch];
+        __shared__ int32_t s_vec[GS], s_at[GS], s_start[GS + 1];
+        const int count = *a.gcount;
+        const int64_t G = ceil_div(count, GS), T = ceil_div((int64_t)a.n + 1, kSlabCols);
+        const int64_t zper = ceil_div(a.nsplit, kSplitZeroRows);
+        const auto* val = (const X*)a.val;
+        for (int64_t i = blockIdx.x; i < G * (T + zper); i += gridDim.x) {
+            if (i >= G * T) {
+                const int g = (int)((i - G * T) / zper);
+                const int s0 = (int)((i - G * T) % zper) * kSplitZeroRows;
+                const int ns = min(kSplitZeroRows, a.nsplit - s0);
+                const int nvec = min(GS, count - g * GS);
+                for (int t = threadIdx.x; t < ns * nvec; t += kBlock)
+                    ((typename SR<DT>::Y*)a.Y)[(int64_t)a.gvec[g * GS + t % nvec] * a.m + a.split_rows[s0 + t / nvec]] =
+                        (typename SR<DT>::Y)0;
+                continue;
+            }
+            // an XCD's workgroups take neighbouring tiles: they share lines of
+            // the sparser vectors
+            const int64_t t = xcd_tile(i, G * T);
+            const int g = (int)(t / T);
+            const int c0 = (int)(t % T) * kSlabCols;
+            const int rows = (int)min((int64_t)kSlabCols, (int64_t)a.n + 1 - c0);
+            const int nvec = min(GS, count - g * GS);
+            for (int e = threadIdx.x; e < kSlabCols * kPitch; e += kBlock) s_x[e] = (X)0;
+            // eight lanes search a vector's list for the first entries that
+            // are not below c0 and c0 + kSlabCols, nine ways a step
+            const int v = threadIdx.x >> 3, l = threadIdx.x & 7;
+            const bool mine = v < nvec;
+            const int b = mine ? a.gvec[g * GS + v] : 0;
+            const int base = mine ? a.vec_ptr[b] : 0;
+            const int nx = mine ? a.vec_ptr[b + 1] - base : 0;
+            const int32_t* idx = a.idx + base;
+            int lo[2] = {0, 0}, hi[2] = {c0 == 0 ? 0 : nx, nx};
+            if (c0 + rows > a.n) lo[1] = nx;
+            while (__any(lo[0] < hi[0] || lo[1] < hi[1])) {
+                int at[2], col[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int w = hi[k] - lo[k];
+                    at[k] = lo[k] + (w >= 9 ? (l + 1) * (w / 9) : min(l, w - 1));
+                    col[k] = w > 0 ? idx[at[k]] : 0;
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const uint32_t m = (uint32_t)(__ballot(col[k] >= c0 + k * kSlabCols) >> (lane_id() & 56)) & 255u;
+                    const int f = m ? __ffs(m) - 1 : 8;
+                    const int up = __shfl(at[k], (lane_id() & 56) | min(f, 7), kWave);
+                    const int below = __shfl(at[k], (lane_id() & 56) | max(f - 1, 0), kWave);
+                    if (hi[k] > lo[k]) {
+                        if (f < 8) hi[k] = up;
+                        if (f > 0) lo[k] = below + 1;
+                    }
+                }
+            }
+            if (v < GS && l == 0) {
+                s_vec[v] = b;
+                s_start[v + 1] = max(0, lo[1] - lo[0]);
+                s_at[v] = base + lo[0];
+            }
+            if (threadIdx.x == 0) s_start[0] = 0;
+            __syncthreads();
+            if (threadIdx.x < kWave) {
+                int sum = threadIdx.x < GS ? s_start[threadIdx.x + 1] : 0;
+                for (int d = 1; d < GS; d <<= 1) {
+                    const int o = __shfl_up(sum, d, kWave);
+                    if ((int)threadIdx.x >= d) sum += o;
+                }
+                if (threadIdx.x < GS) s_start[threadIdx.x + 1] = sum;
+            }
+            __syncthreads();
+            const int total = s_start[GS];
+            constexpr int kPer = 8;
+            for (int e0 = threadIdx.x; e0 < total; e0 += kPer * kBlock) {
+                int u[kPer], c[kPer];
+                X x[kPer];
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) {
+                    const int e = min(e0 + q * kBlock, total - 1);
+                    int w = 0;
+#pragma unroll
+                    for (int d = GS / 2; d > 0; d >>= 1)
+                        if (s_start[w + d] <= e) w += d;
+                    u[q] = w;
+                    const int at = s_at[w] + e - s_start[w];
+                    c[q] = a.idx[at];
+                    x[q] = val[at];
+                }
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) {
+                    const int r = c[q] - c0;
+                    if (r >= 0 && r < rows && c[q] < a.n)
+                        s_x[r * kPitch + u[q]] = x[q];
+                    else
+                        a.stray[s_vec[u[q]]] = 1;
+                }
+            }
+            __syncthreads();
+            auto* xt = (SlotVals<X>*)((X*)a.xt_all + ((int64_t)g * (a.n + 1) + c0) * GS);
+#pragma unroll
+            for (int q = 0; q < kSlabCols * 8 / kBlock; ++q) {
+                const int e = q * kBlock + threadIdx.x;
+                SlotVals<X> o;
+#pragma unroll
+                for (int k = 0; k < E; ++k) o.v[k] = s_x[(e >> 3) * kPitch + (e & 7) * E + k];
+                if ((e >> 3) < rows) xt[e] = o;
+            }
+            __syncthreads();
         }
     }
+}
+
+// The flagged vectors' entries into their slots, in any order: a workgroup per
+// slot of the groups.
+template <int DT>
+__global__ __launch_bounds__(kBlock) void k_batch_stray(BatchDev a) {
+    if constexpr (DT != SPX_BOOL) {
+        using X = typename SR<DT>::X;
+        constexpr int GS = group_size<DT>();
+        const int slot = blockIdx.x;
+        if (slot >= *a.gcount) return;
+        const int b = a.gvec[slot];
+        if (!a.stray[b]) return;
+        auto* xt = (X*)a.xt_all + (int64_t)(slot / GS) * (a.n + 1) * GS + slot % GS;
+        for (int e = a.vec_ptr[b] + threadIdx.x; e < a.vec_ptr[b + 1]; e += kBlock)
+            if (a.idx[e] >= 0 && a.idx[e] < a.n) xt[(int64_t)a.idx[e] * GS] = ((const X*)a.val)[e];
+    }
+}
+
+// A wave's LDS in the fused walk: a unit's entries; for an entry that ends a
+// row, where the row's sums go (kNoEnd for the others); the rows' sums, slot by
+// slot, until they are stored. A row's 16-byte pieces are permuted by the row,
+// so that the rows of one slot lie on different banks.
+template <int DT>
+struct FusedEntry {
+    int32_t col;
+    typename SR<DT>::V val;
 };
+constexpr int kFusedSteps = 4;  // gathers in flight, twice
+template <int DT>
+struct FusedLds {
+    alignas(16) typename SR<DT>::Acc sums[kFusedUnitRows * group_size<DT>()];
+    // lane group h's entries from h * (len + 1), its ends from h * (len + 8):
+    // the eight lane groups read from different banks
+    alignas(16) uint16_t end[kFusedUnitNnz + 8 * 8];
+    FusedEntry<DT> e[kFusedUnitNnz + 8];
+    FusedEntry<DT> none[kFusedSteps];  // past the last step: the slab's zero row
+    int64_t y[group_size<DT>()];  // where the vectors' Y begin
+};
+constexpr uint32_t kNoEnd = 0xffff;
 
-constexpr int kStageRows = 16;  // rows of a fused unit staged in LDS before they are stored
-
-// One work unit of A for the vectors of fused group g (at most 64 V of
-// them; the group's slab rows hold kGroup x group_vpl slots): lane l holds
-// slots V l .. V l + V - 1. The unit's entries stream 32 / V at a time (each a
-// gather of the slab row X^T[col], V values per lane); a row's sums are
-// staged when the stream passes its end, and every kStageRows / V rows the
-// stage goes out as one run of consecutive rows per vector, not as 64 V
-// scattered values per row. A piece of a split row adds its sums with
-// atomics. st: the wave's kStageRows x 64 stage, sb: its 64 V vector ids
-// (LDS).
-template <int DT, bool BUF, int V>
-__device__ __forceinline__ void batch_fused_unit(const BatchDev& a, int g, int32_t unit, typename SR<DT>::Acc* st,
-                                                 int32_t* sb) {
+// One work unit of A for the vectors of fused group g. Eight lanes hold the
+// group's slots, 16 bytes each; the wave's eight lane groups each walk an eighth of the unit's
+// entries, the next kFusedSteps gathers in flight while it adds the last ones (a
+// gather reads eight whole slab rows, a cache line each). A lane group that passes a row's end leaves the
+// row's sum (or the last piece of it) in LDS; the pieces of rows that run on
+// into the next eighth are added at the end, in order. Then the unit's rows go
+// out together, one run of consecutive rows per vector. A piece of a split row
+// adds its sums to Y with atomics.
+//
+// 590 us for the seven groups of 217 vectors on R-MAT 2^18 (7.6M entries: 53M
+// gathered lines, 90 G lines/s, 55 % of them from L2): 330 of it is what a unit
+// takes without the gathers (90 of that the stores of Y, in lines that units
+// share), and lines that all come from L2 would save 65. Two vectors per lane
+// (512-byte gathers, three times the slab per group) took 1066 us beside the
+// other vectors' walk; eight entries of one row per step, the lane groups' sums
+// added at every row's end, twice the instructions; the next unit's entries
+// loaded ahead gave nothing (661 against 652 us).
+template <int DT, bool BUF>
+__device__ __forceinline__ void batch_fused_unit(const BatchDev& a, int g, int32_t unit, FusedLds<DT>& L) {
     using S = SR<DT>;
     using X = typename S::X;
+    using V = typename S::V;
     using Acc = typename S::Acc;
-    constexpr int SLOTS = kGroup * group_vpl<DT>();  // vectors per group, slots per slab row
-    constexpr int GS = kGroup * V;                  // slots this walk covers
-    constexpr int kRows = kStageRows / V;           // rows per stage
-    constexpr int kPer = kWave / kRows;     // vectors per store of the stage
+    constexpr int E = SlotVals<X>::E, GS = group_size<DT>();
     const int4 u = a.units[unit];
-    const int r0 = u.x, nrows = u.y - u.x, k0 = u.z, k1 = u.w;
+    const int r0 = u.x, nrows = u.y - u.x, k0 = u.z, cnt = u.w - u.z;
     const int lane = lane_id();
-    const int nvec = min(GS, *a.gcount - g * SLOTS);
-    bool on[V];
-    typename S::Y* y[V];
+    const int q = lane >> 3, piece = (lane & 7) * 16;
+    const int nvec = min(GS, *a.gcount - g * GS);
+    const char* xt = (const char*)a.xt_all + (int64_t)g * (a.n + 1) * kSlabRow;
+    const auto rsrc = buffer_of(xt, BUF ? (int)((int64_t)(a.n + 1) * kSlabRow) : 0);
+    auto load = [&](int c) {
+        if constexpr (BUF)
+            return __builtin_bit_cast(SlotVals<X>, __builtin_amdgcn_raw_buffer_load_b128(rsrc, c * kSlabRow | piece, 0, 0));
+        else
+            return *(const SlotVals<X>*)(xt + (int64_t)c * kSlabRow + piece);
+    };
+    // lane i holds the end of row r0 + i - 1 in the unit's entries
+    int rp = lane <= nrows ? a.row_ptr[r0 + lane] - k0 : 0;
+    const bool split = nrows == 1 && (lane_value(rp, 0) != 0 || lane_value(rp, 1) != cnt);
+    if (split) rp = lane == 0 ? 0 : cnt;
+    if (lane < GS) L.y[lane] = lane < nvec ? (int64_t)a.gvec[g * GS + lane] * a.m : 0;
+    // A streams through once per group: non-temporal, so that L2 keeps the
+    // slab rows the gathers re-read
+    constexpr int kPer = kFusedUnitNnz / kWave;
+    FusedEntry<DT> in[kPer];
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-        const int slot = lane * V + v;
-        on[v] = slot < nvec;
-        const int b = on[v] ? a.gvec[g * SLOTS + slot] : 0;
-        y[v] = (typename S::Y*)a.Y + (int64_t)b * a.m;
-        sb[slot] = b;
+    for (int p = 0; p < kPer; ++p) {
+        const int i = p * kWave + lane;
+        // past the unit's end: value 0 and the slab's zero row
+        in[p].col = i < cnt ? __builtin_nontemporal_load(a.col_idx + k0 + i) : a.n;
+        in[p].val = i < cnt ? __builtin_nontemporal_load((const V*)a.vals + k0 + i) : (V)0;
     }
-    const SlabRows<X, BUF, V, SLOTS> xt((const X*)a.xt_all + (int64_t)g * a.n * SLOTS, a.n);
-    const auto* vals = (const typename S::V*)a.vals;
-    // lane i holds row_ptr[r0 + i], i <= nrows (nrows < 64)
-    const int rp = lane <= nrows ? a.row_ptr[r0 + lane] : 0;
-    const bool split = nrows == 1 && (k0 != lane_value(rp, 0) || k1 != lane_value(rp, 1));
-    // rows [c0, c0 + cnt) of the stage to Y: lane = (row rr, vector t * kPer + lane / kRows)
-    auto store_stage = [&](int c0, int cnt) {
-        __builtin_amdgcn_wave_barrier();
-        const int rr = lane & (kRows - 1);
-#pragma unroll 4
-        for (int t = 0; t < GS / kPer; ++t) {
-            const int vs = t * kPer + lane / kRows;
-            if (rr < cnt && vs < nvec)
-                __builtin_nontemporal_store(S::out(st[rr * GS + vs]),
-                                            (typename S::Y*)a.Y + (int64_t)sb[vs] * a.m + r0 + c0 + rr);
-        }
-        __builtin_amdgcn_wave_barrier();
+    SlotVals<Acc> z;
+#pragma unroll
+    for (int e = 0; e < E; ++e) z.v[e] = S::zero();
+    for (int i = lane; i < nrows * 8; i += kWave) *(SlotVals<Acc>*)(L.sums + i * E) = z;
+    // lane group h takes the entries from h * len on; inv finds i / len for
+    // i < 512
+    const int len = ((cnt + 7) / 8 + 2 * kFusedSteps - 1) / (2 * kFusedSteps) * (2 * kFusedSteps);
+    const uint32_t inv = len > 0 ? (65536u + len - 1) / len : 0;
+    auto group_of = [&](int i) { return (int)(((uint32_t)i * inv) >> 16); };
+    // of row r, the lane's piece of its sums
+    auto sums_at = [&](int r) { return r * 8 * 16 + ((r & 7) << 4); };
+#pragma unroll
+    for (int p = 0; p < kPer; ++p) {
+        const int i = p * kWave + lane;
+        if (i < 8 * len) L.e[i + group_of(i)] = in[p];
+    }
+    if (lane < kFusedSteps) L.none[lane] = FusedEntry<DT>{a.n, (V)0};
+    for (int i = lane; i < len + 8; i += kWave) ((uint4*)L.end)[i] = uint4{~0u, ~0u, ~0u, ~0u};
+    const int row_end = __shfl_down(rp, 1, kWave);  // of row lane, for lane < nrows
+    const bool some = lane < nrows && row_end > rp;
+    __builtin_amdgcn_wave_barrier();
+    if (some) L.end[row_end - 1 + 8 * group_of(row_end - 1)] = (uint16_t)sums_at(lane);
+    __builtin_amdgcn_wave_barrier();
+    auto sums = [&](uint32_t at) { return (SlotVals<Acc>*)((char*)L.sums + (at ^ piece)); };
+    SlotVals<Acc> acc = z;
+    const FusedEntry<DT>* mine = L.e + q * (len + 1);
+    const uint16_t* ends = L.end + q * (len + 8);
+    struct Steps {
+        FusedEntry<DT> e[kFusedSteps];
+        SlotVals<X> x[kFusedSteps];
+    } A, B;
+    auto fetch = [&](Steps& s, const FusedEntry<DT>* from) {
+#pragma unroll
+        for (int t = 0; t < kFusedSteps; ++t) s.e[t] = from[t];
+#pragma unroll
+        for (int t = 0; t < kFusedSteps; ++t) s.x[t] = load(s.e[t].col);
     };
-    Acc acc[V];
-    auto flush = [&](int i) {
-        if (split) {
+    auto use = [&](const Steps& s, uint32_t end01, uint32_t end23) {
 #pragma unroll
-            for (int v = 0; v < V; ++v)
-                if (on[v]) S::atomic_add(&y[v][r0 + i], acc[v]);
-            return;
-        }
+        for (int t = 0; t < kFusedSteps; ++t) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) st[(i & (kRows - 1)) * GS + lane * V + v] = acc[v];
-        if ((i & (kRows - 1)) == kRows - 1) store_stage(i - (kRows - 1), kRows);
-    };
-    int i = 0;
-    int end = lane_value(rp, 1);
-#pragma unroll
-    for (int v = 0; v < V; ++v) acc[v] = S::zero();
-    // kStep entries per step: lane q loads entry k + q (one coalesced load),
-    // then all kStep slab rows are gathered before the first is used
-    constexpr int kStep = 32 / V;
-    for (int k = k0; k < k1; k += kStep) {
-        const int kk = k + (lane & (kStep - 1));
-        const bool in = kk < k1;
-        // A streams through once per group: non-temporal, so that L2 keeps
-        // the slab rows the gathers re-read
-        const int cl = in ? __builtin_nontemporal_load(a.col_idx + kk) : 0;
-        const typename S::V vl = in ? __builtin_nontemporal_load(vals + kk) : (typename S::V)0;
-        // the step's slab rows into scalars first, with the whole wave
-        // active; then only the group's lanes gather (a partial group moves
-        // only its own bytes)
-        int row[kStep];
-#pragma unroll
-        for (int q = 0; q < kStep; ++q) row[q] = lane_value(cl, q);
-        SlotVals<X, V> xv[kStep];
-        if (on[0]) {
-#pragma unroll
-            for (int q = 0; q < kStep; ++q) xv[q] = xt.load(row[q], lane);
-        } else {
-#pragma unroll
-            for (int q = 0; q < kStep; ++q)
-#pragma unroll
-                for (int v = 0; v < V; ++v) xv[q].v[v] = (X)0;
-        }
-#pragma unroll
-        for (int q = 0; q < kStep; ++q) {
-            if (k + q >= k1) break;
-            while (k + q >= end) {
-                flush(i);
-#pragma unroll
-                for (int v = 0; v < V; ++v) acc[v] = S::zero();
-                ++i;
-                end = lane_value(rp, i + 1);
+            for (int i = 0; i < E; ++i) acc.v[i] = S::fma(s.e[t].val, s.x[t].v[i], acc.v[i]);
+            const uint32_t end = ((t < 2 ? end01 : end23) >> (t % 2 * 16)) & 0xffffu;
+            if (end != kNoEnd) {
+                *sums(end) = acc;
+                acc = z;
             }
-            const typename S::V aq = lane_value(vl, q);
+        }
+    };
+    static_assert(kFusedSteps == 4, "two words of ends per step");
+    fetch(A, mine);
+    for (int t0 = 0; t0 < len; t0 += 2 * kFusedSteps) {
+        fetch(B, mine + t0 + kFusedSteps);
+        const uint4 end = *(const uint4*)(ends + t0);
+        use(A, end.x, end.y);
+        fetch(A, t0 + 2 * kFusedSteps < len ? mine + t0 + 2 * kFusedSteps : L.none);
+        use(B, end.z, end.w);
+    }
+    __builtin_amdgcn_wave_barrier();
+    // the row that runs on past a lane group's eighth
+    for (int h = 0; h < 8; ++h) {
+        const int e = min((h + 1) * len, cnt);
+        const uint64_t m = __ballot(some && rp < e && e < row_end);
+        if (m == 0 || h * len >= cnt) continue;
+        if (q == h) {
+            SlotVals<Acc>* to = sums(sums_at(__ffsll((unsigned long long)m) - 1));
+            SlotVals<Acc> sum = *to;
 #pragma unroll
-            for (int v = 0; v < V; ++v) acc[v] = S::fma(aq, xv[q].v[v], acc[v]);
+            for (int i = 0; i < E; ++i) sum.v[i] = S::add(sum.v[i], acc.v[i]);
+            *to = sum;
         }
     }
-    for (; i < nrows; ++i) {
-        flush(i);
-#pragma unroll
-        for (int v = 0; v < V; ++v) acc[v] = S::zero();
+    __builtin_amdgcn_wave_barrier();
+    auto sum_of = [&](int r, int v) {
+        return *(const Acc*)((const char*)L.sums + ((sums_at(r) ^ (v / E * 16)) | v % E * (int)sizeof(Acc)));
+    };
+    auto* Y = (typename S::Y*)a.Y + r0;
+    if (split) {
+        if (lane < nvec) S::atomic_add(Y + L.y[lane], sum_of(0, lane));
+    } else {
+        const int rr = lane % kFusedUnitRows;
+        for (int v = lane / kFusedUnitRows; v < nvec; v += kWave / kFusedUnitRows)
+            if (rr < nrows) __builtin_nontemporal_store(S::out(sum_of(rr, v)), Y + (L.y[v] + rr));
     }
-    if (!split && (nrows & (kRows - 1))) store_stage(nrows & ~(kRows - 1), nrows & (kRows - 1));
     __builtin_amdgcn_wave_barrier();
 }
 
-// The fused groups' work: item = group x unit, a wave per item, popped in
-// order from a queue of its own (the kernel runs beside the phase-B tiles,
-// so its workgroups become resident as the tiles' leave; every wave exits
-// once the head passes the item count).
-template <int DT, bool BUF, int V>
+// The fused groups' work, one group after the other: units from eight queues
+// (a workgroup's by its number, which goes round the XCDs), one ahead of the
+// walk. (One queue per group and no unit ahead: the pops, atomics on one
+// word, took 890 us in all against 652 for units dealt round the waves; dealt
+// out, the last wave is 15 % behind. Units in runs of 64 on one XCD, whose
+// rows of Y share cache lines: 691. Each XCD at a group of its own: no faster
+// either, since every L2 sees the same share of a slab.)
+constexpr int kFusedQueues = 8;
+
+template <int DT, bool BUF>
 __global__ __launch_bounds__(kBlock) void k_batch_fused(BatchDev a) {
     if constexpr (DT != SPX_BOOL) {  // BOOL vectors never join a group
-        using Acc = typename SR<DT>::Acc;
-        constexpr int SLOTS = kGroup * group_vpl<DT>();
-        __shared__ Acc s_stage[kWavesPerBlock][kStageRows * kGroup];
-        __shared__ int32_t s_vec[kWavesPerBlock][kGroup * V];
-        // groups of this walk: the two-wide one takes every group of more
-        // than 64 vectors, the one-wide one the rest (a last partial group,
-        // or all groups of 8-byte values); one kernel per width, so that
-        // each has its own registers
-        const int gcount = *a.gcount;
-        const int64_t G = ceil_div(gcount, SLOTS);
-        const int last = G > 0 ? gcount - (int)(G - 1) * SLOTS : 0;
-        // groups 0 .. g_wide - 1 are wide
-        const int64_t g_wide = (SLOTS > kGroup && G > 0) ? (last > kGroup ? G : G - 1) : 0;
-        const int64_t g0 = V == 1 ? g_wide : 0;
-        const int64_t ng = V == 1 ? G - g_wide : g_wide;
-        const int64_t total = ng * a.nunits;
-        if (total <= 0) return;  // nothing for this walk: no atomic on the head
-        auto* head = (unsigned long long*)(a.queue + (V == 1 ? 6 : 4));
+        __shared__ FusedLds<DT> s_lds[kWavesPerBlock];
+        FusedLds<DT>& L = s_lds[__builtin_amdgcn_readfirstlane(wave_id())];
+        const int64_t total = ceil_div(*a.gcount, group_size<DT>()) * a.nunits;
+        const int x = blockIdx.x % kFusedQueues;
+        auto pop = [&] { return lane_id() == 0 ? atomicAdd(a.heads + x * 32, 1) : 0; };
+        int next = pop();
         for (;;) {
-            unsigned long long got = 0;
-            if (lane_id() == 0) got = atomicAdd(head, 1ull);
-            // lane 0's value through scalar registers: the item (and so the
-            // group's slab descriptor) is then known to be wave-uniform
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)got);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)(got >> 32));
-            const int64_t item = (int64_t)(((uint64_t)hi << 32) | lo);
-            if (item >= total) break;
-            batch_fused_unit<DT, BUF, V>(a, (int)(g0 + item / a.nunits), (int32_t)(item % a.nunits),
-                                         s_stage[wave_id()], s_vec[wave_id()]);
+            const int64_t i = (int64_t)__builtin_amdgcn_readfirstlane(next) * kFusedQueues + x;
+            if (i >= total) break;
+            next = pop();
+            const int g = (int)(i / a.nunits);
+            batch_fused_unit<DT, BUF>(a, g, (int)(i - (int64_t)g * a.nunits), L);
         }
+    }
+}
+
+// The vectors of no group, by blocks of rows: a workgroup holds kRowsBytes of
+// one vector's Y in LDS, adds the products of the selected columns' entries in
+// those rows to it there, and stores it. A column's entries ascend by row, so a
+// block's are one segment, found in a table (build_segs). A thread reads one
+// segment's bounds; then four lanes take a segment, and a wave a long one. The
+// blocks of one vector follow each other on one XCD: they read neighbouring
+// segments, in the same cache lines.
+//
+// Bound by the chain from index to segment to entries, and by Y: 219 us for
+// the 295 vectors below a density of 2 % on R-MAT 2^18 (4.7M segments, 310 MB
+// of Y; 252 us with 512 threads, 232 with 128 KB of Y each). Atomics into Y
+// took 760 us, and 54 us for zeroing Y before: the chip does 21 G scattered
+// atomics/s, from one XCD or all.
+constexpr int kRowsBytes = 65536;
+constexpr int kRowsThreads = 1024;
+constexpr int kLongSegment = 64;
+
+template <int DT>
+__global__ __launch_bounds__(kRowsThreads) void k_batch_rows(BatchDev a, int32_t b0) {
+    if constexpr (DT != SPX_BOOL) {
+        using S = SR<DT>;
+        using Acc = typename S::Acc;
+        extern __shared__ __align__(16) char s_raw[];
+        Acc* y = (Acc*)s_raw;
+        constexpr int R = kRowsBytes / (int)sizeof(Acc);
+        const int i = blockIdx.x / 8;
+        const int b = b0 + i / a.nblk * 8 + blockIdx.x % 8, blk = i % a.nblk;
+        if (b >= a.B) return;
+        const BatchPlan p = a.plans[b];
+        if (p.gslot >= 0) return;  // in a group, or refused
+        for (int r = threadIdx.x; r < kRowsBytes / 16; r += kRowsThreads) ((uint4*)s_raw)[r] = uint4{0, 0, 0, 0};
+        __syncthreads();
+        const int32_t* __restrict__ idx = a.idx + p.base;
+        const auto* __restrict__ xv = (const typename S::X*)a.val + p.base;
+        const auto* __restrict__ vals = (const typename S::V*)a.vals_csc;
+        const int r0 = blk * R, last = a.nnz - 1, l4 = lane_id() & 3;
+        for (int c0 = 0; c0 < p.nnz_x; c0 += kRowsThreads) {
+            const int e = c0 + threadIdx.x;
+            int k0 = 0, len = 0;
+            typename S::X x = (typename S::X)0;
+            if (e < p.nnz_x) {
+                const int32_t* t = a.segs + (int64_t)idx[e] * a.nblk + blk;
+                k0 = t[0];
+                len = t[1] - k0;
+                x = xv[e];
+            }
+            uint64_t longs = __ballot(len > kLongSegment);
+            while (longs) {
+                const int q = __ffsll((unsigned long long)longs) - 1;
+                longs &= longs - 1;
+                const int kq = lane_value(k0, q), lq = lane_value(len, q);
+                const auto xq = lane_value(x, q);
+                for (int k = lane_id(); k < lq; k += kWave)
+                    S::lds_atomic_add(&y[a.row_idx[kq + k] - r0], S::mul(vals[kq + k], xq));
+            }
+            if (len > kLongSegment) len = 0;
+            int ks[4], ls[4], row[4];
+            typename S::X xs[4];
+            typename S::V v[4];
+            int most = 0;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int from = (lane_id() & 60) | t;
+                ks[t] = __shfl(k0, from, kWave) + l4;
+                ls[t] = __shfl(len, from, kWave) - l4;
+                xs[t] = __shfl(x, from, kWave);
+                most = max(most, ls[t]);
+            }
+            for (int d = 0; __any(d < most); d += 4) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int k = min(ks[t] + d, last);
+                    row[t] = d < ls[t] ? a.row_idx[k] : r0;
+                    v[t] = d < ls[t] ? vals[k] : (typename S::V)0;
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (d < ls[t]) S::lds_atomic_add(&y[row[t] - r0], S::mul(v[t], xs[t]));
+            }
+        }
+        __syncthreads();
+        const int nr = min(R, a.m - r0);
+        auto* out = (typename S::Y*)a.Y + (int64_t)b * a.m + r0;
+        for (int r = threadIdx.x; r < nr; r += kRowsThreads) __builtin_nontemporal_store(S::out(y[r]), out + r);
+    }
+}
+
+// The first entry of column j in rows from block k on, at j * nblk + k; nnz at
+// the end, so that each entry of the table ends the segment before it.
+__global__ __launch_bounds__(kBlock) void k_segs(int64_t total, int32_t nblk, int32_t rows, int32_t nnz,
+                                                 const int32_t* __restrict__ col_ptr,
+                                                 const int32_t* __restrict__ row_idx, int32_t* __restrict__ segs) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i <= total; i += (int64_t)gridDim.x * kBlock) {
+        if (i == total) {
+            segs[i] = nnz;
+            continue;
+        }
+        const int64_t j = i / nblk;
+        const int64_t from = (i - j * nblk) * rows;
+        int lo = col_ptr[j], hi = from ? col_ptr[j + 1] : lo;
+        while (lo < hi) {
+            const int mid = lo + ((hi - lo) >> 1);
+            if (row_idx[mid] < from)
+                lo = mid + 1;
+            else
+                hi = mid;
+        }
+        segs[i] = lo;
     }
 }
 
@@ -587,28 +855,9 @@ __global__ __launch_bounds__(kBlock) void k_batch_phase(BatchDev a) {
         const int item = s_item;
         __syncthreads();
         if (item >= total) break;
-        const int local = item;
         const int32_t* off = a.offs + ph * (a.B + 1);
-        if (local >= off[a.B]) {
-            // a fused group item (phase A: zero kSplitZeroRows split rows of
-            // Y for the group's vectors)
-            if constexpr (PH == 0) {
-                const int gi = local - off[a.B];
-                const int per = (int)ceil_div(a.nsplit, kSplitZeroRows);
-                const int g = gi / per;
-                const int s0 = (gi % per) * kSplitZeroRows;
-                const int ns = min(kSplitZeroRows, a.nsplit - s0);
-                const int gs = a.gsize;
-                const int nvec = min(gs, *a.gcount - g * gs);
-                for (int t = threadIdx.x; t < ns * nvec; t += kBlock) {
-                    const int b = a.gvec[g * gs + t % nvec];
-                    ((typename S::Y*)a.Y)[(int64_t)b * a.m + a.split_rows[s0 + t / nvec]] = (typename S::Y)0;
-                }
-            }
-            continue;
-        }
-        const int b = find_vector(off_in_lds ? s_voff : off, a.B, local);
-        const int j = local - off[b];
+        const int b = find_vector(off_in_lds ? s_voff : off, a.B, item);
+        const int j = item - off[b];
         const BatchPlan p = a.plans[b];
         auto* Yb = (typename S::Y*)a.Y + (int64_t)b * a.m;
         uint32_t* bits = a.bits_all + (int64_t)b * a.nwords;
@@ -616,30 +865,6 @@ __global__ __launch_bounds__(kBlock) void k_batch_phase(BatchDev a) {
         const int32_t* idx = a.idx + p.base;
         const typename S::X* xv = S::kVals ? xval_all + p.base : nullptr;
         const bool csc = p.pattern == SPX_PAT_CSC_SPMSPV;
-        if (p.gslot >= 0) {
-            if constexpr (PH != 1) {
-                if constexpr (S::kVals) {
-                    // the chunk's kScatterChunk entries, eight per thread with
-                    // every load of a step in flight before the stores
-                    const int gs = a.gsize;
-                    auto* xt = (typename S::X*)a.xt_all + (int64_t)(p.gslot / gs) * a.n * gs + p.gslot % gs;
-                    const int e1 = std::min(p.nnz_x, (j + 1) * kScatterChunk);
-                    constexpr int kPer = kScatterChunk / kBlock;
-                    int c[kPer];
-                    typename S::X v[kPer];
-#pragma unroll
-                    for (int q = 0; q < kPer; ++q) {
-                        const int e = j * kScatterChunk + q * kBlock + threadIdx.x;
-                        c[q] = e < e1 ? idx[e] : -1;
-                        v[q] = (PH == 0 && e < e1) ? xv[e] : (typename S::X)0;
-                    }
-#pragma unroll
-                    for (int q = 0; q < kPer; ++q)
-                        if (c[q] >= 0) xt[(int64_t)c[q] * gs] = v[q];
-                }
-            }
-            continue;
-        }
         if constexpr (PH == 0) {
             if (csc) {
                 const int64_t r0 = (int64_t)j * kFillChunk;
@@ -713,10 +938,31 @@ __global__ __launch_bounds__(kBlock) void k_batch_phase(BatchDev a) {
 }
 
 // ------------------------------------------------------------------ host side
+// Blocks of rows of a column-major vector's Y, or 0 where its products go to Y
+// with atomics. By blocks is faster down to an entry in eight segments (128
+// vectors of density 1 % on 2^18 x 2^18, float32: 72 against 134 us with 2
+// entries per row, 85 against 246 with 8, 122 against 623 with 32; density
+// 0.05 %: 42 against 95 us); beyond that the table of segments is more than
+// four times A.
+int32_t batch_row_blocks(int32_t m, int32_t n, int64_t nnz, int dtype) {
+    if (dtype == SPX_BOOL || m <= 0 || n <= 0) return 0;
+    const int64_t nblk = ceil_div(m, kRowsBytes / (dtype == SPX_F64 ? 8 : 4));
+    return n * nblk <= 8 * nnz && n * nblk < ((int64_t)1 << 31) ? (int32_t)nblk : 0;
+}
+
+spx_status batch_build_segs(const spx_csr& A, const int32_t* col_ptr, const int32_t* row_idx, int32_t nblk,
+                            int32_t* segs, hipStream_t s) {
+    const int64_t total = (int64_t)A.n * nblk;
+    k_segs<<<(unsigned)std::min<int64_t>(ceil_div(total + 1, kBlock), 65536), kBlock, 0, s>>>(
+        total, nblk, kRowsBytes / (A.dtype == SPX_F64 ? 8 : 4), A.nnz, col_ptr, row_idx, segs);
+    SPX_HIP(hipGetLastError());
+    return SPX_OK;
+}
+
 static void batch_layout(int32_t m, int32_t n, int dtype, int32_t B, int64_t cap_nnz_x, int64_t tiles_mat,
-                         BatchDev* d, char* base, size_t* bytes) {
+                         bool by_rows, BatchDev* d, char* base, size_t* bytes) {
     Sizer z;
-    size_t off[16];
+    size_t off[20];
     int k = 0;
     auto take = [&](size_t n_bytes) {
         z.used = align_up(z.used, 256);
@@ -726,26 +972,29 @@ static void batch_layout(int32_t m, int32_t n, int dtype, int32_t B, int64_t cap
     const int vs = std::max(1, value_size(dtype));
     const int as = dtype == SPX_F64 ? 8 : 4;
     const int64_t nwords = ceil_div(n, 32) + 1;
+    const int32_t vB = by_rows ? 0 : B;  // vectors that k_batch_phase may run
     take(sizeof(BatchPlan) * (size_t)B);                 // 0 plans
     take(4 * (size_t)3 * (B + 1));                       // 1 offs
     take(4 * 4);                                          // 2 totals
-    take(4 * 8);                                          // 3 queue heads, err, two fused walk heads
-    take(4);                                              // 4 group count
-    take(4 * (size_t)(cap_nnz_x + B));                    // 5 excl
-    take(4 * (size_t)B * nwords);                         // 6 bits (self-cleaning)
-    take((size_t)vs * B * (size_t)n);                     // 7 xd (self-cleaning)
-    take(4 * (size_t)B * tiles_mat);                      // 8 carry rows
-    take((size_t)as * B * tiles_mat);                     // 9 carry values
+    take(4 * 8);                                          // 3 queue heads, err of the last run, err
+    take(4);                                              // 4 vectors in groups
+    take(by_rows ? 0 : 4 * (size_t)(cap_nnz_x + B));      // 5 excl
+    take(4 * (size_t)vB * nwords);                        // 6 bits (self-cleaning)
+    take((size_t)vs * vB * (size_t)n);                    // 7 xd (self-cleaning)
+    take(4 * (size_t)vB * tiles_mat);                     // 8 carry rows
+    take((size_t)as * vB * tiles_mat);                    // 9 carry values
     take(4 * (size_t)B);                                  // 10 group slot -> vector
-    const int64_t gsize = (int64_t)kGroup * (vs == 4 ? 2 : 1);
-    take((size_t)vs * ceil_div(B, gsize) * gsize * (size_t)n);  // 11 group slabs (self-cleaning)
+    const int64_t gsize = kSlabRow / (vs == 8 ? 8 : 4);
+    take((size_t)kSlabRow * ceil_div(B, gsize) * ((size_t)n + 1));  // 11 group slabs
+    take(8 * 128);                                        // 12 queue heads of the groups' walk
+    take(4 * (size_t)B);                                  // 13 the vectors' stray flags
     *bytes = z.used;
     if (!d || !base) return;
     d->plans = (BatchPlan*)(base + off[0]);
     d->offs = (int32_t*)(base + off[1]);
     d->totals = (int32_t*)(base + off[2]);
     d->queue = (int32_t*)(base + off[3]);
-    d->err = d->queue + 3;
+    d->err = d->queue + 4;
     d->excl_all = (int32_t*)(base + off[5]);
     d->bits_all = (uint32_t*)(base + off[6]);
     d->xd_all = base + off[7];
@@ -753,15 +1002,17 @@ static void batch_layout(int32_t m, int32_t n, int dtype, int32_t B, int64_t cap
     d->carry_val_all = base + off[9];
     d->nwords = nwords;
     d->gcount = (int32_t*)(base + off[4]);
+    d->heads = (int32_t*)(base + off[12]);
+    d->stray = (int32_t*)(base + off[13]);
     d->gvec = (int32_t*)(base + off[10]);
     d->xt_all = base + off[11];
     d->gsize = (int32_t)gsize;
 }
 
 size_t batch_ws_size(int32_t m, int32_t n, int dtype, int32_t B, int64_t cap_nnz_x, int64_t tiles_mat,
-                     size_t* zero_from, size_t* zero_bytes) {
+                     bool by_rows, size_t* zero_from, size_t* zero_bytes) {
     size_t bytes = 0;
-    batch_layout(m, n, dtype, B, cap_nnz_x, tiles_mat, nullptr, nullptr, &bytes);
+    batch_layout(m, n, dtype, B, cap_nnz_x, tiles_mat, by_rows, nullptr, nullptr, &bytes);
     // the whole workspace is zeroed at allocation; only the bitvector and
     // value slots rely on it (they are self-cleaning afterwards)
     if (zero_from) *zero_from = 0;
@@ -794,67 +1045,54 @@ spx_status launch_batch(const BatchLaunch& L, void* ws, size_t ws_bytes, hipStre
     d.nunits = L.nunits;
     d.split_rows = L.split_rows;
     d.nsplit = L.nsplit;
+    d.segs = L.segs;
+    d.nblk = L.nblk;
     size_t need = 0;
-    batch_layout(d.m, d.n, L.csr.dtype, L.B, L.cap_nnz_x, L.tiles_mat, &d, (char*)ws, &need);
+    // laid out for the capacity, not for this call's B: the parts that are kept
+    // zero between runs stay where they are
+    batch_layout(d.m, d.n, L.csr.dtype, L.cap_B, L.cap_nnz_x, L.tiles_mat, L.segs != nullptr, &d, (char*)ws, &need);
     if (need > ws_bytes) return fail(SPX_ERR_WORKSPACE, "run_batch: workspace too small");
-    if (err_dev) *err_dev = d.err;
+    if (err_dev) *err_dev = d.queue + 3;
     if (L.B == 0) return SPX_OK;
     // a group's slab addressed by 32-bit buffer offsets when it fits
-    const int vsz = std::max(1, value_size(L.csr.dtype));
-    const bool slab_buf = (int64_t)d.n * d.gsize * vsz < ((int64_t)1 << 31);
-    // the fused walk's items are dealt out by a grid stride, so its grid is
-    // what stays resident at once (no late workgroup forms a tail)
+    const bool slab_buf = (int64_t)(d.n + (int64_t)1) * kSlabRow < ((int64_t)1 << 31);
+    // the walk's grid is what stays resident at once, a multiple of the XCDs
     auto resident = [&](const void* fn) {
-        int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlock, 0) != hipSuccess || per_cu < 1)
-            per_cu = 1;
+        int per_cu = *L.fused_per_cu;
+        if (per_cu == 0) {
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlock, 0) != hipSuccess || per_cu < 1)
+                per_cu = 1;
+            *L.fused_per_cu = per_cu;
+        }
         return (unsigned)std::max(1, L.persistent_grid / 4) * (unsigned)per_cu;
     };
-    unsigned fused_grid = 1, fused_grid2 = 1;
+    // vectors per launch of k_batch_rows: a grid holds fewer than 2^32 threads
+    const int32_t rows_step = (int32_t)std::max<int64_t>(8, ((1 << 21) / std::max(1, d.nblk)) & ~7);
     const bool fused = L.csr.dtype != SPX_BOOL && d.units && d.nunits > 0;
-    const bool branch = L.side && L.fork && L.join;
-    hipStream_t fs = branch ? L.side : s;
     switch (L.csr.dtype) {
-#define SPX_DT(DT)                                                                                      \
-    case DT:                                                                                            \
-        fused_grid = slab_buf ? resident((const void*)k_batch_fused<DT, true, 1>)                       \
-                              : resident((const void*)k_batch_fused<DT, false, 1>);                     \
-        fused_grid2 = slab_buf ? resident((const void*)k_batch_fused<DT, true, group_vpl<DT>()>)        \
-                               : resident((const void*)k_batch_fused<DT, false, group_vpl<DT>()>);      \
-        break;
-        SPX_DT(SPX_F32)
-        SPX_DT(SPX_F64)
-        SPX_DT(SPX_I32)
-#undef SPX_DT
-        default:
-            break;
-    }
-    switch (L.csr.dtype) {
-#define SPX_DT(DT)                                                            \
-    case DT:                                                                  \
-        k_batch_reset<<<1, 1, 0, s>>>(d.err, d.gcount);                       \
-        k_batch_plan<DT><<<L.B, kBlock, 0, s>>>(d);                           \
-        k_batch_scan<<<1, kBlock, 0, s>>>(d);                                 \
-        k_batch_phase<DT, 0><<<L.persistent_grid, kBlock, 0, s>>>(d);         \
-        if (fused) {                                                          \
-            if (branch) {                                                     \
-                SPX_HIP(hipEventRecord(L.fork, s));                           \
-                SPX_HIP(hipStreamWaitEvent(L.side, L.fork, 0));               \
-            }                                                                 \
-            if (slab_buf) {                                                   \
-                k_batch_fused<DT, true, 1><<<fused_grid, kBlock, 0, fs>>>(d); \
-                if (d.gsize > kGroup)                                         \
-                    k_batch_fused<DT, true, group_vpl<DT>()><<<fused_grid2, kBlock, 0, fs>>>(d); \
-            } else {                                                          \
-                k_batch_fused<DT, false, 1><<<fused_grid, kBlock, 0, fs>>>(d); \
-                if (d.gsize > kGroup)                                         \
-                    k_batch_fused<DT, false, group_vpl<DT>()><<<fused_grid2, kBlock, 0, fs>>>(d); \
-            }                                                                 \
-            if (branch) SPX_HIP(hipEventRecord(L.join, L.side));              \
-        }                                                                     \
-        k_batch_phase<DT, 1><<<L.persistent_grid, kBlock, 0, s>>>(d);         \
-        if (fused && branch) SPX_HIP(hipStreamWaitEvent(s, L.join, 0));       \
-        k_batch_phase<DT, 2><<<L.persistent_grid, kBlock, 0, s>>>(d);         \
+#define SPX_DT(DT)                                                                                    \
+    case DT:                                                                                          \
+        k_batch_plan<DT><<<L.B, kBlock, 0, s>>>(d);                                                   \
+        k_batch_scan<<<1, kBlock, 0, s>>>(d);                                                         \
+        if (fused) {                                                                                  \
+            k_batch_slabs<DT><<<L.persistent_grid, kBlock, 0, s>>>(d);                                \
+            k_batch_stray<DT><<<L.B, kBlock, 0, s>>>(d);                                              \
+            if (slab_buf)                                                                             \
+                k_batch_fused<DT, true><<<resident((const void*)k_batch_fused<DT, true>), kBlock, 0, s>>>(d);\
+            else                                                                                      \
+                k_batch_fused<DT, false><<<resident((const void*)k_batch_fused<DT, false>), kBlock, 0, s>>>(d);\
+        }                                                                                             \
+        if (d.segs) {                                                                                 \
+            SPX_HIP(hipFuncSetAttribute((const void*)k_batch_rows<DT>,                                \
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, kRowsBytes));     \
+            for (int32_t b0 = 0; b0 < L.B; b0 += std::min(rows_step, L.B - b0))                       \
+                k_batch_rows<DT><<<(unsigned)(ceil_div(std::min(rows_step, L.B - b0), 8) * 8 * d.nblk), \
+                                   kRowsThreads, kRowsBytes, s>>>(d, b0);                             \
+        } else {                                                                                      \
+            k_batch_phase<DT, 0><<<L.persistent_grid, kBlock, 0, s>>>(d);                             \
+            k_batch_phase<DT, 1><<<L.persistent_grid, kBlock, 0, s>>>(d);                             \
+            k_batch_phase<DT, 2><<<L.persistent_grid, kBlock, 0, s>>>(d);                             \
+        }                                                                                             \
         break;
         SPX_DT(SPX_F32)
         SPX_DT(SPX_F64)

@@ -147,6 +147,19 @@ struct SR<SPX_BOOL> {
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+// Buffer loads: a 32-bit byte offset from a base in scalar registers, and 0
+// for what lies past the size (no branch around the load).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
+}
+template <typename T, int AUX = 0>
+__device__ __forceinline__ T buffer_value(__amdgpu_buffer_rsrc_t r, int at) {
+    if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, at, 0, AUX));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, AUX));
+}
+
 // ---------------------------------------------------------------------------
 // Bounded accumulation chains. A kernel that walks a long row (or column)
 // keeps U independent partial sums, one per unrolled load slot, and every

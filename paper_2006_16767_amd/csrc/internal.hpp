@@ -237,6 +237,7 @@ struct BatchLaunch {
     const int32_t* part;  // merge-path partition of A at tile 2048
     int64_t tiles_mat;
     int32_t B;
+    int32_t cap_B;  // vectors and entries the workspace is laid out for
     int64_t cap_nnz_x;
     const int32_t* vec_ptr;
     const int32_t* idx;
@@ -252,16 +253,18 @@ struct BatchLaunch {
     int32_t nunits;
     const int32_t* split_rows;
     int32_t nsplit;
-    // while the launches are captured: a second stream and two events that
-    // put the fused groups' walk on a branch of its own, beside the
-    // per-vector tiles (null: one stream)
-    hipStream_t side;
-    hipEvent_t fork, join;
+    // the columns' segments in blocks of rows (batch_build_segs), or null
+    const int32_t* segs;
+    int32_t nblk;
+    int32_t* fused_per_cu;  // resident workgroups of the walk per CU, 0 = not asked yet (kept by the handle)
 };
 constexpr int kFusedUnitNnz = 512;
-constexpr int kFusedUnitRows = 63;
+constexpr int kFusedUnitRows = 32;
 size_t batch_ws_size(int32_t m, int32_t n, int dtype, int32_t B, int64_t cap_nnz_x, int64_t tiles_mat,
-                     size_t* zero_from, size_t* zero_bytes);
+                     bool by_rows, size_t* zero_from, size_t* zero_bytes);
+int32_t batch_row_blocks(int32_t m, int32_t n, int64_t nnz, int dtype);
+spx_status batch_build_segs(const spx_csr& A, const int32_t* col_ptr, const int32_t* row_idx, int32_t nblk,
+                            int32_t* segs, hipStream_t s);  // n * nblk + 1 words
 spx_status launch_batch(const BatchLaunch& L, void* ws, size_t ws_bytes, hipStream_t s, int32_t** err_dev);
 
 // breadth-first search (bfs.hip). count points at two packed 64-bit

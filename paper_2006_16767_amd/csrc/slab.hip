@@ -68,19 +68,6 @@ constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;      // quad_perm
 constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;    // rotations of a row of 16 lanes
 constexpr int kDppBcast = 0x150;                     // row_newbcast: lane n of the row to all
 
-// Buffer loads: a 32-bit byte offset from a base in scalar registers, and 0
-// for what lies past the size (no branch around the load).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000);
-}
-template <typename T>
-__device__ __forceinline__ T buffer_value(__amdgpu_buffer_rsrc_t r, int at) {
-    if constexpr (sizeof(T) == 4)
-        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0));
-    else
-        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, 0));
-}
-
 template <typename T>
 struct alignas(16) SlabVec {
     static constexpr int E = 16 / sizeof(T);  // values per 16-byte LDS read
