@@ -13,6 +13,7 @@ does, and fails loudly if it has not been built.
 from __future__ import annotations
 
 import ctypes as C
+import itertools
 
 from . import _lib
 from ._lib import (BOOL, DIST_BALANCED, DIST_DIRECT, F32, F32_MINPLUS, F64, I32, NO_SYNC, PAT_CSC_SPMSPV,
@@ -112,6 +113,19 @@ def _vec(x, n):
         return _lib.Vec(_lib.VEC_SPARSE, n, int(idx.numel()), _ptr(idx), _ptr(val)), (idx, val)
     # the library checks the dense length against the matrix's n
     return _lib.Vec(_lib.VEC_DENSE, int(x.numel()), -1, None, _ptr(x)), (x,)
+
+
+def _unset_plans(cap: int):
+    """Plans for a graph driver to fill from the front: those it does not
+    reach keep pattern -1. (Setting and reading 4096 of them one by one took
+    350 us a call, more than a search.)"""
+    plans = (Plan * cap)()
+    C.memset(plans, 0xFF, C.sizeof(plans))
+    return plans
+
+
+def _set_plans(plans):
+    return list(itertools.takewhile(lambda p: p.pattern >= 0, plans))
 
 
 class Matrix:
@@ -348,15 +362,13 @@ class Matrix:
         level = torch.empty(self.n, dtype=torch.int32, device=self.row_ptr.device)
         nl = C.c_int32(0)
         cap = 4096
-        plans = (Plan * cap)()
-        for i in range(cap):
-            plans[i].pattern = -1  # entries the search does not reach stay -1
+        plans = _unset_plans(cap)
         # a masked-pull level comes back with lanes = -1
         _lib.call("spx_bfs", self._h, int(source), _ptr(level), int(max_levels),
                   None if plan is None else C.byref(plan), _lib.BFS_PUSH_ONLY if push_only else 0, C.byref(nl),
                   plans, cap, _stream(stream))
         self.bfs_levels = nl.value
-        return level, [plans[i] for i in range(cap) if plans[i].pattern >= 0]
+        return level, _set_plans(plans)
 
     def pack_mask(self, rows_mask, stream=None):
         """A bool / uint8 tensor of m entries as the bitvector (int32 words,
@@ -404,14 +416,12 @@ class Matrix:
         res = self.out_tensor() if want_residual else None
         ni = C.c_int32(0)
         cap = 4096
-        plans = (Plan * cap)()
-        for i in range(cap):
-            plans[i].pattern = -1
+        plans = _unset_plans(cap)
         _lib.call("spx_pagerank", self._h, float(damping), float(eps), int(max_iters),
                   None if plan is None else C.byref(plan), _ptr(rank), None if res is None else _ptr(res),
                   C.byref(ni), plans, cap, _stream(stream))
         self.pr_iters = ni.value
-        out = [plans[i] for i in range(cap) if plans[i].pattern >= 0]
+        out = _set_plans(plans)
         return (rank, res, out) if want_residual else (rank, out)
 
     def batch_status(self, stream=None) -> int:

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -248,8 +249,7 @@ struct spx_matrix {
     uint8_t* bfs_y = nullptr;
     int32_t* drv_count = nullptr;     // two packed counters of the graph drivers
     uint32_t* bfs_bits[2] = {nullptr, nullptr};
-    int32_t* drv_host = nullptr;      // pinned copies of the counters (two slots of 16 bytes)
-    hipEvent_t drv_ev[2] = {nullptr, nullptr};
+    unsigned long long* drv_host = nullptr;  // pinned: the totals of the last two rounds
     // trees for callers that know nnz_s without a device round trip (the
     // graph drivers); the host-feature trees otherwise
     Selector sel_known;
@@ -511,8 +511,6 @@ extern "C" spx_status spx_matrix_destroy(spx_matrix* H) {
     tile_sorted_free(&H->ts);
     if (H->drv_host) hipHostFree(H->drv_host);
     if (H->cnt_host) hipHostFree(H->cnt_host);
-    for (auto& e : H->drv_ev)
-        if (e) hipEventDestroy(e);
     for (auto& e : H->ev_conv) {
         hipEventDestroy(e.first);
         hipEventDestroy(e.second);
@@ -1570,23 +1568,37 @@ static spx_status ensure_driver_counters(spx_matrix* H) {
     if (H->drv_host) return SPX_OK;
     if (!H->drv_count && hipMalloc((void**)&H->drv_count, 256) != hipSuccess)
         return fail(SPX_ERR_ALLOC, "driver counters: allocation failed");
-    for (auto& e : H->drv_ev)
-        if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-            e = nullptr;
-            return fail(SPX_ERR_HIP, "driver events: creation failed");
-        }
-    if (hipHostMalloc((void**)&H->drv_host, 64, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void**)&H->drv_host, 64, hipHostMallocCoherent) != hipSuccess) {
         H->drv_host = nullptr;
         return fail(SPX_ERR_ALLOC, "driver counters: pinned allocation failed");
     }
     return SPX_OK;
 }
 
-// Copies counter (round & 1) to the pinned host words drv_host[0..1] and
-// waits for it.
-static spx_status read_driver_counter(spx_matrix* H, int32_t round, hipStream_t s) {
-    SPX_HIP(hipMemcpyAsync(H->drv_host, H->drv_count + 2 * (round & 1), 8, hipMemcpyDeviceToHost, s));
-    SPX_HIP(hipStreamSynchronize(s));
+// The pinned word of a round, marked as not written yet: before the launch
+// whose last workgroup stores the round's total there.
+static void* open_driver_count(spx_matrix* H, int32_t round) {
+    volatile unsigned long long* h = H->drv_host + (round & 1);
+    *h = ~0ull;
+    std::atomic_thread_fence(std::memory_order_seq_cst);
+    return (void*)h;
+}
+
+// Waits for the total of the round: a kernel that is queued behind it on the
+// stream does not hold the host up. After a second without a result the
+// stream is synchronized, which reports a failed launch.
+static spx_status read_driver_count(spx_matrix* H, int32_t round, hipStream_t s, int32_t* low, int64_t* high) {
+    volatile unsigned long long* h = H->drv_host + (round & 1);
+    const auto t0 = std::chrono::steady_clock::now();
+    unsigned long long v = *h;
+    while (v == ~0ull && std::chrono::steady_clock::now() - t0 < std::chrono::seconds(1)) v = *h;
+    if (v == ~0ull) {
+        SPX_HIP(hipStreamSynchronize(s));
+        v = *h;
+    }
+    if (v == ~0ull) return fail(SPX_ERR_HIP, "graph driver: the kernel wrote no count");
+    *low = (int32_t)(uint32_t)v;
+    *high = (int64_t)(v >> 32);
     return SPX_OK;
 }
 
@@ -1626,12 +1638,12 @@ extern "C" spx_status spx_bfs(spx_matrix* H, int32_t source, int32_t* level, int
             return fail(SPX_ERR_ALLOC, "breadth-first search buffers: allocation failed");
     }
     const bool may_pull = !plan && !(flags & SPX_BFS_PUSH_ONLY);
-    SPX_TRY(launch_bfs_seed(A.n, source, H->col_ptr, level, H->bfs_front[0], H->bfs_bits[0], H->drv_count, s));
-    auto read_count = [&](int32_t L) { return read_driver_counter(H, L, s); };
-    SPX_TRY(read_count(0));
+    SPX_TRY(launch_bfs_seed(A.n, source, H->col_ptr, level, H->bfs_front[0], H->bfs_bits[0], H->drv_count,
+                            open_driver_count(H, 0), s));
     int cur = 0;
-    int32_t nf = H->drv_host[0];
-    int64_t mf = H->drv_host[1];          // out-edges of the frontier
+    int32_t nf = 0;
+    int64_t mf = 0;  // out-edges of the frontier
+    SPX_TRY(read_driver_count(H, 0, s, &nf, &mf));
     int64_t mu = (int64_t)A.nnz - mf;     // out-edges of the unvisited vertices
     bool pull = false;
     int32_t depth = 1;  // levels labelled so far
@@ -1643,9 +1655,10 @@ extern "C" spx_status spx_bfs(spx_matrix* H, int32_t source, int32_t* level, int
                 pull = false;
         }
         spx_plan p{};
+        void* host = open_driver_count(H, depth);
         if (pull) {
             SPX_TRY(launch_bfs_pull(A.n, A.row_ptr, A.col_idx, H->bfs_bits[cur], depth, H->col_ptr, level,
-                                    H->bfs_front[cur ^ 1], H->bfs_bits[cur ^ 1], H->drv_count, s));
+                                    H->bfs_front[cur ^ 1], H->bfs_bits[cur ^ 1], H->drv_count, host, s));
             p = spx_plan{SPX_PAT_CSR_SPMSPV, SPX_DIST_DIRECT, SPX_WB_NONE, -1, 0, 0};
         } else {
             spx_vec x{SPX_VEC_SPARSE, A.n, nf, H->bfs_front[cur], nullptr};
@@ -1657,16 +1670,15 @@ extern "C" spx_status spx_bfs(spx_matrix* H, int32_t source, int32_t* level, int
                 p = H->last_plan;
             }
             SPX_TRY(launch_bfs_update(A.n, H->bfs_y, depth, H->col_ptr, level, H->bfs_front[cur ^ 1],
-                                      H->bfs_bits[cur ^ 1], H->drv_count, s));
+                                      H->bfs_bits[cur ^ 1], H->drv_count, host, s));
         }
         if (depth - 1 < plans_cap) plans[depth - 1] = p;
-        SPX_TRY(read_count(depth));
-        nf = H->drv_host[0];
-        mf = H->drv_host[1];
+        SPX_TRY(read_driver_count(H, depth, s, &nf, &mf));
         mu -= mf;
         cur ^= 1;
         if (nf > 0) ++depth;
     }
+    SPX_HIP(hipStreamSynchronize(s));
     *n_levels = depth;
     return SPX_OK;
 }
@@ -1738,24 +1750,18 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
         SPX_TRY(launch_spmv_csr(&At, H->pr_xd[1], nullptr, H->pr_W, &bal, part, ws, s));
         SPX_HIP(hipMemcpyAsync(H->drv_host, H->pr_bad, 4, hipMemcpyDeviceToHost, s));
         SPX_HIP(hipStreamSynchronize(s));
-        if (H->drv_host[0]) return fail(SPX_ERR_ARG, "PageRank needs nonnegative edge weights");
+        if (*(const uint32_t*)H->drv_host) return fail(SPX_ERR_ARG, "PageRank needs nonnegative edge weights");
         H->pr_W_valid = true;
     }
     a.stage = PR_INIT;
     SPX_TRY(launch_pagerank(a, s));
-    SPX_TRY(fill_u32((uint32_t*)H->drv_count, 0u, 4, s));
-    // Round k's counter is copied to pinned slot k & 1 and marked by an
-    // event, so the host can wait for a round's select without waiting for
-    // the product queued behind it.
+    SPX_TRY(fill_u32((uint32_t*)H->drv_count, 0u, 64, s));
     auto enqueue_select = [&](int32_t round) -> spx_status {
         a.stage = PR_SELECT;
         a.round = round;
         a.y = round ? H->pr_y : nullptr;
-        SPX_TRY(launch_pagerank(a, s));
-        SPX_HIP(hipMemcpyAsync(H->drv_host + 4 * (round & 1), H->drv_count + 2 * (round & 1), 8,
-                               hipMemcpyDeviceToHost, s));
-        SPX_HIP(hipEventRecord(H->drv_ev[round & 1], s));
-        return SPX_OK;
+        a.host = open_driver_count(H, round);
+        return launch_pagerank(a, s);
     };
     auto choose = [&](int32_t nx, int64_t ns, spx_plan* q) -> spx_status {
         if (plan) {
@@ -1776,9 +1782,9 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
     spx_plan spec_plan{};
     for (int32_t round = 0; it < max_iters;) {
         if (round == 0) SPX_TRY(enqueue_select(0));
-        SPX_HIP(hipEventSynchronize(H->drv_ev[round & 1]));
-        const int32_t nx = H->drv_host[4 * (round & 1)];
-        const int64_t ns = H->drv_host[4 * (round & 1) + 1];  // column lengths of supp(x)
+        int32_t nx = 0;
+        int64_t ns = 0;  // column lengths of supp(x)
+        SPX_TRY(read_driver_count(H, round, s, &nx, &ns));
         spx_plan p{};
         if (spec) {
             // an empty x gave y = 0: nothing to count and nothing to fold

@@ -17,16 +17,15 @@
 
 namespace spx {
 
-// Two counters alternate between levels: level L appends into count[L & 1]
-// and clears the other one for level L + 1 (the host has read it before
-// level L is enqueued, on the same stream).
+// Level L appends into counter L & 1 and clears the other one for level L + 1
+// (the host has read it before level L is enqueued, on the same stream).
 //
 // level = -1 except the source (0); the frontier is the source, as a list
-// and as a bitvector; count[0] holds {1 vertex, out-degree of the source}
-// and count[1] is cleared.
+// and as a bitvector; the counter of level 0 holds {1 vertex, out-degree of
+// the source}, the other one is cleared.
 __global__ __launch_bounds__(kBlock) void k_bfs_seed(int32_t n, int32_t source, const int32_t* __restrict__ col_ptr,
                                                      int32_t* __restrict__ level, int32_t* __restrict__ frontier,
-                                                     uint32_t* __restrict__ bits, Count* __restrict__ count) {
+                                                     uint32_t* __restrict__ bits, Counters c) {
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n; v += stride)
         level[v] = v == source ? 0 : -1;
@@ -35,8 +34,11 @@ __global__ __launch_bounds__(kBlock) void k_bfs_seed(int32_t n, int32_t source, 
         bits[w] = w == source >> 5 ? 1u << (source & 31) : 0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         frontier[0] = source;
-        count[0] = ((Count)(uint32_t)(col_ptr[source + 1] - col_ptr[source]) << 32) | 1ull;
-        count[1] = 0;
+        const Count seed = ((Count)(uint32_t)(col_ptr[source + 1] - col_ptr[source]) << 32) | 1ull;
+        *c.count = seed;
+        *c.clear = 0;
+        *c.done = 0;
+        __hip_atomic_store(c.host, seed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -45,10 +47,9 @@ __global__ __launch_bounds__(kBlock) void k_bfs_seed(int32_t n, int32_t source, 
 __global__ __launch_bounds__(kWideBlock) void k_bfs_update(int32_t n, const uint8_t* __restrict__ y, int32_t L,
                                                        const int32_t* __restrict__ col_ptr,
                                                        int32_t* __restrict__ level, int32_t* __restrict__ next,
-                                                       uint32_t* __restrict__ next_bits,
-                                                       Count* __restrict__ count, Count* __restrict__ count_clear) {
+                                                       uint32_t* __restrict__ next_bits, Counters c) {
     __shared__ Count tmp[kWideBlock / kWave];
-    if (blockIdx.x == 0 && threadIdx.x == 0) *count_clear = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *c.clear = 0;
     for (int64_t base = (int64_t)blockIdx.x * kWideChunk; base < n; base += (int64_t)gridDim.x * kWideChunk) {
         const int64_t v0 = base + (int64_t)threadIdx.x * kVpt;
         uint64_t yy = 0;
@@ -70,8 +71,9 @@ __global__ __launch_bounds__(kWideBlock) void k_bfs_update(int32_t n, const uint
             }
         }
         write_bits(mask, v0, n, next_bits);
-        block_append<kWideBlock>(mask, v0, deg, next, count, tmp);
+        block_append<kWideBlock>(mask, v0, deg, next, c.count, tmp);
     }
+    publish_count(c);
 }
 
 // Masked pull (the row-major expansion restricted to the unvisited rows,
@@ -93,10 +95,9 @@ __global__ __launch_bounds__(kBlock) void k_bfs_pull(int32_t n, const int32_t* _
                                                      const uint32_t* __restrict__ bits, int32_t L,
                                                      const int32_t* __restrict__ col_ptr,
                                                      int32_t* __restrict__ level, int32_t* __restrict__ next,
-                                                     uint32_t* __restrict__ next_bits,
-                                                     Count* __restrict__ count, Count* __restrict__ count_clear) {
+                                                     uint32_t* __restrict__ next_bits, Counters c) {
     __shared__ uint8_t hit[kChunk];
-    if (blockIdx.x == 0 && threadIdx.x == 0) *count_clear = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *c.clear = 0;
     __shared__ int16_t open[kChunk];
     __shared__ int n_open;
     __shared__ Count tmp[kWavesPerBlock];
@@ -160,35 +161,35 @@ __global__ __launch_bounds__(kBlock) void k_bfs_pull(int32_t n, const int32_t* _
             }
         }
         write_bits(mask, v0, n, next_bits);
-        block_append<kBlock>(mask, v0, deg, next, count, tmp);
+        block_append<kBlock>(mask, v0, deg, next, c.count, tmp);
     }
+    publish_count(c);
 }
 
 spx_status launch_bfs_seed(int32_t n, int32_t source, const int32_t* col_ptr, int32_t* level, int32_t* frontier,
-                           uint32_t* bits, void* count, hipStream_t s) {
+                           uint32_t* bits, void* count, void* host, hipStream_t s) {
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, kBlock), 4096));
-    k_bfs_seed<<<grid, kBlock, 0, s>>>(n, source, col_ptr, level, frontier, bits, (Count*)count);
+    k_bfs_seed<<<grid, kBlock, 0, s>>>(n, source, col_ptr, level, frontier, bits, counters_of(count, 0, host));
     SPX_HIP(hipGetLastError());
     return SPX_OK;
 }
 
 spx_status launch_bfs_update(int32_t n, const uint8_t* y, int32_t L, const int32_t* col_ptr, int32_t* level,
-                             int32_t* next, uint32_t* next_bits, void* count, hipStream_t s) {
+                             int32_t* next, uint32_t* next_bits, void* count, void* host, hipStream_t s) {
     if ((uintptr_t)y % 8) return fail(SPX_ERR_ARG, "breadth-first search: product buffer must be 8-byte aligned");
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, kWideChunk), 2048));
-    Count* c = (Count*)count;
-    k_bfs_update<<<grid, kWideBlock, 0, s>>>(n, y, L, col_ptr, level, next, next_bits, c + (L & 1), c + ((L - 1) & 1));
+    k_bfs_update<<<grid, kWideBlock, 0, s>>>(n, y, L, col_ptr, level, next, next_bits,
+                                           counters_of(count, L, host));
     SPX_HIP(hipGetLastError());
     return SPX_OK;
 }
 
 spx_status launch_bfs_pull(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, const uint32_t* bits,
                            int32_t L, const int32_t* col_ptr, int32_t* level, int32_t* next, uint32_t* next_bits,
-                           void* count, hipStream_t s) {
+                           void* count, void* host, hipStream_t s) {
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, kChunk), 2048));
-    Count* c = (Count*)count;
-    k_bfs_pull<<<grid, kBlock, 0, s>>>(n, row_ptr, col_idx, bits, L, col_ptr, level, next, next_bits, c + (L & 1),
-                                       c + ((L - 1) & 1));
+    k_bfs_pull<<<grid, kBlock, 0, s>>>(n, row_ptr, col_idx, bits, L, col_ptr, level, next, next_bits,
+                                       counters_of(count, L, host));
     SPX_HIP(hipGetLastError());
     return SPX_OK;
 }

@@ -17,6 +17,39 @@ namespace spx {
 // 2^31), so one atomic add updates both.
 using Count = unsigned long long;
 
+// The drivers' counter words in device memory: two counters that alternate
+// between rounds (round k appends into count[k & 1] and clears the other one),
+// and a cache line further the workgroups of the running kernel that have
+// finished. host: a pinned word that takes the round's total.
+struct Counters {
+    Count* count;
+    Count* clear;
+    uint32_t* done;
+    Count* host;
+};
+constexpr Count kNoCount = ~0ull;  // in the pinned word: not written yet
+
+inline Counters counters_of(void* words, int32_t round, void* host) {
+    Count* c = (Count*)words;
+    return Counters{c + (round & 1), c + ((round + 1) & 1), (uint32_t*)(c + 16), (Count*)host};
+}
+
+// The workgroup has added its share: the last one to come here stores the
+// total to the pinned word, which the host polls. (A copy of the counter and a
+// stream synchronization per round cost 4 us and 20 to 30 us until the next
+// launch.) The word itself is all that the host reads, and kernels see each
+// other's data by stream order, so there is no fence, only the wait for the
+// workgroup's own add.
+__device__ __forceinline__ void publish_count(const Counters& c) {
+    if (threadIdx.x != 0) return;
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+    if (atomicAdd(c.done, 1u) + 1 == gridDim.x) {
+        *c.done = 0;
+        __hip_atomic_store(c.host, atomicAdd(c.count, 0ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 // Vertices per thread: a workgroup owns NT * kVpt consecutive vertices and
 // appends the ones it selects with a single atomic on the counter. Atomics
 // on one word serialize (about 12 ns each on this GPU, so one per wave

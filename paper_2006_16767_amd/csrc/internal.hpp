@@ -267,23 +267,23 @@ spx_status batch_build_segs(const spx_csr& A, const int32_t* col_ptr, const int3
                             int32_t* segs, hipStream_t s);  // n * nblk + 1 words
 spx_status launch_batch(const BatchLaunch& L, void* ws, size_t ws_bytes, hipStream_t s, int32_t** err_dev);
 
-// breadth-first search (bfs.hip). count points at two packed 64-bit
-// frontier counters {vertices (low half), their out-degrees (high half)},
-// read on the host as two int32 words (little-endian); level L appends
-// into count[L & 1] and clears the other. The bitvectors hold
-// ceil(n / 32) words.
+// breadth-first search (bfs.hip). count: the graph drivers' counter words
+// (frontier.hpp; 256 bytes), two packed 64-bit frontier counters {vertices
+// (low half), their out-degrees (high half)}; host: the pinned word that takes
+// the level's total when the kernel's last workgroup is done (set to all ones
+// before the launch). Level L appends into counter L & 1 and clears the other.
+// The bitvectors hold ceil(n / 32) words.
 spx_status launch_bfs_seed(int32_t n, int32_t source, const int32_t* col_ptr, int32_t* level, int32_t* frontier,
-                           uint32_t* bits, void* count, hipStream_t s);
+                           uint32_t* bits, void* count, void* host, hipStream_t s);
 spx_status launch_bfs_update(int32_t n, const uint8_t* y, int32_t L, const int32_t* col_ptr, int32_t* level,
-                             int32_t* next, uint32_t* next_bits, void* count, hipStream_t s);
+                             int32_t* next, uint32_t* next_bits, void* count, void* host, hipStream_t s);
 spx_status launch_bfs_pull(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, const uint32_t* bits,
                            int32_t L, const int32_t* col_ptr, int32_t* level, int32_t* next, uint32_t* next_bits,
-                           void* count, hipStream_t s);
+                           void* count, void* host, hipStream_t s);
 
 // incremental PageRank (pagerank.hip): one launch per stage. count: two
 // packed counters as for breadth-first search, {entries appended to x,
-// their column lengths}; round s appends into count[s & 1], clears the
-// other.
+// their column lengths}, and host the pinned word of the round.
 enum PrStage { PR_NEGCHECK, PR_ONES, PR_INIT, PR_SELECT, PR_FOLD };
 struct PrArgs {
     int stage = PR_INIT;
@@ -305,6 +305,7 @@ struct PrArgs {
     void* xd[2] = {nullptr, nullptr};  // dense (alternating, 16-byte aligned),
     const int32_t* map = nullptr;      // at map[v] (nullptr: v)
     void* count = nullptr;
+    void* host = nullptr;
 };
 spx_status launch_pagerank(const PrArgs& a, hipStream_t s);
 

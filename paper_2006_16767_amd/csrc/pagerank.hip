@@ -86,7 +86,7 @@ __device__ __forceinline__ void store8(T* __restrict__ a, int64_t v0, int32_t n,
 
 // One round. y = nullptr on the first round (no product yet). The counter
 // gets {appended entries of x (low), their column lengths (high), i.e. the
-// nnz_s of the next product}; count_clear is zeroed for the next round.
+// nnz_s of the next product}; the other counter is zeroed for the next round.
 // Besides the list (x_idx, x_val), x goes dense into xd_fill at position
 // map[v] (the column order of the row-major copy; v itself when map is
 // null): xd_fill was zeroed by the previous round, and this round zeroes
@@ -100,11 +100,10 @@ __global__ __launch_bounds__(kWideBlock) void k_pr_select(int32_t n, T d, T eps,
                                                       const T* __restrict__ W, const int32_t* __restrict__ col_ptr,
                                                       const int32_t* __restrict__ map, int32_t* __restrict__ x_idx,
                                                       T* __restrict__ x_val, T* __restrict__ xd_fill,
-                                                      T* __restrict__ xd_clear, Count* __restrict__ count,
-                                                      Count* __restrict__ count_clear) {
+                                                      T* __restrict__ xd_clear, Counters c) {
 #pragma clang fp contract(off)
     __shared__ Count tmp[kWideBlock / kWave];
-    if (blockIdx.x == 0 && threadIdx.x == 0) *count_clear = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *c.clear = 0;
     for (int64_t base = (int64_t)blockIdx.x * kWideChunk; base < n; base += (int64_t)gridDim.x * kWideChunk) {
         const int64_t v0 = base + (int64_t)threadIdx.x * kVpt;
         // all loads of a phase are independent, so they are in flight together
@@ -154,11 +153,12 @@ __global__ __launch_bounds__(kWideBlock) void k_pr_select(int32_t n, T d, T eps,
         if (y || act) store8(r, v0, n, rv);
         const T zero[kVpt] = {};
         store8(xd_clear, v0, n, zero);
-        block_append<kWideBlock>(mask, ns, count, tmp, [&](uint32_t slot, int j) {
+        block_append<kWideBlock>(mask, ns, c.count, tmp, [&](uint32_t slot, int j) {
             x_idx[slot] = (int32_t)(v0 + j);
             x_val[slot] = xv[j];
         });
     }
+    publish_count(c);
 }
 
 // r += d y (the product of the last round, when the rounds stop at the
@@ -192,11 +192,10 @@ static spx_status pr_t(const PrArgs& a, hipStream_t s) {
             break;
         case PR_SELECT: {
             const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(a.n, kWideChunk), 2048));
-            Count* c = (Count*)a.count;
             k_pr_select<T><<<grid, kWideBlock, 0, s>>>(a.n, (T)a.damping, (T)a.eps, (const T*)a.y, (T*)a.r, (T*)a.p,
                                                    (const T*)a.W, a.col_ptr, a.map, a.x_idx, (T*)a.x_val,
                                                    (T*)a.xd[a.round & 1], (T*)a.xd[(a.round + 1) & 1],
-                                                   c + (a.round & 1), c + ((a.round - 1) & 1));
+                                                   counters_of(a.count, a.round, a.host));
             break;
         }
         case PR_FOLD:
