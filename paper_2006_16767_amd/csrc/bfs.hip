@@ -42,6 +42,18 @@ __global__ __launch_bounds__(kBlock) void k_bfs_seed(int32_t n, int32_t source, 
     }
 }
 
+// The column lengths of the vertices v0 + j with bit j of mask set.
+__device__ __forceinline__ uint32_t degrees(uint32_t mask, int64_t v0, int32_t n, const int32_t* __restrict__ col_ptr) {
+    int32_t cp[kVpt];
+    load_run(col_ptr, v0, (int64_t)n + 1, cp);
+    const int32_t end = v0 + kVpt <= n ? col_ptr[v0 + kVpt] : 0;
+    uint32_t deg = 0;
+#pragma unroll
+    for (int j = 0; j < kVpt; ++j)
+        if ((mask >> j) & 1u) deg += (uint32_t)((j + 1 < kVpt ? cp[j + 1] : end) - cp[j]);
+    return deg;
+}
+
 // Vertices reached by the product and not labelled yet get level L and go
 // to the next frontier. Thread t of a chunk owns its 8 consecutive vertices.
 __global__ __launch_bounds__(kWideBlock) void k_bfs_update(int32_t n, const uint8_t* __restrict__ y, int32_t L,
@@ -59,15 +71,21 @@ __global__ __launch_bounds__(kWideBlock) void k_bfs_update(int32_t n, const uint
             for (int j = 0; v0 + j < n; ++j) yy |= (uint64_t)(y[v0 + j] != 0) << (8 * j);
         }
         uint32_t mask = 0, deg = 0;
+        if (yy) {
+            // the levels together, then the column pointers together (one
+            // vertex after the other is up to eight round trips of each)
+            int32_t lv[kVpt];
+            load_run(level, v0, n, lv);
 #pragma unroll
-        for (int j = 0; j < kVpt; ++j) {
-            if ((yy >> (8 * j)) & 0xffu) {
-                const int64_t v = v0 + j;
-                if (level[v] < 0) {
-                    level[v] = L;
+            for (int j = 0; j < kVpt; ++j) {
+                if (((yy >> (8 * j)) & 0xffu) && lv[j] < 0) {
+                    lv[j] = L;
                     mask |= 1u << j;
-                    deg += (uint32_t)(col_ptr[v + 1] - col_ptr[v]);
                 }
+            }
+            if (mask) {
+                store_run(level, v0, n, lv);
+                deg = degrees(mask, v0, n, col_ptr);
             }
         }
         write_bits(mask, v0, n, next_bits);
@@ -79,71 +97,88 @@ __global__ __launch_bounds__(kWideBlock) void k_bfs_update(int32_t n, const uint
 // Masked pull (the row-major expansion restricted to the unvisited rows,
 // with early exit). Row i of A lists the vertices with an edge into i; an
 // unvisited i joins level L at its first entry in the frontier's
-// bitvector (written by the previous level). Per chunk of kChunk rows:
-//   A. each thread takes 8 rows strided by the workgroup size (coalesced)
+// bitvector (written by the previous level). Per chunk of kPullChunk rows:
+//   A. each thread takes rows strided by the workgroup size (coalesced)
 //      and tests their first two entries, all loads independent;
-//   B. the rows still open are listed in LDS and scanned by one wave each,
-//      256 entries per step, stopping at the first hit;
-//   C. each thread labels and appends its 8 consecutive rows' hits.
+//   B. the rows still open are listed in LDS and scanned by kPullLanes lanes
+//      each, four entries per lane and step, stopping at the first hit;
+//   C. threads label and append 8 consecutive rows' hits each.
 // Rows of visited vertices are not read.
+//
+// Bound by the chain level, row_ptr, col_idx, bitvector: 16 and 11 us for the
+// two pulled levels of a search of the R-MAT graph of 2^20 vertices (16 edges
+// each), 22 and 18 us with 256 threads to 2048 rows, a branch around each
+// vertex's loads and a wave per open row.
+constexpr int kPullChunk = 4096;
+constexpr int kPullLanes = 16;
 __device__ __forceinline__ bool in_bits(const uint32_t* __restrict__ bits, int32_t c) {
     return (bits[c >> 5] >> (c & 31)) & 1u;
 }
 
-__global__ __launch_bounds__(kBlock) void k_bfs_pull(int32_t n, const int32_t* __restrict__ row_ptr,
+__global__ __launch_bounds__(kWideBlock) void k_bfs_pull(int32_t n, const int32_t* __restrict__ row_ptr,
                                                      const int32_t* __restrict__ col_idx,
                                                      const uint32_t* __restrict__ bits, int32_t L,
                                                      const int32_t* __restrict__ col_ptr,
                                                      int32_t* __restrict__ level, int32_t* __restrict__ next,
                                                      uint32_t* __restrict__ next_bits, Counters c) {
-    __shared__ uint8_t hit[kChunk];
+    constexpr int kPer = kPullChunk / kWideBlock;
+    __shared__ alignas(8) uint8_t hit[kPullChunk];
     if (blockIdx.x == 0 && threadIdx.x == 0) *c.clear = 0;
-    __shared__ int16_t open[kChunk];
+    __shared__ int16_t open[kPullChunk];
     __shared__ int n_open;
-    __shared__ Count tmp[kWavesPerBlock];
-    for (int64_t base = (int64_t)blockIdx.x * kChunk; base < n; base += (int64_t)gridDim.x * kChunk) {
+    __shared__ Count tmp[kWideBlock / kWave];
+    for (int64_t base = (int64_t)blockIdx.x * kPullChunk; base < n; base += (int64_t)gridDim.x * kPullChunk) {
         if (threadIdx.x == 0) n_open = 0;
         __syncthreads();
-        // A
-        int32_t k0[kVpt], k1[kVpt];
+        // A: no branch around a load, so that each step's are in flight together
+        int32_t lv[kPer], k0[kPer], k1[kPer], c0[kPer], c1[kPer];
 #pragma unroll
-        for (int j = 0; j < kVpt; ++j) {
-            const int64_t r = base + j * kBlock + threadIdx.x;
-            k0[j] = k1[j] = 0;
-            if (r < n && level[r] < 0) {
-                k0[j] = row_ptr[r];
-                k1[j] = row_ptr[r + 1];
-            }
-        }
-        int32_t c0[kVpt], c1[kVpt];
-#pragma unroll
-        for (int j = 0; j < kVpt; ++j) {
-            c0[j] = k1[j] > k0[j] ? col_idx[k0[j]] : -1;
-            c1[j] = k1[j] > k0[j] + 1 ? col_idx[k0[j] + 1] : -1;
+        for (int j = 0; j < kPer; ++j) {
+            const int64_t r = base + j * kWideBlock + threadIdx.x;
+            lv[j] = r < n ? level[r] : 0;
         }
 #pragma unroll
-        for (int j = 0; j < kVpt; ++j) {
-            const bool h = (c0[j] >= 0 && in_bits(bits, c0[j])) || (c1[j] >= 0 && in_bits(bits, c1[j]));
-            const int p = j * kBlock + threadIdx.x;
+        for (int j = 0; j < kPer; ++j) {
+            const int64_t r = lv[j] < 0 ? base + j * kWideBlock + threadIdx.x : 0;
+            k0[j] = row_ptr[r];
+            k1[j] = row_ptr[r + 1];
+        }
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            if (lv[j] >= 0) k1[j] = k0[j];
+            c0[j] = col_idx[k1[j] > k0[j] ? k0[j] : 0];  // a level with out-edges to pull: nnz > 0
+            c1[j] = col_idx[k1[j] > k0[j] + 1 ? k0[j] + 1 : 0];
+        }
+        uint32_t w0[kPer], w1[kPer];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            w0[j] = bits[c0[j] >> 5];
+            w1[j] = bits[c1[j] >> 5];
+        }
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const bool h = (k1[j] > k0[j] && ((w0[j] >> (c0[j] & 31)) & 1u)) ||
+                           (k1[j] > k0[j] + 1 && ((w1[j] >> (c1[j] & 31)) & 1u));
+            const int p = j * kWideBlock + threadIdx.x;
             hit[p] = h;
             if (!h && k1[j] > k0[j] + 2) open[atomicAdd(&n_open, 1)] = (int16_t)p;
         }
         __syncthreads();
         // B
-        const int no = n_open, lane = lane_id();
-        for (int q = wave_id(); q < no; q += kWavesPerBlock) {
+        const int no = n_open, lane = threadIdx.x % kPullLanes;
+        for (int q = threadIdx.x / kPullLanes; q < no; q += kWideBlock / kPullLanes) {
             const int p = open[q];
             const int64_t r = base + p;
             const int32_t e = row_ptr[r + 1];
             bool found = false;
-            for (int32_t kb = row_ptr[r] + 2; kb < e && !found; kb += 4 * kWave) {
+            for (int32_t kb = row_ptr[r] + 2; kb < e && !found; kb += 4 * kPullLanes) {
                 bool h = false;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int32_t k = kb + u * kWave + lane;
-                    h |= k < e && in_bits(bits, col_idx[k]);
+                    const int32_t k = kb + u * kPullLanes + lane;
+                    h |= k < e && in_bits(bits, col_idx[min(k, e - 1)]);
                 }
-                found = __ballot(h) != 0;
+                found = (__ballot(h) >> (lane_id() - lane)) & ((1ull << kPullLanes) - 1ull);
             }
             if (found && lane == 0) hit[p] = 1;
         }
@@ -151,17 +186,19 @@ __global__ __launch_bounds__(kBlock) void k_bfs_pull(int32_t n, const int32_t* _
         // C
         const int64_t v0 = base + (int64_t)threadIdx.x * kVpt;
         uint32_t mask = 0, deg = 0;
+        if (threadIdx.x < kPullChunk / kVpt) {
+            const uint64_t h = *(const uint64_t*)(hit + threadIdx.x * kVpt);
 #pragma unroll
-        for (int j = 0; j < kVpt; ++j) {
-            if (hit[threadIdx.x * kVpt + j]) {
-                const int64_t v = v0 + j;
-                level[v] = L;
-                mask |= 1u << j;
-                deg += (uint32_t)(col_ptr[v + 1] - col_ptr[v]);
+            for (int j = 0; j < kVpt; ++j) {
+                if ((h >> (8 * j)) & 1u) {
+                    level[v0 + j] = L;
+                    mask |= 1u << j;
+                }
             }
+            if (mask) deg = degrees(mask, v0, n, col_ptr);
         }
-        write_bits(mask, v0, n, next_bits);
-        block_append<kBlock>(mask, v0, deg, next, c.count, tmp);
+        write_bits(mask, threadIdx.x < kPullChunk / kVpt ? v0 : n, n, next_bits);
+        block_append<kWideBlock>(mask, v0, deg, next, c.count, tmp);
     }
     publish_count(c);
 }
@@ -187,8 +224,8 @@ spx_status launch_bfs_update(int32_t n, const uint8_t* y, int32_t L, const int32
 spx_status launch_bfs_pull(int32_t n, const int32_t* row_ptr, const int32_t* col_idx, const uint32_t* bits,
                            int32_t L, const int32_t* col_ptr, int32_t* level, int32_t* next, uint32_t* next_bits,
                            void* count, void* host, hipStream_t s) {
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, kChunk), 2048));
-    k_bfs_pull<<<grid, kBlock, 0, s>>>(n, row_ptr, col_idx, bits, L, col_ptr, level, next, next_bits,
+    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, kPullChunk), 2048));
+    k_bfs_pull<<<grid, kWideBlock, 0, s>>>(n, row_ptr, col_idx, bits, L, col_ptr, level, next, next_bits,
                                        counters_of(count, L, host));
     SPX_HIP(hipGetLastError());
     return SPX_OK;

@@ -1,5 +1,5 @@
 // Frontier appends shared by the graph drivers (breadth-first search and
-// PageRank): a workgroup owns kChunk consecutive vertices, 8 per thread,
+// PageRank): a workgroup owns consecutive vertices, 8 per thread,
 // and appends the ones it selects to an output list with one atomic on a
 // packed counter.
 #pragma once
@@ -58,7 +58,6 @@ __device__ __forceinline__ void publish_count(const Counters& c) {
 // kernels therefore run 1024-thread workgroups (kWideBlock), the same
 // threads in a quarter of the atomics.
 constexpr int kVpt = 8;
-constexpr int kChunk = kBlock * kVpt;
 constexpr int kWideBlock = 1024;
 constexpr int kWideChunk = kWideBlock * kVpt;
 
@@ -80,6 +79,51 @@ __device__ __forceinline__ T block_scan_nt(T v, T* tmp, T* total) {
     __syncthreads();
     *total = tot;
     return w + pre;
+}
+
+// N consecutive values from v0, as 16-byte loads and stores of 4-byte aligned
+// words (which is what a global access of that width needs); element by
+// element at the tail.
+struct __attribute__((packed, aligned(4))) Words4 {
+    uint32_t w[4];
+};
+
+template <int N, typename T>
+__device__ __forceinline__ void load_run(const T* __restrict__ a, int64_t v0, int64_t n, T (&o)[N]) {
+    if (v0 + N <= n) {
+        static_assert(N * sizeof(T) % 16 == 0);
+        Words4 w[N * sizeof(T) / 16];
+#pragma unroll
+        for (int u = 0; u < (int)(N * sizeof(T) / 16); ++u) w[u] = ((const Words4*)(a + v0))[u];
+        __builtin_memcpy(o, w, sizeof(o));
+    } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j) o[j] = v0 + j < n ? a[v0 + j] : (T)0;
+    }
+}
+
+template <int N, typename T>
+__device__ __forceinline__ void store_run(T* __restrict__ a, int64_t v0, int64_t n, const T (&o)[N]) {
+    if (v0 + N <= n) {
+        Words4 w[N * sizeof(T) / 16];
+        __builtin_memcpy(w, o, sizeof(o));
+#pragma unroll
+        for (int u = 0; u < (int)(N * sizeof(T) / 16); ++u) ((Words4*)(a + v0))[u] = w[u];
+    } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (v0 + j < n) a[v0 + j] = o[j];
+    }
+}
+
+// The workgroup's share of the counter without a list: {popcount of mask,
+// high} summed, one atomic whose result nothing waits for. Contains
+// __syncthreads; tmp: NT / 64 words of LDS.
+template <int NT>
+__device__ __forceinline__ void block_count(uint32_t mask, uint32_t high, Count* __restrict__ count, Count* tmp) {
+    Count total;
+    block_scan_nt<NT, Count>(((Count)high << 32) | (Count)__popc(mask), tmp, &total);
+    if (threadIdx.x == 0 && total) atomicAdd(count, total);
 }
 
 // Thread t holds the candidates v0 + j for the set bits j of mask, and

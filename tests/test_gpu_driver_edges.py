@@ -1,0 +1,52 @@
+"""The graph drivers' kernels at the edges of their tiles (8 vertices per
+thread, 32 per bitvector word, 4096 rows per workgroup of the pull), and rows
+that the pull has to scan past its first entries, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2006_16767_amd as spx
+from paper_2006_16767_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _graph(n, seed):
+    """Random edges, and vertices 1 and n - 2 with edges from every third
+    vertex and from a late one only, so that a pull meets long rows with and
+    without an early hit."""
+    rng = np.random.default_rng(seed)
+    e = 4 * n
+    src, dst = rng.integers(0, n, e), rng.integers(0, max(1, n - 5), e)
+    src = np.concatenate([src, np.arange(0, n, 3), np.arange(n // 2, n)])
+    dst = np.concatenate([dst, np.full(len(range(0, n, 3)), min(1, n - 1)), np.full(n - n // 2, max(0, n - 2))])
+    key = np.unique(dst.astype(np.int64) * n + src)
+    return synth._coo_to_csr(n, n, key // n, key % n, None)
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 33, 4095, 4096, 4097, 8200, 20001])
+def test_bfs_tile_edges(n):
+    torch = _torch()
+    A = _graph(n, n)
+    M = spx.Matrix.from_host(A, dtype=spx.BOOL)
+    s = int(A.col_idx[0])
+    dst = np.repeat(np.arange(n), np.diff(A.row_ptr)).astype(np.int32)
+    want = oracle.bfs_levels(A.col_idx, dst, n, s)
+    for push_only in (False, True):
+        level, _ = M.bfs(s, push_only=push_only)
+        assert np.array_equal(level.cpu().numpy(), want), f"n={n} push_only={push_only}"
+    # levels at an address that is only 4-byte aligned
+    import ctypes as C
+    from paper_2006_16767_amd import _lib
+    buf = torch.full((n + 1,), 77, dtype=torch.int32, device="cuda")
+    nl = C.c_int32(0)
+    _lib.call("spx_bfs", M._h, s, C.c_void_p(buf.data_ptr() + 4), 1 << 30, None, 0, C.byref(nl), None, 0, None)
+    torch.cuda.synchronize()
+    assert np.array_equal(buf[1:].cpu().numpy(), want) and int(buf[0]) == 77
