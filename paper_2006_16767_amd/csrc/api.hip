@@ -1756,8 +1756,9 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
     a.stage = PR_INIT;
     SPX_TRY(launch_pagerank(a, s));
     SPX_TRY(fill_u32((uint32_t*)H->drv_count, 0u, 64, s));
-    auto enqueue_select = [&](int32_t round) -> spx_status {
+    auto enqueue_select = [&](int32_t round, bool list) -> spx_status {
         a.stage = PR_SELECT;
+        a.list = list;
         a.round = round;
         a.y = round ? H->pr_y : nullptr;
         a.host = open_driver_count(H, round);
@@ -1781,7 +1782,7 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
     bool spec = false;     // this round's product was queued before its count was read
     spx_plan spec_plan{};
     for (int32_t round = 0; it < max_iters;) {
-        if (round == 0) SPX_TRY(enqueue_select(0));
+        if (round == 0) SPX_TRY(enqueue_select(0, true));
         int32_t nx = 0;
         int64_t ns = 0;  // column lengths of supp(x)
         SPX_TRY(read_driver_count(H, round, s, &nx, &ns));
@@ -1805,17 +1806,14 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
         pending = true;
         if (it >= max_iters) break;
         ++round;
-        SPX_TRY(enqueue_select(round));
-        spec = false;
-        if (p.pattern != SPX_PAT_CSC_SPMSPV) {
-            spx_plan q{};
-            SPX_TRY(choose(nx, ns, &q));
-            if (q.pattern != SPX_PAT_CSC_SPMSPV) {
-                spx_vec xd_only{SPX_VEC_SPARSE, A.n, 0, H->pr_xidx, H->pr_xval};
-                SPX_TRY(exec_prepared(H, &xd_only, H->pr_xd[round & 1], H->pr_y, &q, -1, s));
-                spec = true;
-                spec_plan = q;
-            }
+        spx_plan q{};
+        if (p.pattern != SPX_PAT_CSC_SPMSPV) SPX_TRY(choose(nx, ns, &q));
+        spec = p.pattern != SPX_PAT_CSC_SPMSPV && q.pattern != SPX_PAT_CSC_SPMSPV;
+        SPX_TRY(enqueue_select(round, !spec));  // a row-major product reads no list
+        if (spec) {
+            spx_vec xd_only{SPX_VEC_SPARSE, A.n, 0, H->pr_xidx, H->pr_xval};
+            SPX_TRY(exec_prepared(H, &xd_only, H->pr_xd[round & 1], H->pr_y, &q, -1, s));
+            spec_plan = q;
         }
     }
     if (pending) {

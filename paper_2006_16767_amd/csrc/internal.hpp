@@ -300,9 +300,10 @@ struct PrArgs {
     void* r = nullptr;                 // residual
     void* p = nullptr;                 // rank
     const void* y = nullptr;           // last product (nullptr on round 0)
+    bool list = true;                  // SELECT: write the list
     int32_t* x_idx = nullptr;          // next product's input: list,
     void* x_val = nullptr;
-    void* xd[2] = {nullptr, nullptr};  // dense (alternating, 16-byte aligned),
+    void* xd[2] = {nullptr, nullptr};  // dense (alternating),
     const int32_t* map = nullptr;      // at map[v] (nullptr: v)
     void* count = nullptr;
     void* host = nullptr;

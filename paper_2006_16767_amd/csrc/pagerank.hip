@@ -9,8 +9,8 @@
 // (k_pr_select) folds the previous product into r (r += d y), moves every
 // active residual (|r_v| > eps) into p_v, clears it, and appends the
 // active vertices with W_v > 0 to the sparse input x_v = r_v / W_v of the
-// next product y = A x, as a list and as a dense vector, so that no
-// conversion runs before a row-major kernel.
+// next product y = A x, as a dense vector, so that no conversion runs before
+// a row-major kernel, and as a list unless that product is row-major.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -51,50 +51,26 @@ __global__ __launch_bounds__(kBlock) void k_pr_init(int32_t n, T r0, T* __restri
     }
 }
 
-// Eight consecutive values from v0 (a multiple of 8; the array 16-byte
-// aligned), as 16-byte loads; element by element at the tail.
-template <typename T>
-__device__ __forceinline__ void load8(const T* __restrict__ a, int64_t v0, int32_t n, T (&o)[kVpt]) {
-    if (v0 + kVpt <= n) {
-        constexpr int nv = kVpt * sizeof(T) / 16;
-        const uint4* q = (const uint4*)(a + v0);
-        uint4 w[nv];
-#pragma unroll
-        for (int u = 0; u < nv; ++u) w[u] = q[u];
-        __builtin_memcpy(o, w, sizeof(o));
-    } else {
-#pragma unroll
-        for (int j = 0; j < kVpt; ++j) o[j] = v0 + j < n ? a[v0 + j] : (T)0;
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ void store8(T* __restrict__ a, int64_t v0, int32_t n, const T (&o)[kVpt]) {
-    if (v0 + kVpt <= n) {
-        constexpr int nv = kVpt * sizeof(T) / 16;
-        uint4 w[nv];
-        __builtin_memcpy(w, o, sizeof(o));
-        uint4* q = (uint4*)(a + v0);
-#pragma unroll
-        for (int u = 0; u < nv; ++u) q[u] = w[u];
-    } else {
-#pragma unroll
-        for (int j = 0; j < kVpt; ++j)
-            if (v0 + j < n) a[v0 + j] = o[j];
-    }
-}
-
 // One round. y = nullptr on the first round (no product yet). The counter
-// gets {appended entries of x (low), their column lengths (high), i.e. the
+// gets {entries of x (low), their column lengths (high), i.e. the
 // nnz_s of the next product}; the other counter is zeroed for the next round.
-// Besides the list (x_idx, x_val), x goes dense into xd_fill at position
-// map[v] (the column order of the row-major copy; v itself when map is
-// null): xd_fill was zeroed by the previous round, and this round zeroes
-// xd_clear for the next one (two buffers alternate, each zeroed while the
-// other is in use). r += d y is rounded as a product and then a sum (no
-// fused multiply-add), the order the definition states. r, p, y, W,
-// col_ptr, map and xd_clear are 16-byte aligned.
-template <typename T>
+// x goes dense into xd_fill at position map[v] (the column order of the
+// row-major copy; v itself when map is null): xd_fill was zeroed by the
+// previous round, and this round zeroes xd_clear for the next one (two buffers
+// alternate, each zeroed while the other is in use). LIST: x also as a list
+// (x_idx, x_val), for a product that may be column-major. r += d y is rounded
+// as a product and then a sum (no fused multiply-add), the order the
+// definition states.
+//
+// Bound by its 42 MB, by the scattered stores of x and by latency (three steps
+// of loads, then the counter): 12.9 us with every one of 2^20 vertices active,
+// 8 to 10 once the frontier thins out. Half the vertices per workgroup and no
+// list in the row-major rounds took a ranking of the R-MAT graph of 2^20
+// vertices (66 rounds) from 4902 to 4856 us.
+constexpr int kSelVpt = 4;
+constexpr int kSelChunk = kWideBlock * kSelVpt;
+
+template <typename T, bool LIST>
 __global__ __launch_bounds__(kWideBlock) void k_pr_select(int32_t n, T d, T eps, const T* __restrict__ y,
                                                       T* __restrict__ r, T* __restrict__ p,
                                                       const T* __restrict__ W, const int32_t* __restrict__ col_ptr,
@@ -104,59 +80,61 @@ __global__ __launch_bounds__(kWideBlock) void k_pr_select(int32_t n, T d, T eps,
 #pragma clang fp contract(off)
     __shared__ Count tmp[kWideBlock / kWave];
     if (blockIdx.x == 0 && threadIdx.x == 0) *c.clear = 0;
-    for (int64_t base = (int64_t)blockIdx.x * kWideChunk; base < n; base += (int64_t)gridDim.x * kWideChunk) {
-        const int64_t v0 = base + (int64_t)threadIdx.x * kVpt;
+    for (int64_t base = (int64_t)blockIdx.x * kSelChunk; base < n; base += (int64_t)gridDim.x * kSelChunk) {
+        const int64_t v0 = base + (int64_t)threadIdx.x * kSelVpt;
         // all loads of a phase are independent, so they are in flight together
-        T rv[kVpt], wv[kVpt], xv[kVpt];
-        load8(r, v0, n, rv);
-        load8(W, v0, n, wv);
+        T rv[kSelVpt], wv[kSelVpt], xv[kSelVpt];
+        load_run(r, v0, n, rv);
+        load_run(W, v0, n, wv);
         if (y) {
-            T yv[kVpt];
-            load8(y, v0, n, yv);
+            T yv[kSelVpt];
+            load_run(y, v0, n, yv);
 #pragma unroll
-            for (int j = 0; j < kVpt; ++j) {
+            for (int j = 0; j < kSelVpt; ++j) {
                 const T dy = d * yv[j];
                 rv[j] = rv[j] + dy;
             }
         }
         uint32_t act = 0;
 #pragma unroll
-        for (int j = 0; j < kVpt; ++j)
+        for (int j = 0; j < kSelVpt; ++j)
             if (v0 + j < n && (rv[j] > eps || rv[j] < -eps)) act |= 1u << j;
         uint32_t mask = 0, ns = 0;
 #pragma unroll
-        for (int j = 0; j < kVpt; ++j) xv[j] = (T)0;
+        for (int j = 0; j < kSelVpt; ++j) xv[j] = (T)0;
         if (act) {
             // the rank, the column pointers and the map of the thread's
             // vertices only when one of them is active
-            T pv[kVpt];
-            int32_t cp[kVpt], mp[kVpt];
-            load8(p, v0, n, pv);
-            load8(col_ptr, v0, n, cp);
-            if (map) load8(map, v0, n, mp);
+            T pv[kSelVpt];
+            int32_t cp[kSelVpt], mp[kSelVpt];
+            load_run(p, v0, n, pv);
+            load_run(col_ptr, v0, (int64_t)n + 1, cp);
+            const int32_t end = v0 + kSelVpt <= n ? col_ptr[v0 + kSelVpt] : 0;
+            if (map) load_run(map, v0, n, mp);
 #pragma unroll
-            for (int j = 0; j < kVpt; ++j) {
+            for (int j = 0; j < kSelVpt; ++j) {
                 if (!((act >> j) & 1u)) continue;
                 pv[j] = pv[j] + rv[j];
                 if (wv[j] > (T)0) {
                     mask |= 1u << j;
                     xv[j] = rv[j] / wv[j];
-                    // end of column v0 + j (col_ptr has n + 1 entries)
-                    const int32_t next = j + 1 < kVpt && v0 + j + 1 < n ? cp[j + 1] : col_ptr[v0 + j + 1];
-                    ns += (uint32_t)(next - cp[j]);
+                    ns += (uint32_t)((j + 1 < kSelVpt ? cp[j + 1] : end) - cp[j]);
                     xd_fill[map ? mp[j] : v0 + j] = xv[j];
                 }
                 rv[j] = (T)0;
             }
-            store8(p, v0, n, pv);
+            store_run(p, v0, n, pv);
         }
-        if (y || act) store8(r, v0, n, rv);
-        const T zero[kVpt] = {};
-        store8(xd_clear, v0, n, zero);
-        block_append<kWideBlock>(mask, ns, c.count, tmp, [&](uint32_t slot, int j) {
-            x_idx[slot] = (int32_t)(v0 + j);
-            x_val[slot] = xv[j];
-        });
+        if (y || act) store_run(r, v0, n, rv);
+        const T zero[kSelVpt] = {};
+        store_run(xd_clear, v0, n, zero);
+        if constexpr (LIST)
+            block_append<kWideBlock>(mask, ns, c.count, tmp, [&](uint32_t slot, int j) {
+                x_idx[slot] = (int32_t)(v0 + j);
+                x_val[slot] = xv[j];
+            });
+        else
+            block_count<kWideBlock>(mask, ns, c.count, tmp);
     }
     publish_count(c);
 }
@@ -191,11 +169,12 @@ static spx_status pr_t(const PrArgs& a, hipStream_t s) {
                                                            (T*)a.xd[0]);
             break;
         case PR_SELECT: {
-            const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(a.n, kWideChunk), 2048));
-            k_pr_select<T><<<grid, kWideBlock, 0, s>>>(a.n, (T)a.damping, (T)a.eps, (const T*)a.y, (T*)a.r, (T*)a.p,
-                                                   (const T*)a.W, a.col_ptr, a.map, a.x_idx, (T*)a.x_val,
-                                                   (T*)a.xd[a.round & 1], (T*)a.xd[(a.round + 1) & 1],
-                                                   counters_of(a.count, a.round, a.host));
+            const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(a.n, kSelChunk), 2048));
+            const auto kernel = a.list ? k_pr_select<T, true> : k_pr_select<T, false>;
+            kernel<<<grid, kWideBlock, 0, s>>>(a.n, (T)a.damping, (T)a.eps, (const T*)a.y, (T*)a.r, (T*)a.p,
+                                               (const T*)a.W, a.col_ptr, a.map, a.x_idx, (T*)a.x_val,
+                                               (T*)a.xd[a.round & 1], (T*)a.xd[(a.round + 1) & 1],
+                                               counters_of(a.count, a.round, a.host));
             break;
         }
         case PR_FOLD:
