@@ -723,19 +723,34 @@ __global__ __launch_bounds__(kBlock) void k_batch_fused(BatchDev a) {
 // The vectors of no group, by blocks of rows: a workgroup holds kRowsBytes of
 // one vector's Y in LDS, adds the products of the selected columns' entries in
 // those rows to it there, and stores it. A column's entries ascend by row, so a
-// block's are one segment, found in a table (build_segs). A thread reads one
-// segment's bounds; then four lanes take a segment, and a wave a long one. The
-// blocks of one vector follow each other on one XCD: they read neighbouring
-// segments, in the same cache lines.
+// block's are one segment, found in a table (k_segs). A thread reads one
+// segment's bounds; then the wave takes its 64 segments as one run of entries,
+// 64 at a step. The blocks of one vector follow each other on one XCD: they
+// read neighbouring segments, in the same cache lines.
 //
-// Bound by the chain from index to segment to entries, and by Y: 219 us for
-// the 295 vectors below a density of 2 % on R-MAT 2^18 (4.7M segments, 310 MB
-// of Y; 252 us with 512 threads, 232 with 128 KB of Y each). Atomics into Y
-// took 760 us, and 54 us for zeroing Y before: the chip does 21 G scattered
-// atomics/s, from one XCD or all.
+// Bound by the chain from index to segment to entries, by its cache lines
+// (three per segment, 14M) and by Y: 190 us for the 295 vectors below a density
+// of 2 % on R-MAT 2^18 (4.7M segments of 1.8 entries on average, of 13 in the
+// first block; 310 MB of Y). 55 of it is zeroing and storing Y; 16 are adds to
+// one row by several lanes. Four lanes to a segment and a wave to a long one
+// took 219 us (where all segments are short it is 5 % faster), 512 threads
+// 252; 128 KB of Y per workgroup 182. Atomics into Y took 760 us, and 54 us
+// for zeroing Y before: the chip does 21 G scattered atomics/s, from one XCD or
+// all.
 constexpr int kRowsBytes = 65536;
 constexpr int kRowsThreads = 1024;
-constexpr int kLongSegment = 64;
+constexpr int kRowsSteps = 4;
+
+// Lane dst / 4 gets the value (ds_permute moves words).
+template <typename T>
+__device__ __forceinline__ T permute_to(int dst, T v) {
+    uint32_t w[sizeof(T) / 4];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)w[i]);
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
 
 template <int DT>
 __global__ __launch_bounds__(kRowsThreads) void k_batch_rows(BatchDev a, int32_t b0) {
@@ -743,6 +758,7 @@ __global__ __launch_bounds__(kRowsThreads) void k_batch_rows(BatchDev a, int32_t
         using S = SR<DT>;
         using Acc = typename S::Acc;
         extern __shared__ __align__(16) char s_raw[];
+        __shared__ unsigned long long s_starts[kRowsThreads / kWave][kRowsSteps];
         Acc* y = (Acc*)s_raw;
         constexpr int R = kRowsBytes / (int)sizeof(Acc);
         const int i = blockIdx.x / 8;
@@ -755,7 +771,8 @@ __global__ __launch_bounds__(kRowsThreads) void k_batch_rows(BatchDev a, int32_t
         const int32_t* __restrict__ idx = a.idx + p.base;
         const auto* __restrict__ xv = (const typename S::X*)a.val + p.base;
         const auto* __restrict__ vals = (const typename S::V*)a.vals_csc;
-        const int r0 = blk * R, last = a.nnz - 1, l4 = lane_id() & 3;
+        const int r0 = blk * R, lane = lane_id();
+        unsigned long long* starts = s_starts[wave_id()];
         for (int c0 = 0; c0 < p.nnz_x; c0 += kRowsThreads) {
             const int e = c0 + threadIdx.x;
             int k0 = 0, len = 0;
@@ -766,38 +783,51 @@ __global__ __launch_bounds__(kRowsThreads) void k_batch_rows(BatchDev a, int32_t
                 len = t[1] - k0;
                 x = xv[e];
             }
-            uint64_t longs = __ballot(len > kLongSegment);
-            while (longs) {
-                const int q = __ffsll((unsigned long long)longs) - 1;
-                longs &= longs - 1;
-                const int kq = lane_value(k0, q), lq = lane_value(len, q);
-                const auto xq = lane_value(x, q);
-                for (int k = lane_id(); k < lq; k += kWave)
-                    S::lds_atomic_add(&y[a.row_idx[kq + k] - r0], S::mul(vals[kq + k], xq));
+            // the wave's segments end to end: position p of the run belongs to
+            // the last non-empty segment that starts at or before it, found
+            // as a rank in the bits of the starts (kRowsSteps words of 64
+            // positions at a time); first, the non-empty segments side by side
+            const uint64_t some = __ballot(len > 0);
+            const int at = __popcll(some & ((1ull << lane) - 1ull));
+            const int incl = wave_incl_scan(len);
+            const int total = __shfl(incl, kWave - 1, kWave);
+            const int dst = (len > 0 ? at : kWave - 1) * 4;
+            int start = incl - len, shift = k0 - start;  // entry = position + shift
+            if (__popcll(some) < kWave) {  // else they are
+                const int n0 = __popcll(some);
+                start = __builtin_amdgcn_ds_permute(dst, start);
+                shift = __builtin_amdgcn_ds_permute(dst, shift);
+                x = permute_to(dst, x);
+                if (lane >= n0) start = total;
             }
-            if (len > kLongSegment) len = 0;
-            int ks[4], ls[4], row[4];
-            typename S::X xs[4];
-            typename S::V v[4];
-            int most = 0;
+            int before = 0;
+            for (int p0 = 0; p0 < total; p0 += kRowsSteps * kWave) {
+                if (lane < kRowsSteps) starts[lane] = 0;
+                __builtin_amdgcn_wave_barrier();
+                const int o = start - p0;
+                if (o >= 0 && o < kRowsSteps * kWave && start < total)
+                    atomicOr(&starts[o / kWave], 1ull << (o % kWave));
+                __builtin_amdgcn_wave_barrier();
+                int row[kRowsSteps], k[kRowsSteps];
+                typename S::X xs[kRowsSteps];
+                typename S::V v[kRowsSteps];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int from = (lane_id() & 60) | t;
-                ks[t] = __shfl(k0, from, kWave) + l4;
-                ls[t] = __shfl(len, from, kWave) - l4;
-                xs[t] = __shfl(x, from, kWave);
-                most = max(most, ls[t]);
-            }
-            for (int d = 0; __any(d < most); d += 4) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int k = min(ks[t] + d, last);
-                    row[t] = d < ls[t] ? a.row_idx[k] : r0;
-                    v[t] = d < ls[t] ? vals[k] : (typename S::V)0;
+                for (int t = 0; t < kRowsSteps; ++t) {
+                    const uint64_t w = starts[t];
+                    const int rank = before + __popcll(w & (~0ull >> (kWave - 1 - lane))) - 1;
+                    before += __popcll(w);
+                    const int p = p0 + t * kWave + lane;
+                    k[t] = min(p, total - 1) + __shfl(shift, rank, kWave);
+                    xs[t] = __shfl(x, rank, kWave);
                 }
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    if (d < ls[t]) S::lds_atomic_add(&y[row[t] - r0], S::mul(v[t], xs[t]));
+                for (int t = 0; t < kRowsSteps; ++t) {
+                    row[t] = a.row_idx[k[t]];
+                    v[t] = vals[k[t]];
+                }
+#pragma unroll
+                for (int t = 0; t < kRowsSteps; ++t)
+                    if (p0 + t * kWave + lane < total) S::lds_atomic_add(&y[row[t] - r0], S::mul(v[t], xs[t]));
             }
         }
         __syncthreads();
@@ -940,8 +970,8 @@ __global__ __launch_bounds__(kBlock) void k_batch_phase(BatchDev a) {
 // ------------------------------------------------------------------ host side
 // Blocks of rows of a column-major vector's Y, or 0 where its products go to Y
 // with atomics. By blocks is faster down to an entry in eight segments (128
-// vectors of density 1 % on 2^18 x 2^18, float32: 72 against 134 us with 2
-// entries per row, 85 against 246 with 8, 122 against 623 with 32; density
+// vectors of density 1 % on 2^18 x 2^18, float32: 77 against 134 us with 2
+// entries per row, 89 against 246 with 8, 129 against 623 with 32; density
 // 0.05 %: 42 against 95 us); beyond that the table of segments is more than
 // four times A.
 int32_t batch_row_blocks(int32_t m, int32_t n, int64_t nnz, int dtype) {
