@@ -1272,7 +1272,8 @@ static spx_status run_counts(spx_matrix* H, const spx_vec* x, void* y, int64_t n
 // whose value is exactly 0 and contribute nothing), the column-major ones
 // read the list.
 static spx_status exec_prepared(spx_matrix* H, const spx_vec* x, const void* xd, void* y, const spx_plan* p,
-                                int64_t nnz_s, hipStream_t s) {
+                                int64_t nnz_s, hipStream_t s, Carries* keep) {
+    *keep = Carries{};
     if (p->pattern == SPX_PAT_CSC_SPMSPV) return exec_plan(H, x, y, p, nnz_s, x->nnz_x, s);
     const spx_csr& A = H->gorder ? H->gcsr : H->csr;
     const int dt = A.dtype;
@@ -1310,7 +1311,7 @@ static spx_status exec_prepared(spx_matrix* H, const spx_vec* x, const void* xd,
         H->bits_clean = true;
     } else
         SPX_TRY(launch_spmv_csr(&A, xd, bits, y, p, part, ws, s, nullptr, nullptr,
-                                H->gorder && H->ts.pk ? &H->ts : nullptr));
+                                H->gorder && H->ts.pk ? &H->ts : nullptr, keep));
     record(H, H->ev_kern, false, s);
     return SPX_OK;
 }
@@ -1799,7 +1800,7 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
             if (nx == 0) break;
             SPX_TRY(choose(nx, ns, &p));
             spx_vec x{SPX_VEC_SPARSE, A.n, nx, H->pr_xidx, H->pr_xval};
-            SPX_TRY(exec_prepared(H, &x, H->pr_xd[round & 1], H->pr_y, &p, ns, s));
+            SPX_TRY(exec_prepared(H, &x, H->pr_xd[round & 1], H->pr_y, &p, ns, s, &a.carries));
         }
         if (it < plans_cap) plans[it] = p;
         ++it;
@@ -1812,11 +1813,12 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
         SPX_TRY(enqueue_select(round, !spec));  // a row-major product reads no list
         if (spec) {
             spx_vec xd_only{SPX_VEC_SPARSE, A.n, 0, H->pr_xidx, H->pr_xval};
-            SPX_TRY(exec_prepared(H, &xd_only, H->pr_xd[round & 1], H->pr_y, &q, -1, s));
+            SPX_TRY(exec_prepared(H, &xd_only, H->pr_xd[round & 1], H->pr_y, &q, -1, s, &a.carries));
             spec_plan = q;
         }
     }
     if (pending) {
+        SPX_TRY(launch_csr_fixup(a.carries, A.dtype, H->pr_y, s));
         a.stage = PR_FOLD;
         a.y = H->pr_y;
         SPX_TRY(launch_pagerank(a, s));

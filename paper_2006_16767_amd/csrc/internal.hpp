@@ -98,6 +98,19 @@ struct Unscatter {
     int32_t n = 0;  // length of x: past n / 16 entries the whole buffers are cleared with coalesced stores
 };
 
+// The carries of a balanced row-major product: tile t's last row, if it goes
+// on in the next tile (-1 otherwise), and its sum there. A launch that is given
+// one leaves the fix-up to the caller, who adds them (tiles = 0: nothing to
+// add). part: the tiles' bounds, 2 * t + 2 the row of tile t's end; the rest
+// lies in the launch's workspace.
+struct Carries {
+    int32_t tiles = 0;
+    const int32_t* part = nullptr;
+    const int32_t* row = nullptr;
+    const void* val = nullptr;
+};
+spx_status launch_csr_fixup(const Carries& c, int dtype, void* y, hipStream_t s);  // F32 or F64
+
 // Column-sorted copy of a CSR for the balanced SpMV with 2048-item merge
 // tiles (csr_tile.hpp: inside each tile the entries ordered by column, each
 // word = column | position in the tile << 21; needs n <= 2^21).
@@ -117,7 +130,7 @@ struct TileSorted {
 spx_status launch_spmv_csr(const spx_csr* A, const void* x, const uint32_t* bits, void* y,
                            const spx_plan* plan, const int32_t* part, Arena& ws, hipStream_t s,
                            const Unscatter* un = nullptr, bool* cleared = nullptr,
-                           const TileSorted* ts = nullptr);
+                           const TileSorted* ts = nullptr, Carries* keep = nullptr);
 // Builds ts for A (the partition of 2048-item tiles given); returns
 // SPX_ERR_UNSUPPORTED when n > 2^21. Synchronizes the stream.
 spx_status tile_sorted_build(const spx_csr& A, const int32_t* part, const int32_t* src_of_A, TileSorted* ts,
@@ -299,7 +312,8 @@ struct PrArgs {
     void* W = nullptr;                 // column sums
     void* r = nullptr;                 // residual
     void* p = nullptr;                 // rank
-    const void* y = nullptr;           // last product (nullptr on round 0)
+    const void* y = nullptr;           // last product (nullptr on round 0),
+    Carries carries;                   // and what it still lacks
     bool list = true;                  // SELECT: write the list
     int32_t* x_idx = nullptr;          // next product's input: list,
     void* x_val = nullptr;

@@ -70,8 +70,24 @@ __global__ __launch_bounds__(kBlock) void k_pr_init(int32_t n, T r0, T* __restri
 constexpr int kSelVpt = 4;
 constexpr int kSelChunk = kWideBlock * kSelVpt;
 
+// The first tile whose last row is row or a later one. Every lane of the wave
+// must call it with the same row.
+__device__ __forceinline__ int first_tile_from(const Carries& c, int64_t row) {
+    int lo = 0, hi = c.tiles;
+    while (lo < hi) {
+        const int step = (hi - lo + kWave - 1) / kWave;
+        const int t = lo + lane_id() * step;
+        const uint64_t at = __ballot(t >= hi || c.part[2 * t + 2] >= row);
+        const int f = at ? __ffsll((unsigned long long)at) - 1 : kWave;
+        hi = min(hi, lo + f * step);
+        lo = f > 0 ? lo + (f - 1) * step + 1 : lo;
+    }
+    return lo;
+}
+
 template <typename T, bool LIST>
 __global__ __launch_bounds__(kWideBlock) void k_pr_select(int32_t n, T d, T eps, const T* __restrict__ y,
+                                                      Carries carries,
                                                       T* __restrict__ r, T* __restrict__ p,
                                                       const T* __restrict__ W, const int32_t* __restrict__ col_ptr,
                                                       const int32_t* __restrict__ map, int32_t* __restrict__ x_idx,
@@ -79,6 +95,8 @@ __global__ __launch_bounds__(kWideBlock) void k_pr_select(int32_t n, T d, T eps,
                                                       T* __restrict__ xd_clear, Counters c) {
 #pragma clang fp contract(off)
     __shared__ Count tmp[kWideBlock / kWave];
+    __shared__ T s_add[kSelChunk];
+    __shared__ int s_tile[2];
     if (blockIdx.x == 0 && threadIdx.x == 0) *c.clear = 0;
     for (int64_t base = (int64_t)blockIdx.x * kSelChunk; base < n; base += (int64_t)gridDim.x * kSelChunk) {
         const int64_t v0 = base + (int64_t)threadIdx.x * kSelVpt;
@@ -89,6 +107,28 @@ __global__ __launch_bounds__(kWideBlock) void k_pr_select(int32_t n, T d, T eps,
         if (y) {
             T yv[kSelVpt];
             load_run(y, v0, n, yv);
+            if (carries.tiles) {
+                // what rows of the chunk that span tiles still lack, added in
+                // tile order by the thread of a row's first tile
+                if (wave_id() < 2) {
+                    const int t = first_tile_from(carries, base + wave_id() * kSelChunk);
+                    if (lane_id() == 0) s_tile[wave_id()] = t;
+                }
+#pragma unroll
+                for (int j = 0; j < kSelVpt; ++j) s_add[threadIdx.x * kSelVpt + j] = (T)0;
+                __syncthreads();
+                for (int t = s_tile[0] + (int)threadIdx.x; t < s_tile[1]; t += kWideBlock) {
+                    const int row = carries.row[t];
+                    if (row < 0 || (t > 0 && carries.row[t - 1] == row)) continue;
+                    T sum = (T)0;
+                    for (int u = t; u < carries.tiles && carries.row[u] == row; ++u)
+                        sum = sum + ((const T*)carries.val)[u];
+                    s_add[row - base] = sum;
+                }
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < kSelVpt; ++j) yv[j] = yv[j] + s_add[threadIdx.x * kSelVpt + j];
+            }
 #pragma unroll
             for (int j = 0; j < kSelVpt; ++j) {
                 const T dy = d * yv[j];
@@ -171,7 +211,7 @@ static spx_status pr_t(const PrArgs& a, hipStream_t s) {
         case PR_SELECT: {
             const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(a.n, kSelChunk), 2048));
             const auto kernel = a.list ? k_pr_select<T, true> : k_pr_select<T, false>;
-            kernel<<<grid, kWideBlock, 0, s>>>(a.n, (T)a.damping, (T)a.eps, (const T*)a.y, (T*)a.r, (T*)a.p,
+            kernel<<<grid, kWideBlock, 0, s>>>(a.n, (T)a.damping, (T)a.eps, (const T*)a.y, a.carries, (T*)a.r, (T*)a.p,
                                                (const T*)a.W, a.col_ptr, a.map, a.x_idx, (T*)a.x_val,
                                                (T*)a.xd[a.round & 1], (T*)a.xd[(a.round + 1) & 1],
                                                counters_of(a.count, a.round, a.host));

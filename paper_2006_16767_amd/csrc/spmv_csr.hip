@@ -243,7 +243,7 @@ spx_status merge_partition(int32_t m, int32_t nnz, const int32_t* row_ptr, int t
 template <int DT, bool VALID>
 static spx_status launch_csr_t(const spx_csr* A, const void* x, const uint32_t* bits, void* y,
                                const spx_plan* plan, const int32_t* part, Arena& ws, hipStream_t s,
-                               const Unscatter* un, bool* cleared, const TileSorted* ts) {
+                               const Unscatter* un, bool* cleared, const TileSorted* ts, Carries* keep) {
     using S = SR<DT>;
     const auto* vals = (const typename S::V*)A->vals;
     const auto* xv = (const typename S::X*)x;
@@ -303,6 +303,10 @@ static spx_status launch_csr_t(const spx_csr* A, const void* x, const uint32_t* 
             k_csr_merge<DT, VALID, 2048><<<(unsigned)tiles, kBlock, 0, s>>>(A->m, A->row_ptr, A->col_idx, vals, xv,
                                                                            bits, yv, part, tiles, crow, cval);
         SPX_HIP(hipGetLastError());
+        if (keep && !un) {
+            *keep = Carries{(int32_t)tiles, part, crow, cval};
+            return SPX_OK;
+        }
         const Unscatter u = un ? *un : Unscatter{};
         const int64_t work = std::max<int64_t>(tiles, (int64_t)u.nnz_x * 16 > u.n ? u.n : u.nnz_x);
         k_csr_merge_fixup<DT><<<(unsigned)std::min<int64_t>(ceil_div(work, kBlock), 8192), kBlock, 0, s>>>(
@@ -316,14 +320,14 @@ static spx_status launch_csr_t(const spx_csr* A, const void* x, const uint32_t* 
 
 spx_status launch_spmv_csr(const spx_csr* A, const void* x, const uint32_t* bits, void* y,
                            const spx_plan* plan, const int32_t* part, Arena& ws, hipStream_t s,
-                           const Unscatter* un, bool* cleared, const TileSorted* ts) {
+                           const Unscatter* un, bool* cleared, const TileSorted* ts, Carries* keep) {
     if (cleared) *cleared = false;
     const bool valid = plan->pattern == SPX_PAT_CSR_SPMSPV;
     switch (A->dtype) {
 #define SPX_DT(DT)                                                                            \
     case DT:                                                                                  \
-        return valid ? launch_csr_t<DT, true>(A, x, bits, y, plan, part, ws, s, un, cleared, ts)  \
-                     : launch_csr_t<DT, false>(A, x, bits, y, plan, part, ws, s, un, cleared, ts);
+        return valid ? launch_csr_t<DT, true>(A, x, bits, y, plan, part, ws, s, un, cleared, ts, keep)  \
+                     : launch_csr_t<DT, false>(A, x, bits, y, plan, part, ws, s, un, cleared, ts, keep);
         SPX_DT(SPX_F32)
         SPX_DT(SPX_F64)
         SPX_DT(SPX_I32)
@@ -332,6 +336,22 @@ spx_status launch_spmv_csr(const spx_csr* A, const void* x, const uint32_t* bits
 #undef SPX_DT
     }
     return fail(SPX_ERR_DTYPE, "spmv: unknown dtype");
+}
+
+template <int DT>
+static spx_status csr_fixup_t(const Carries& c, void* y, hipStream_t s) {
+    using S = SR<DT>;
+    k_csr_merge_fixup<DT><<<(unsigned)std::min<int64_t>(ceil_div(c.tiles, kBlock), 8192), kBlock, 0, s>>>(
+        c.tiles, c.row, (const typename S::Acc*)c.val, (typename S::Y*)y, Unscatter{});
+    SPX_HIP(hipGetLastError());
+    return SPX_OK;
+}
+
+spx_status launch_csr_fixup(const Carries& c, int dtype, void* y, hipStream_t s) {
+    if (c.tiles == 0) return SPX_OK;
+    if (dtype == SPX_F32) return csr_fixup_t<SPX_F32>(c, y, s);
+    if (dtype == SPX_F64) return csr_fixup_t<SPX_F64>(c, y, s);
+    return fail(SPX_ERR_DTYPE, "fix-up: F32 or F64 only");
 }
 
 // --------------------------------------------------------------- column-sorted copy

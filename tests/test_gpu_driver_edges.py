@@ -50,3 +50,26 @@ def test_bfs_tile_edges(n):
     _lib.call("spx_bfs", M._h, s, C.c_void_p(buf.data_ptr() + 4), 1 << 30, None, 0, C.byref(nl), None, 0, None)
     torch.cuda.synchronize()
     assert np.array_equal(buf[1:].cpu().numpy(), want) and int(buf[0]) == 77
+
+
+@pytest.mark.parametrize("pattern", [spx.PAT_SPMV, spx.PAT_CSR_SPMSPV])
+@pytest.mark.parametrize("n", [1, 5, 4095, 4096, 4097, 12289, 40003])
+def test_pagerank_rows_across_tiles(n, pattern):
+    """Balanced row-major products leave the rows that span merge tiles (a
+    third of the vertices point at vertex 1) to the next select, which adds
+    what its chunk of rows lacks; stopped early, to the fold."""
+    _torch()
+    A = _graph(n, n + 1)
+    A = A.with_vals(np.random.default_rng(n).uniform(0.1, 1.0, A.nnz))
+    M = spx.Matrix.from_host(A)
+    plan = spx.Plan()
+    plan.pattern, plan.distribution, plan.writeback = pattern, spx.DIST_BALANCED, 0
+    eps = 1e-3 * 0.15 / n
+    for limit in (2, 10 ** 6):
+        rank, res, _ = M.pagerank(0.85, eps, max_iters=limit, plan=plan, want_residual=True)
+        p, r, k = oracle.pagerank_incremental(A, 0.85, eps, limit)
+        assert M.pr_iters == k
+        # the two add a row's products in different orders: a relative 1e-16
+        # times the products per row and rounds, far below 1e-11
+        for got, want in ((rank, p), (res, r)):
+            assert np.abs(got.cpu().numpy() - want).max() <= 1e-11 * np.abs(want).max(), f"n={n} limit={limit}"
