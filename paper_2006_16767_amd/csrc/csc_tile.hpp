@@ -17,7 +17,6 @@ namespace spx {
 constexpr int kCscIpt = 8;
 constexpr int kCscTile = kBlock * kCscIpt;
 
-
 template <int DT>
 struct CscTileLds {
     int32_t excl[kCscTile + 1];
@@ -30,17 +29,18 @@ struct CscTile {
     int e0, p0, e1, p1, ecount;
 };
 
-// Finds the tile's bounds and stages its entries. Ends with __syncthreads.
+// Finds the tile's bounds and stages its entries (size: items per tile, at most
+// kCscTile). Ends with __syncthreads.
 template <int DT>
 __device__ __forceinline__ CscTile csc_tile_setup(int64_t tile, int32_t nnz_x, int64_t nnz_s,
                                                   const int32_t* __restrict__ x_idx,
                                                   const typename SR<DT>::X* __restrict__ x_val,
                                                   const int32_t* __restrict__ col_ptr,
-                                                  const Excl excl, CscTileLds<DT>& L) {
+                                                  const Excl excl, CscTileLds<DT>& L, int size = kCscTile) {
     using S = SR<DT>;
     const int64_t total = (int64_t)nnz_x + nnz_s;
-    const int64_t d0 = tile * kCscTile;
-    const int64_t d1 = d0 + kCscTile < total ? d0 + kCscTile : total;
+    const int64_t d0 = tile * size;
+    const int64_t d1 = d0 + size < total ? d0 + size : total;
     auto ends = [&](int e) { return excl[e + 1]; };
     if (wave_id() < 2) {
         const int64_t d = wave_id() == 0 ? d0 : d1;
@@ -99,9 +99,10 @@ __device__ __forceinline__ void csc_merge_tile(int64_t tile, int32_t nnz_x, int6
                                                const int32_t* __restrict__ col_ptr,
                                                const int32_t* __restrict__ row_idx,
                                                const typename SR<DT>::V* __restrict__ vals,
-                                               const Excl excl, const Emit& emit, CscTileLds<DT>& L) {
+                                               const Excl excl, const Emit& emit, CscTileLds<DT>& L,
+                                               int size = kCscTile) {
     using S = SR<DT>;
-    const CscTile t = csc_tile_setup<DT>(tile, nnz_x, nnz_s, x_idx, x_val, col_ptr, excl, L);
+    const CscTile t = csc_tile_setup<DT>(tile, nnz_x, nnz_s, x_idx, x_val, col_ptr, excl, L, size);
     for (int p = t.p0 + threadIdx.x; p < t.p1; p += kBlock) {
         const int u = csc_tile_locate<DT>(p, t, L);
         const int k = L.cs[u] + (p - L.excl[u]);

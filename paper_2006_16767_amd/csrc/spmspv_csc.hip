@@ -246,6 +246,20 @@ __global__ __launch_bounds__(kBlock) void k_scan_run_totals(const int32_t* __res
     scan_run_totals(sums, T, off, tmp);
 }
 
+// Bound by the chain of a tile (the search for its bounds, the staging, then
+// per position of a thread a search in LDS and the entry's loads) and, once
+// there are many products, by the atomics (21 G/s). Tiles of kCscTile items
+// from kSpreadTiles tiles on, smaller ones below (a multiple of the
+// workgroup): a short product is spread over the chip, a thread has one or two
+// positions instead of eight, one after the other. On R-MAT 2^20 with 4000
+// entries of x (60 000 products, 32 tiles of kCscTile) the kernel takes 6.8 us,
+// 9.6 before; a call 12.0 against 14.6, with 1000 entries 10.1 against 13.4,
+// with 20 000 entries 28.1 against 28.4. (512 tiles: 12.3 and 28.0; four
+// positions at a time: no faster, 66.8 against 65.4 us where the atomics bound
+// it.)
+constexpr int kSpreadTiles = 256;
+constexpr int kMergeGrid = 1536;  // six workgroups per CU, what LDS admits
+
 template <int DT>
 __global__ __launch_bounds__(kBlock) void k_csc_merge_atomic(int32_t nnz_x, const int32_t* __restrict__ x_idx,
                                                              const typename SR<DT>::X* __restrict__ x_val,
@@ -256,9 +270,11 @@ __global__ __launch_bounds__(kBlock) void k_csc_merge_atomic(int32_t nnz_x, cons
                                                              typename SR<DT>::Y* __restrict__ y) {
     __shared__ CscTileLds<DT> L;
     const int64_t nnz_s = excl[nnz_x];
-    const int64_t tiles = ceil_div((int64_t)nnz_x + nnz_s, kCscTile);
+    const int64_t total = (int64_t)nnz_x + nnz_s;
+    const int size = (int)std::min<int64_t>(kCscTile, ceil_div(ceil_div(total, kSpreadTiles), kBlock) * kBlock);
+    const int64_t tiles = size ? ceil_div(total, size) : 0;
     for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x)
-        csc_merge_tile<DT>(t, nnz_x, nnz_s, x_idx, x_val, col_ptr, row_idx, vals, excl, EmitAtomic<DT>{y}, L);
+        csc_merge_tile<DT>(t, nnz_x, nnz_s, x_idx, x_val, col_ptr, row_idx, vals, excl, EmitAtomic<DT>{y}, L, size);
 }
 
 template <int DT>
@@ -570,7 +586,7 @@ static spx_status launch_csc_t(const CscArgs& A, int32_t nnz_x, const int32_t* x
             }
         } else {
             if (wb == SPX_WB_ATOMIC) {
-                const int grid = (int)std::min<int64_t>(merge_tiles, 8192);
+                const int grid = (int)std::min<int64_t>(ceil_div((int64_t)nnz_x + ub, kBlock), kMergeGrid);
                 k_csc_merge_atomic<DT><<<grid, kBlock, 0, s>>>(nnz_x, x_idx, x_val, A.col_ptr, A.row_idx, vals,
                                                               ex, y);
             } else {
