@@ -269,9 +269,8 @@ struct spx_matrix {
     void* pr_p = nullptr;  // rank, copied to the caller's array at the end
     uint32_t* pr_bad = nullptr;
     bool pr_W_valid = false;
-    // batched path: a second stream for the fused groups' walk, and the events
-    // that fork to it and join it
-    int32_t fused_per_cu = 0;
+    int32_t fused_per_cu = 0;  // batched path: resident workgroups of the groups' walk per CU
+    PermBlocks perm_blocks;    // perm by blocks, for the refresh of vals_csc (built by the first one)
     // profiling
     int profiling = 0;
     double host_ms[2] = {0, 0};
@@ -501,7 +500,7 @@ extern "C" spx_status spx_matrix_destroy(spx_matrix* H) {
                     H->units, H->split_rows, H->segs, H->bfs_front[0], H->bfs_front[1], H->bfs_y, H->drv_count,
                     H->bfs_bits[0], H->bfs_bits[1], H->pr_W, H->pr_r, H->pr_y, H->pr_xidx, H->pr_xval,
                     H->pr_xd[0], H->pr_xd[1], H->pr_p, H->pr_bad, H->cnt_dev, H->slab_part,
-                    H->dots_part};
+                    H->dots_part, H->perm_blocks.at, H->perm_blocks.from};
     for (void* p : ptrs)
         if (p) hipFree(p);
     sell_free(&H->sell);
@@ -819,12 +818,30 @@ extern "C" spx_status spx_matrix_csc(const spx_matrix* H, spx_csc* out) {
     return SPX_OK;
 }
 
+// vals_csc from vals. The blocked form of the permutation is built by the
+// first refresh that finds it worth while, unless that one is being captured
+// or the memory for it is not there.
+static spx_status refresh_csc(spx_matrix* H, int vs, hipStream_t s) {
+    const spx_csr& A = H->csr;
+    if (!H->perm_blocks.at && perm_blocks_pay(A.nnz, A.n, vs)) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        SPX_HIP(hipStreamIsCapturing(s, &cap));
+        if (cap == hipStreamCaptureStatusNone) {
+            const spx_status st = perm_blocks_build(H->perm, A.nnz, vs, &H->perm_blocks, s);
+            if (st != SPX_OK && st != SPX_ERR_ALLOC) return st;
+            if (st == SPX_ERR_ALLOC) (void)hipGetLastError();
+        }
+    }
+    if (H->perm_blocks.at) return gather_blocks(A.vals, H->perm_blocks, H->vals_csc, A.nnz, vs, s);
+    return gather_perm(A.vals, H->perm, H->vals_csc, A.nnz, vs, s);
+}
+
 extern "C" spx_status spx_matrix_values_updated(spx_matrix* H, void* stream) {
     if (!H) return fail(SPX_ERR_ARG, "handle is null");
     const int vs = value_size(H->csr.dtype);
     H->pr_W_valid = false;
     if (vs == 0 || H->csr.nnz == 0) return SPX_OK;
-    SPX_TRY(gather_perm(H->csr.vals, H->perm, H->vals_csc, H->csr.nnz, vs, (hipStream_t)stream));
+    SPX_TRY(refresh_csc(H, vs, (hipStream_t)stream));
     if (H->gsrc) SPX_TRY(gather_perm(H->csr.vals, H->gsrc, H->gvals, H->csr.nnz, vs, (hipStream_t)stream));
     if (H->sell.col) SPX_TRY(sell_refresh(H->sell, H->gorder ? H->gcsr : H->csr, (hipStream_t)stream));
     if (H->ell.col) SPX_TRY(ell_refresh(H->ell, H->gorder ? H->gcsr : H->csr, (hipStream_t)stream));
@@ -1441,10 +1458,12 @@ extern "C" spx_status run_batch(spx_matrix* H, int32_t B, int64_t total_nnz_x, c
         H->nblk = batch_row_blocks(A.m, A.n, A.nnz, A.dtype);
         if (H->nblk) {
             if (hipMalloc((void**)&H->segs, ((size_t)A.n * H->nblk + 1) * 4) != hipSuccess) {
+                (void)hipGetLastError();  // without the table, by atomics
                 H->segs = nullptr;
-                return fail(SPX_ERR_ALLOC, "run_batch: column segments allocation failed");
+                H->nblk = 0;
+            } else {
+                SPX_TRY(batch_build_segs(A, H->col_ptr, H->row_idx, H->nblk, H->segs, s));
             }
-            SPX_TRY(batch_build_segs(A, H->col_ptr, H->row_idx, H->nblk, H->segs, s));
         }
     }
     // capacity-bounded workspace, zeroed at allocation (the per-vector

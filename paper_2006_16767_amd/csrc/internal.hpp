@@ -82,6 +82,14 @@ spx_status expand_rows(const int32_t* row_ptr, int32_t m, int32_t* rows_out, hip
 // out[p] = in[perm[p]] for element size esize (4 or 8)
 spx_status gather_perm(const void* in, const int32_t* perm, void* out, int64_t n, int esize,
                        hipStream_t s);
+// A permutation grouped by the block of its source (prim.hip).
+struct PermBlocks {
+    int32_t* at = nullptr;
+    uint16_t* from = nullptr;
+};
+bool perm_blocks_pay(int64_t n, int64_t runs, int esize);
+spx_status perm_blocks_build(const int32_t* perm, int64_t n, int esize, PermBlocks* out, hipStream_t s);
+spx_status gather_blocks(const void* in, const PermBlocks& b, void* out, int64_t n, int esize, hipStream_t s);
 
 // ------------------------------------------------------------------ kernels
 // Positions a sparse x was scattered to (map[idx[e]], or idx[e] when map is

@@ -386,6 +386,126 @@ spx_status gather_perm(const void* in, const int32_t* perm, void* out, int64_t n
     return SPX_OK;
 }
 
+// The same by blocks of in: a workgroup holds kPermBytes of it in LDS and
+// stores the positions that read them, at[i] ascending within the block. Worth
+// it where a block's positions lie in runs, as for the transpose of a matrix
+// with few columns (a block holds rows, a run a column's entries in them): a
+// store touches a line per run, where the gather above reads a line per entry.
+// The blocks of neighbouring runs go to one XCD, whose L2 joins them to lines.
+// 3.4M entries of a 16384 x 4096 matrix (runs of four): 13 against 23 us.
+constexpr int kPermBytes = 65536;
+constexpr int kPermThreads = 1024;
+
+template <typename T>
+__global__ __launch_bounds__(kPermThreads) void k_gather_blocks(const T* __restrict__ in,
+                                                                const int32_t* __restrict__ at,
+                                                                const uint16_t* __restrict__ from,
+                                                                T* __restrict__ out, int64_t n) {
+    constexpr int E = kPermBytes / (int)sizeof(T), kPer = E / kPermThreads;
+    extern __shared__ __align__(16) char s_raw[];
+    T* block = (T*)s_raw;
+    const int64_t i0 = xcd_tile(blockIdx.x, gridDim.x) * E;
+    const int cnt = (int)min((int64_t)E, n - i0);
+    T v[kPer];
+    int32_t k[kPer];
+    int f[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int q = u * kPermThreads + (int)threadIdx.x;
+        const int64_t i = i0 + min(q, cnt - 1);
+        v[u] = in[i];
+        k[u] = __builtin_nontemporal_load(at + i);
+        f[u] = __builtin_nontemporal_load(from + i);
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int q = u * kPermThreads + (int)threadIdx.x;
+        if (q < cnt) block[q] = v[u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+        if (u * kPermThreads + (int)threadIdx.x < cnt) out[k[u]] = block[f[u]];
+}
+
+// keys[p] = the block of in that position p reads, vals[p] = p
+__global__ __launch_bounds__(kBlock) void k_perm_keys(int64_t n, int shift, const int32_t* __restrict__ perm,
+                                                      uint32_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (p >= n) return;
+    keys[p] = (uint32_t)perm[p] >> shift;
+    vals[p] = (uint32_t)p;
+}
+
+__global__ __launch_bounds__(kBlock) void k_perm_from(int64_t n, int mask, const int32_t* __restrict__ perm,
+                                                      const int32_t* __restrict__ at, uint16_t* __restrict__ from) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) from[i] = (uint16_t)(perm[at[i]] & mask);
+}
+
+// runs: the runs of positions that a block's readers make (the columns of a
+// transposed matrix). From one entry per run on (16384 x 16384 with 13.4M
+// entries: 73 against 86 us; 65536 x 16384 with 21.5M: 110 against 237;
+// longer lists of columns, as graphs have, would store a line per entry), and
+// from 64 blocks on (1.7M entries of 16384 x 1024, 102 blocks: 7 against 14 us;
+// 0.8M, 51 blocks: 13.6 against 14.2, which does not pay for the lists).
+bool perm_blocks_pay(int64_t n, int64_t runs, int esize) {
+    const int64_t E = kPermBytes / esize;
+    return runs <= E && n >= 64 * E && n < ((int64_t)1 << 31);
+}
+
+// at and from of k_gather_blocks, for a permutation of [0, n). Synchronizes.
+spx_status perm_blocks_build(const int32_t* perm, int64_t n, int esize, PermBlocks* out, hipStream_t s) {
+    const int shift = esize == 4 ? 14 : 13;
+    uint32_t *keys = nullptr, *keys2 = nullptr, *at = nullptr, *at2 = nullptr;
+    uint16_t* from = nullptr;
+    int32_t* ws = nullptr;
+    spx_status st = SPX_OK;
+    bool alt = false;
+    if (hipMalloc((void**)&keys, n * 4) != hipSuccess || hipMalloc((void**)&keys2, n * 4) != hipSuccess ||
+        hipMalloc((void**)&at, n * 4) != hipSuccess || hipMalloc((void**)&at2, n * 4) != hipSuccess ||
+        hipMalloc((void**)&from, n * 2) != hipSuccess ||
+        hipMalloc((void**)&ws, radix_ws_elems(n) * 4) != hipSuccess) {
+        st = fail(SPX_ERR_ALLOC, "permutation blocks: allocation failed");
+    } else {
+        const unsigned grid = (unsigned)ceil_div(n, kBlock);
+        int bits = 1;
+        while (((n - 1) >> shift) >> bits) ++bits;
+        k_perm_keys<<<grid, kBlock, 0, s>>>(n, shift, perm, keys, at);
+        st = radix_sort_pairs(keys, at, keys2, at2, n, bits, ws, s, &alt);
+        if (st == SPX_OK) {
+            if (alt) std::swap(at, at2);
+            k_perm_from<<<grid, kBlock, 0, s>>>(n, (1 << shift) - 1, perm, (const int32_t*)at, from);
+            if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
+                st = fail(SPX_ERR_HIP, "permutation blocks");
+        }
+    }
+    for (void* p : {(void*)keys, (void*)keys2, (void*)at2, (void*)ws})
+        if (p) hipFree(p);
+    if (st != SPX_OK) {
+        if (at) hipFree(at);
+        if (from) hipFree(from);
+        return st;
+    }
+    out->at = (int32_t*)at;
+    out->from = from;
+    return SPX_OK;
+}
+
+template <typename T>
+static spx_status gather_blocks_t(const void* in, const PermBlocks& b, void* out, int64_t n, hipStream_t s) {
+    SPX_HIP(hipFuncSetAttribute((const void*)k_gather_blocks<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kPermBytes));
+    k_gather_blocks<T><<<(unsigned)ceil_div(n, kPermBytes / (int)sizeof(T)), kPermThreads, kPermBytes, s>>>(
+        (const T*)in, b.at, b.from, (T*)out, n);
+    SPX_HIP(hipGetLastError());
+    return SPX_OK;
+}
+
+spx_status gather_blocks(const void* in, const PermBlocks& b, void* out, int64_t n, int esize, hipStream_t s) {
+    return esize == 4 ? gather_blocks_t<uint32_t>(in, b, out, n, s) : gather_blocks_t<uint64_t>(in, b, out, n, s);
+}
+
 // ------------------------------------------------------------------ conversions
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_scatter_bits(int32_t nnz_x, const int32_t* __restrict__ idx,
