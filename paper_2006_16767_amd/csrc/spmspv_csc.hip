@@ -172,9 +172,12 @@ __global__ __launch_bounds__(kBlock) void k_csc_prologue(int32_t nnz_x, const in
 // the next call). No workgroup waits for another: the thread that writes a
 // run total fences it before its workgroup arrives, and the last one fences
 // before it reads the totals. Each fence writes back the XCD's L2, so the
-// one-launch form is kept for few runs.
+// one-launch form is kept for few runs. The atomic product adds up to
+// kLsOwnTiles totals itself, in every workgroup: 4000 entries of x on R-MAT
+// 2^20 take 3.6 + 7.3 us that way and 5.6 + 6.8 through the last workgroup.
 constexpr int kLsMaxTiles = 4096;  // nnz_x + 1 <= 2^20
 constexpr int kLsFenceTiles = 32;
+constexpr int kLsOwnTiles = kBlock;
 constexpr int kLsPer = kLsMaxTiles / kBlock;
 
 // off[0..T) = exclusive prefix of sums[0..T), by one 256-thread workgroup
@@ -252,11 +255,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_run_totals(const int32_t* __res
 // from kSpreadTiles tiles on, smaller ones below (a multiple of the
 // workgroup): a short product is spread over the chip, a thread has one or two
 // positions instead of eight, one after the other. On R-MAT 2^20 with 4000
-// entries of x (60 000 products, 32 tiles of kCscTile) the kernel takes 6.8 us,
+// entries of x (60 000 products, 32 tiles of kCscTile) the kernel took 6.8 us,
 // 9.6 before; a call 12.0 against 14.6, with 1000 entries 10.1 against 13.4,
 // with 20 000 entries 28.1 against 28.4. (512 tiles: 12.3 and 28.0; four
 // positions at a time: no faster, 66.8 against 65.4 us where the atomics bound
-// it.)
+// it.) With the run totals added up here as well (kLsOwnTiles) the call takes
+// 10.7, 9.9 and 26.5.
 constexpr int kSpreadTiles = 256;
 constexpr int kMergeGrid = 1536;  // six workgroups per CU, what LDS admits
 
@@ -266,9 +270,19 @@ __global__ __launch_bounds__(kBlock) void k_csc_merge_atomic(int32_t nnz_x, cons
                                                              const int32_t* __restrict__ col_ptr,
                                                              const int32_t* __restrict__ row_idx,
                                                              const typename SR<DT>::V* __restrict__ vals,
-                                                             const Excl excl,
+                                                             Excl excl, const int32_t* __restrict__ sums, int T,
                                                              typename SR<DT>::Y* __restrict__ y) {
     __shared__ CscTileLds<DT> L;
+    __shared__ int32_t s_off[kLsOwnTiles];
+    if (sums) {
+        // the run totals come as they are
+        __shared__ int32_t tmp[kWavesPerBlock];
+        const int32_t v = (int)threadIdx.x < T ? sums[threadIdx.x] : 0;
+        int32_t all;
+        s_off[threadIdx.x] = block_incl_scan<int32_t>(v, tmp, &all) - v;
+        __syncthreads();
+        excl.off = s_off;
+    }
     const int64_t nnz_s = excl[nnz_x];
     const int64_t total = (int64_t)nnz_x + nnz_s;
     const int size = (int)std::min<int64_t>(kCscTile, ceil_div(ceil_div(total, kSpreadTiles), kBlock) * kBlock);
@@ -506,6 +520,8 @@ static spx_status launch_csc_t(const CscArgs& A, int32_t nnz_x, const int32_t* x
         nnz_x > 0 && (dist == SPX_DIST_BALANCED || wb == SPX_WB_SORT || wb == SPX_WB_BUCKET || wb == SPX_WB_MERGE);
     int32_t* excl = nullptr;
     Excl ex{nullptr, nullptr};
+    const int32_t* run_sums = nullptr;  // totals of the runs that the product adds up itself
+    int runs = 0;
     if (need_excl) {
         excl = ws.take<int32_t>((size_t)nnz_x + 1);
         int32_t* sws = ws.take<int32_t>(scan_ws_elems((int64_t)nnz_x + 1));
@@ -519,16 +535,18 @@ static spx_status launch_csc_t(const CscArgs& A, int32_t nnz_x, const int32_t* x
             if (!sums || !off) return fail(SPX_ERR_WORKSPACE, "spmspv_csc: workspace too small");
             const int64_t ywords = fill_y ? (int64_t)(ybytes / 4) : 0;
             const int F = fill_y ? (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(ywords, kBlock), 2048)) : 0;
-            uint32_t* counter = T <= kLsFenceTiles ? A.scan_counter : nullptr;
+            if (wb == SPX_WB_ATOMIC && T <= kLsOwnTiles) run_sums = sums;
+            uint32_t* counter = T <= kLsFenceTiles && !run_sums ? A.scan_counter : nullptr;
             k_csc_lengths_scan<<<(unsigned)(F + T), kBlock, 0, s>>>(nnz_x, x_idx, A.col_ptr, excl, sums, off,
                                                                    counter, (uint32_t*)y, ywords,
                                                                    fill_y ? (int)(ybytes & 3) : 0, zero_word(DT), F);
             SPX_HIP(hipGetLastError());
-            if (!counter) {
+            if (!counter && !run_sums) {
                 k_scan_run_totals<<<1, kBlock, 0, s>>>(sums, (int)T, off);
                 SPX_HIP(hipGetLastError());
             }
-            ex.off = off;
+            ex.off = run_sums ? nullptr : off;
+            runs = (int)T;
         } else if (nnz_x + 1 <= kProMax && ((uintptr_t)y & 3) == 0) {
             const int64_t ywords = fill_y ? (int64_t)(ybytes / 4) : 0;
             const int fill_blocks = fill_y ? (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(ywords, kBlock), 4096)) : 0;
@@ -588,7 +606,7 @@ static spx_status launch_csc_t(const CscArgs& A, int32_t nnz_x, const int32_t* x
             if (wb == SPX_WB_ATOMIC) {
                 const int grid = (int)std::min<int64_t>(ceil_div((int64_t)nnz_x + ub, kBlock), kMergeGrid);
                 k_csc_merge_atomic<DT><<<grid, kBlock, 0, s>>>(nnz_x, x_idx, x_val, A.col_ptr, A.row_idx, vals,
-                                                              ex, y);
+                                                              ex, run_sums, runs, y);
             } else {
                 const int grid = (int)std::min<int64_t>(merge_tiles, 64);
                 k_csc_merge_lds<DT><<<grid, kBlock, (size_t)A.m * sizeof(Acc), s>>>(

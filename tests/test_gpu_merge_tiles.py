@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kind", ["f32", "f64", "i32", "bool"])
-@pytest.mark.parametrize("items", [16, 272, 65518, 65535, 65552, 131088, 600015])
+@pytest.mark.parametrize("items", [16, 272, 65518, 65535, 65552, 131088, 600015,
+                                   4080, 4096, 1048544, 1048576])  # 1, 2, 256, 257 runs of 256 lengths
 def test_tile_size_follows_the_items(kind, items):
     """Every column has 15 entries, so an entry of x is 16 items of the merge
     (65535 and 600015: one column has 14)."""
