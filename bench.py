@@ -234,7 +234,7 @@ def extra_batched(torch, spx, synth, flush, reps=5):
     """Batched vs looped, both halves of the batched workload: 512 sparse
     vectors (densities log-uniform in [1e-4, 0.5]) on R-MAT 2^18 (degree
     32), and 256 rows of a 100k x 50k power-law matrix as x against it.
-    One graph launch of run_batch vs a loop of run() on the same stream."""
+    One call of run_batch vs a loop of run() on the same stream."""
     A = synth.cfg4_rmat()
     r = _batched(torch, spx, A, synth.cfg4_rmat_batch(A.n, 512), "rmat18_deg32_f32_batch512", flush, reps)
     S = synth.cfg4_svm()
