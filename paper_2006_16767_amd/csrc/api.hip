@@ -1274,14 +1274,6 @@ static spx_status select_counts(spx_matrix* H, const spx_vec* x, int64_t nnz_s, 
     return SPX_OK;
 }
 
-// run() for a sparse x with known nnz_s; the column-major kernels get the
-// exact nnz_s too.
-static spx_status run_counts(spx_matrix* H, const spx_vec* x, void* y, int64_t nnz_s, hipStream_t s) {
-    spx_plan p;
-    SPX_TRY(select_counts(H, x, nnz_s, s, &p));
-    return exec_plan(H, x, y, &p, nnz_s, x->nnz_x, s);
-}
-
 // Executes plan p for a sparse x (F32/F64) that the caller has also written
 // dense into xd, at grank[j] when the handle keeps the renumbered copy: the
 // row-major kernels read xd with no conversion (the CSR SpMSpV takes its
@@ -1682,15 +1674,25 @@ extern "C" spx_status spx_bfs(spx_matrix* H, int32_t source, int32_t* level, int
             p = spx_plan{SPX_PAT_CSR_SPMSPV, SPX_DIST_DIRECT, SPX_WB_NONE, -1, 0, 0};
         } else {
             spx_vec x{SPX_VEC_SPARSE, A.n, nf, H->bfs_front[cur], nullptr};
-            if (plan) {
-                SPX_TRY(run_plan(H, &x, H->bfs_y, plan, stream));
+            if (plan)
                 p = *plan;
+            else
+                SPX_TRY(select_counts(H, &x, mf, s, &p));
+            const CscArgs a{A.m, A.n, A.nnz, A.dtype, H->col_ptr, H->row_idx, nullptr, A.row_ptr, H->scan_counter, mf};
+            if (bfs_walks(a, nf, &p)) {
+                H->last_plan = p;
+                record(H, H->ev_kern, true, s);
+                SPX_TRY(launch_bfs_walk(a, nf, x.idx, &p, depth, level, H->bfs_front[cur ^ 1], H->bfs_bits[cur ^ 1],
+                                        H->drv_count, host, s));
+                record(H, H->ev_kern, false, s);
             } else {
-                SPX_TRY(run_counts(H, &x, H->bfs_y, mf, s));
-                p = H->last_plan;
+                if (plan)
+                    SPX_TRY(run_plan(H, &x, H->bfs_y, plan, stream));
+                else
+                    SPX_TRY(exec_plan(H, &x, H->bfs_y, &p, mf, nf, s));
+                SPX_TRY(launch_bfs_update(A.n, H->bfs_y, depth, H->col_ptr, level, H->bfs_front[cur ^ 1],
+                                          H->bfs_bits[cur ^ 1], H->drv_count, host, s));
             }
-            SPX_TRY(launch_bfs_update(A.n, H->bfs_y, depth, H->col_ptr, level, H->bfs_front[cur ^ 1],
-                                      H->bfs_bits[cur ^ 1], H->drv_count, host, s));
         }
         if (depth - 1 < plans_cap) plans[depth - 1] = p;
         SPX_TRY(read_driver_count(H, depth, s, &nf, &mf));

@@ -42,18 +42,6 @@ __global__ __launch_bounds__(kBlock) void k_bfs_seed(int32_t n, int32_t source, 
     }
 }
 
-// The column lengths of the vertices v0 + j with bit j of mask set.
-__device__ __forceinline__ uint32_t degrees(uint32_t mask, int64_t v0, int32_t n, const int32_t* __restrict__ col_ptr) {
-    int32_t cp[kVpt];
-    load_run(col_ptr, v0, (int64_t)n + 1, cp);
-    const int32_t end = v0 + kVpt <= n ? col_ptr[v0 + kVpt] : 0;
-    uint32_t deg = 0;
-#pragma unroll
-    for (int j = 0; j < kVpt; ++j)
-        if ((mask >> j) & 1u) deg += (uint32_t)((j + 1 < kVpt ? cp[j + 1] : end) - cp[j]);
-    return deg;
-}
-
 // Vertices reached by the product and not labelled yet get level L and go
 // to the next frontier. Thread t of a chunk owns its 8 consecutive vertices.
 __global__ __launch_bounds__(kWideBlock) void k_bfs_update(int32_t n, const uint8_t* __restrict__ y, int32_t L,
@@ -70,24 +58,11 @@ __global__ __launch_bounds__(kWideBlock) void k_bfs_update(int32_t n, const uint
         } else {
             for (int j = 0; v0 + j < n; ++j) yy |= (uint64_t)(y[v0 + j] != 0) << (8 * j);
         }
-        uint32_t mask = 0, deg = 0;
-        if (yy) {
-            // the levels together, then the column pointers together (one
-            // vertex after the other is up to eight round trips of each)
-            int32_t lv[kVpt];
-            load_run(level, v0, n, lv);
+        uint32_t reached = 0;
 #pragma unroll
-            for (int j = 0; j < kVpt; ++j) {
-                if (((yy >> (8 * j)) & 0xffu) && lv[j] < 0) {
-                    lv[j] = L;
-                    mask |= 1u << j;
-                }
-            }
-            if (mask) {
-                store_run(level, v0, n, lv);
-                deg = degrees(mask, v0, n, col_ptr);
-            }
-        }
+        for (int j = 0; j < kVpt; ++j) reached |= (uint32_t)(((yy >> (8 * j)) & 0xffu) != 0) << j;
+        uint32_t deg = 0;
+        const uint32_t mask = label_unvisited(reached, v0, n, L, col_ptr, level, &deg);
         write_bits(mask, v0, n, next_bits);
         block_append<kWideBlock>(mask, v0, deg, next, c.count, tmp);
     }

@@ -156,6 +156,44 @@ __device__ __forceinline__ void block_append(uint32_t mask, int64_t v0, uint32_t
     block_append<NT>(mask, high, count, tmp, [&](uint32_t slot, int j) { next[slot] = (int32_t)(v0 + j); });
 }
 
+// The column lengths of the vertices v0 + j with bit j of mask set.
+__device__ __forceinline__ uint32_t degrees(uint32_t mask, int64_t v0, int32_t n, const int32_t* __restrict__ col_ptr) {
+    int32_t cp[kVpt];
+    load_run(col_ptr, v0, (int64_t)n + 1, cp);
+    const int32_t end = v0 + kVpt <= n ? col_ptr[v0 + kVpt] : 0;
+    uint32_t deg = 0;
+#pragma unroll
+    for (int j = 0; j < kVpt; ++j)
+        if ((mask >> j) & 1u) deg += (uint32_t)((j + 1 < kVpt ? cp[j + 1] : end) - cp[j]);
+    return deg;
+}
+
+// Breadth-first search: of the vertices v0 + j with bit j of reached set, the
+// unvisited ones get level L; returned as a mask, *deg their column lengths.
+// The levels are loaded together, then the column pointers together (one
+// vertex after the other is up to eight round trips of each).
+__device__ __forceinline__ uint32_t label_unvisited(uint32_t reached, int64_t v0, int32_t n, int32_t L,
+                                                    const int32_t* __restrict__ col_ptr, int32_t* __restrict__ level,
+                                                    uint32_t* deg) {
+    uint32_t mask = 0;
+    *deg = 0;
+    if (!reached) return 0;
+    int32_t lv[kVpt];
+    load_run(level, v0, n, lv);
+#pragma unroll
+    for (int j = 0; j < kVpt; ++j) {
+        if (((reached >> j) & 1u) && v0 + j < n && lv[j] < 0) {
+            lv[j] = L;
+            mask |= 1u << j;
+        }
+    }
+    if (mask) {
+        store_run(level, v0, n, lv);
+        *deg = degrees(mask, v0, n, col_ptr);
+    }
+    return mask;
+}
+
 // Writes the next frontier's bitvector for the 8 consecutive vertices
 // v0.. of every thread (v0 a multiple of 8): the four threads of one
 // 32-bit word are neighbouring lanes. Every lane of the wave must call it.

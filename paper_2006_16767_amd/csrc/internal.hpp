@@ -302,6 +302,13 @@ spx_status launch_bfs_pull(int32_t n, const int32_t* row_ptr, const int32_t* col
                            int32_t L, const int32_t* col_ptr, int32_t* level, int32_t* next, uint32_t* next_bits,
                            void* count, void* host, hipStream_t s);
 
+// A push level on the bucket walk: product, labels and frontier in one launch
+// (spmspv_bucket.hip), for the plans that bfs_walks accepts.
+bool bfs_walks(const CscArgs& A, int32_t nnz_x, const spx_plan* plan);
+spx_status launch_bfs_walk(const CscArgs& A, int32_t nnz_x, const int32_t* x_idx, const spx_plan* plan, int32_t L,
+                           int32_t* level, int32_t* next, uint32_t* next_bits, void* count, void* host,
+                           hipStream_t s);
+
 // incremental PageRank (pagerank.hip): one launch per stage. count: two
 // packed counters as for breadth-first search, {entries appended to x,
 // their column lengths}, and host the pinned word of the round.

@@ -27,6 +27,7 @@
 
 #include "common.hpp"
 #include "csc_tile.hpp"
+#include "frontier.hpp"
 #include "csc_walk.hpp"
 #include "internal.hpp"
 
@@ -495,6 +496,45 @@ static spx_status launch_bucket_t(const CscArgs& A, int32_t nnz_x, const int32_t
     return SPX_OK;
 }
 
+// A level of the breadth-first search on the walk: the bucket's rows that the
+// frontier reaches are labelled and appended from LDS, with no product in
+// memory and no second launch: 8 to 10 us for 4.9 of the walk, the gap and
+// 5.5 to 6.5 of the update; a search of the R-MAT graph of 2^20 vertices, with
+// three such levels, 199 -> 193 us on one machine.
+template <int G>
+__global__ __launch_bounds__(kAccThreads) void k_bfs_walk(int32_t m, int logR, int32_t nnz_x,
+                                                          const int32_t* __restrict__ x_idx,
+                                                          const int32_t* __restrict__ col_ptr,
+                                                          const int32_t* __restrict__ row_idx, int32_t L,
+                                                          int32_t* __restrict__ level, int32_t* __restrict__ next,
+                                                          uint32_t* __restrict__ next_bits, Counters c) {
+    extern __shared__ __align__(16) char s_raw[];
+    __shared__ Count tmp[kAccThreads / kWave];
+    uint32_t* acc = (uint32_t*)s_raw;
+    const int R = 1 << logR;
+    const int lo = blockIdx.x << logR;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *c.clear = 0;
+    for (int r = threadIdx.x; r < R; r += kAccThreads) acc[r] = 0u;
+    __syncthreads();
+    walk_columns<SPX_BOOL, G>(kAccThreads, nnz_x, x_idx, nullptr, col_ptr, row_idx, lo, lo + R,
+                              [&](int r, int, SR<SPX_BOOL>::X) { acc[r] = 1u; });
+    __syncthreads();
+    for (int r0 = 0; r0 < R; r0 += kAccThreads * kVpt) {
+        const int r = r0 + (int)threadIdx.x * kVpt;
+        uint32_t reached = 0;
+        if (r < R) {
+            const uint4 a = *(const uint4*)(acc + r), b = *(const uint4*)(acc + r + 4);
+            reached = a.x | a.y << 1 | a.z << 2 | a.w << 3 | b.x << 4 | b.y << 5 | b.z << 6 | b.w << 7;
+        }
+        const int64_t v0 = r < R ? (int64_t)lo + r : m;
+        uint32_t deg = 0;
+        const uint32_t mask = label_unvisited(reached, v0, m, L, col_ptr, level, &deg);
+        write_bits(mask, v0, m, next_bits);
+        block_append<kAccThreads>(mask, v0, deg, next, c.count, tmp);
+    }
+    publish_count(c);
+}
+
 // Every bucket's workgroup scans the short columns of x whole and cuts the
 // long ones to its rows by binary search, so a walk's cost follows nnz_x
 // and the average column length, not nnz_s (a hub column costs two
@@ -522,6 +562,17 @@ static void walk_launch(int G, unsigned grid, size_t lds, hipStream_t s, int32_t
     }
 }
 
+// lanes per x entry: the plan's, else the most that send every entry out in
+// one round of the workgroup
+static int walk_lanes(const spx_plan* plan, int32_t nnz_x) {
+    int G = plan->lanes;
+    if (G <= 0) {
+        G = 64;
+        while (G > 1 && (int64_t)nnz_x * G > kAccThreads) G >>= 1;
+    }
+    return G > 64 || (G & (G - 1)) ? 0 : G;
+}
+
 template <int DT>
 static spx_status launch_walk_t(const CscArgs& A, int32_t nnz_x, const int32_t* x_idx, const void* x_val, void* y,
                                 const spx_plan* plan, hipStream_t s) {
@@ -529,14 +580,8 @@ static spx_status launch_walk_t(const CscArgs& A, int32_t nnz_x, const int32_t* 
     BucketGeom g;
     if (!bucket_geometry(A.m, DT, plan->bucket_rows, &g))
         return fail(SPX_ERR_UNSUPPORTED, "bucket write-back: rows per bucket must fit 64 KiB of LDS and at most 4096 buckets");
-    // lanes per x entry: the plan's, else the most that send every entry
-    // out in one round of the workgroup
-    int G = plan->lanes;
-    if (G <= 0) {
-        G = 64;
-        while (G > 1 && (int64_t)nnz_x * G > kAccThreads) G >>= 1;
-    }
-    if (G > 64 || (G & (G - 1))) return fail(SPX_ERR_ARG, "lanes must be a power of two in [1, 64]");
+    const int G = walk_lanes(plan, nnz_x);
+    if (!G) return fail(SPX_ERR_ARG, "lanes must be a power of two in [1, 64]");
     const size_t R = (size_t)1 << g.logR;
     if (A.sparse) {
         const size_t lds = R * sizeof(typename S::Acc) + (S::kVals ? ceil_div(R, 32) * 4 : 0);
@@ -559,6 +604,39 @@ spx_status launch_csc_bucket_walk(const CscArgs& A, int32_t nnz_x, const int32_t
         case SPX_F32_MINPLUS: return launch_walk_t<SPX_F32_MINPLUS>(A, nnz_x, x_idx, x_val, y, plan, s);
     }
     return fail(SPX_ERR_DTYPE, "bucket: unknown dtype");
+}
+
+// Whether a plan's product of a frontier is a walk, over no more buckets (of 64
+// rows or more: whole words of the frontier's bitvector) than the update has
+// workgroups to add to the counter.
+bool bfs_walks(const CscArgs& A, int32_t nnz_x, const spx_plan* plan) {
+    BucketGeom g;
+    return plan->pattern == SPX_PAT_CSC_SPMSPV && nnz_x > 0 && csc_bucket_walks(A, nnz_x, plan) &&
+           bucket_geometry(A.m, SPX_BOOL, plan->bucket_rows, &g) && g.NB <= 2048 && walk_lanes(plan, nnz_x) > 0;
+}
+
+spx_status launch_bfs_walk(const CscArgs& A, int32_t nnz_x, const int32_t* x_idx, const spx_plan* plan, int32_t L,
+                           int32_t* level, int32_t* next, uint32_t* next_bits, void* count, void* host,
+                           hipStream_t s) {
+    BucketGeom g;
+    if (!bucket_geometry(A.m, SPX_BOOL, plan->bucket_rows, &g)) return fail(SPX_ERR_UNSUPPORTED, "search: buckets");
+    const size_t lds = ((size_t)1 << g.logR) * 4;
+    const Counters c = counters_of(count, L, host);
+    switch (walk_lanes(plan, nnz_x)) {
+#define SPX_G(GG)                                                                                              \
+    case GG:                                                                                                   \
+        SPX_HIP(hipFuncSetAttribute((const void*)k_bfs_walk<GG>, hipFuncAttributeMaxDynamicSharedMemorySize,   \
+                                    (int)lds));                                                                \
+        k_bfs_walk<GG><<<(unsigned)g.NB, kAccThreads, lds, s>>>(A.m, g.logR, nnz_x, x_idx, A.col_ptr, A.row_idx, L, \
+                                                               level, next, next_bits, c);                     \
+        break;
+        SPX_G(1) SPX_G(2) SPX_G(4) SPX_G(8) SPX_G(16) SPX_G(32) SPX_G(64)
+#undef SPX_G
+        default:
+            return fail(SPX_ERR_ARG, "lanes must be a power of two in [1, 64]");
+    }
+    SPX_HIP(hipGetLastError());
+    return SPX_OK;
 }
 
 spx_status launch_csc_bucket(const CscArgs& A, int32_t nnz_x, const int32_t* x_idx, const void* x_val, void* y,

@@ -52,6 +52,26 @@ def test_bfs_tile_edges(n):
     assert np.array_equal(buf[1:].cpu().numpy(), want) and int(buf[0]) == 77
 
 
+@pytest.mark.parametrize("bucket_rows", [0, 64, 128, 4096, 16384])
+@pytest.mark.parametrize("lanes", [0, 1, 64])
+def test_bfs_levels_on_the_bucket_walk(bucket_rows, lanes):
+    """Every level on a direct bucket plan: a short frontier runs as one walk
+    per bucket of rows (buckets of whole bitvector words), a long one as the
+    product and the update; the last bucket is ragged."""
+    _torch()
+    n = 20001
+    A = _graph(n, 77)
+    M = spx.Matrix.from_host(A, dtype=spx.BOOL)
+    s = int(A.col_idx[0])
+    want = oracle.bfs_levels(A.col_idx, np.repeat(np.arange(n), np.diff(A.row_ptr)).astype(np.int32), n, s)
+    plan = spx.Plan()
+    plan.pattern, plan.distribution, plan.writeback = spx.PAT_CSC_SPMSPV, spx.DIST_DIRECT, spx.WB_BUCKET
+    plan.bucket_rows, plan.lanes = bucket_rows, lanes
+    level, plans = M.bfs(s, plan=plan)
+    assert np.array_equal(level.cpu().numpy(), want)
+    assert len(plans) == M.bfs_levels and all(p.lanes == lanes and p.bucket_rows == bucket_rows for p in plans)
+
+
 @pytest.mark.parametrize("pattern", [spx.PAT_SPMV, spx.PAT_CSR_SPMSPV])
 @pytest.mark.parametrize("n", [1, 5, 4095, 4096, 4097, 12289, 40003])
 def test_pagerank_rows_across_tiles(n, pattern):
