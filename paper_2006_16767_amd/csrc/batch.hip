@@ -6,6 +6,7 @@
 //                      x_sparsity, and where a tree reads them nnz_s and
 //                      m_sparsity, from the lengths of the columns it selects)
 //  k_batch_scan        deals the vectors that share passes over A out to groups
+//                      and puts the others in order, the longest first
 //  k_batch_slabs       the groups' vectors as dense slabs X^T (n rows = columns
 //                      of A, one slot per vector, a cache line per row)
 //  k_batch_stray       vectors whose indices do not ascend, into their slots
@@ -100,7 +101,7 @@ struct BatchDev {
     // workspace
     BatchPlan* plans;
     int32_t* offs;    // 3 x (B + 1)
-    int32_t* totals;  // 4
+    int32_t* totals;  // 4 (with segs only [0]: the end of gvec)
     int32_t* queue;   // queue heads of the phases, [3] = err of the last run
     int32_t* err;     // of this run, cleared by k_batch_scan
     int32_t* excl_all;  // cap_nnz_x + B
@@ -119,7 +120,7 @@ struct BatchDev {
     int32_t* gcount;  // vectors in groups
     int32_t* heads;   // of the queues of work units, 128 bytes apart
     int32_t* stray;   // a flag per vector: k_batch_slabs met an entry outside its tile
-    int32_t* gvec;    // slot -> vector
+    int32_t* gvec;    // slot -> vector, behind the groups' slots the other vectors for k_batch_rows
     void* xt_all;     // ceil(B / gsize) slabs of (n + 1) x gsize values, row n zero
     int32_t gsize;    // vectors per fused group and slots per slab row
 };
@@ -281,6 +282,30 @@ __global__ __launch_bounds__(kBlock) void k_batch_scan(BatchDev a) {
         count += tot;
     }
     if (threadIdx.x == 0) *a.gcount = count;
+    if (a.segs) {
+        // the others behind them, the longest first (four bins per octave), so
+        // that no long one starts when the rest is done
+        constexpr int kBins = 128;
+        __shared__ int32_t s_bin[kBins];
+        auto bin_of = [](const BatchPlan& p) {
+            const int k = (int)(__float_as_uint((float)max(p.nnz_x, 1)) >> 21) - (127 << 2);
+            return kBins - 1 - min(k, kBins - 1);
+        };
+        for (int i = threadIdx.x; i < kBins; i += kBlock) s_bin[i] = 0;
+        __syncthreads();  // and the slots of the groups are dealt
+        auto rest = [&](int b) { return a.plans[b].gslot < 0; };
+        for (int b = threadIdx.x; b < a.B; b += kBlock)
+            if (rest(b)) atomicAdd(&s_bin[bin_of(a.plans[b])], 1);
+        __syncthreads();
+        const int v = threadIdx.x < kBins ? s_bin[threadIdx.x] : 0;
+        int32_t tot;
+        const int32_t incl = block_incl_scan(v, s_tmp, &tot);
+        if (threadIdx.x < kBins) s_bin[threadIdx.x] = count + incl - v;
+        if (threadIdx.x == 0) a.totals[0] = count + tot;  // without those that were refused
+        __syncthreads();
+        for (int b = threadIdx.x; b < a.B; b += kBlock)
+            if (rest(b)) a.gvec[atomicAdd(&s_bin[bin_of(a.plans[b])], 1)] = b;
+    }
     if (threadIdx.x < 8) a.heads[threadIdx.x * 32] = 0;
     if (a.segs) return;  // no queues
     for (int ph = 0; ph < 3; ++ph) {
@@ -729,10 +754,11 @@ __global__ __launch_bounds__(kBlock) void k_batch_fused(BatchDev a) {
 // read neighbouring segments, in the same cache lines.
 //
 // Bound by the chain from index to segment to entries, by its cache lines
-// (three per segment, 14M) and by Y: 190 us for the 295 vectors below a density
+// (three per segment, 14M) and by Y: 150 us for the 295 vectors below a density
 // of 2 % on R-MAT 2^18 (4.7M segments of 1.8 entries on average, of 13 in the
-// first block; 310 MB of Y). 55 of it is zeroing and storing Y; 16 are adds to
-// one row by several lanes. Four lanes to a segment and a wave to a long one
+// first block; 310 MB of Y), 190 when the vectors came in the batch's order and
+// the last long one ran on alone. 55 of it is zeroing and storing Y; 16 are adds
+// to one row by several lanes. In the batch's order, four lanes to a segment and a wave to a long one
 // took 219 us (where all segments are short it is 5 % faster), 512 threads
 // 252; 128 KB of Y per workgroup 182. Atomics into Y took 760 us, and 54 us
 // for zeroing Y before: the chip does 21 G scattered atomics/s, from one XCD or
@@ -762,10 +788,10 @@ __global__ __launch_bounds__(kRowsThreads) void k_batch_rows(BatchDev a, int32_t
         Acc* y = (Acc*)s_raw;
         constexpr int R = kRowsBytes / (int)sizeof(Acc);
         const int i = blockIdx.x / 8;
-        const int b = b0 + i / a.nblk * 8 + blockIdx.x % 8, blk = i % a.nblk;
-        if (b >= a.B) return;
+        const int at = *a.gcount + b0 + i / a.nblk * 8 + (int)(blockIdx.x % 8), blk = i % a.nblk;
+        if (at >= a.totals[0]) return;
+        const int b = a.gvec[at];
         const BatchPlan p = a.plans[b];
-        if (p.gslot >= 0) return;  // in a group, or refused
         for (int r = threadIdx.x; r < kRowsBytes / 16; r += kRowsThreads) ((uint4*)s_raw)[r] = uint4{0, 0, 0, 0};
         __syncthreads();
         const int32_t* __restrict__ idx = a.idx + p.base;
