@@ -1397,8 +1397,8 @@ static int lanes_for(double avg) {
 }
 
 // Work units of the fused row-major groups of run_batch: consecutive whole
-// rows up to kFusedUnitNnz entries and kFusedUnitRows rows per unit; a longer
-// row becomes pieces of kFusedUnitNnz entries (a split row).
+// rows up to fused_unit_nnz entries and kFusedUnitRows rows per unit; a longer
+// row becomes pieces of that many entries (a split row).
 static spx_status build_units(spx_matrix* H, hipStream_t s) {
     const spx_csr& A = H->csr;
     std::vector<int32_t> rp((size_t)A.m + 1);
@@ -1406,18 +1406,19 @@ static spx_status build_units(spx_matrix* H, hipStream_t s) {
     SPX_HIP(hipStreamSynchronize(s));
     std::vector<int32_t> u;
     std::vector<int32_t> split;
+    const int32_t most = fused_unit_nnz(value_size(A.dtype));
     int32_t r = 0;
     while (r < A.m) {
         const int32_t len = rp[r + 1] - rp[r];
-        if (len > kFusedUnitNnz) {
-            for (int32_t k = rp[r]; k < rp[r + 1]; k += kFusedUnitNnz)
-                u.insert(u.end(), {r, r + 1, k, std::min(k + kFusedUnitNnz, rp[r + 1])});
+        if (len > most) {
+            for (int32_t k = rp[r]; k < rp[r + 1]; k += most)
+                u.insert(u.end(), {r, r + 1, k, std::min(k + most, rp[r + 1])});
             split.push_back(r);
             ++r;
             continue;
         }
         const int32_t r0 = r;
-        while (r < A.m && r - r0 < kFusedUnitRows && rp[r + 1] - rp[r0] <= kFusedUnitNnz) ++r;
+        while (r < A.m && r - r0 < kFusedUnitRows && rp[r + 1] - rp[r0] <= most) ++r;
         u.insert(u.end(), {r0, r, rp[r0], rp[r]});
     }
     H->nunits = (int32_t)(u.size() / 4);

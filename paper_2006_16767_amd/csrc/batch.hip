@@ -18,7 +18,7 @@
 // Groups: a vector whose plan is row-major (SpMV or CSR SpMSpV, any value type
 // but BOOL), or whose entries reach kFusedMinXSparsity of n, joins a group that
 // shares one pass over A: 32 vectors of 4-byte values, 16 of 8-byte ones.
-// k_batch_fused walks work units of A for each group (at most kFusedUnitNnz
+// k_batch_fused walks work units of A for each group (at most fused_unit_nnz
 // entries of at most kFusedUnitRows whole rows, or a piece of a longer row), a
 // wave per unit. Pieces of split rows are added to Y with atomics (their rows
 // of Y are zeroed beforehand); every other row is written once. Non-support
@@ -560,6 +560,8 @@ __global__ __launch_bounds__(kBlock) void k_batch_stray(BatchDev a) {
 // slot, until they are stored. A row's 16-byte pieces are permuted by the row,
 // so that the rows of one slot lie on different banks.
 template <int DT>
+constexpr int kUnitNnz = fused_unit_nnz((int)sizeof(typename SR<DT>::X));
+template <int DT>
 struct FusedEntry {
     int32_t col;
     typename SR<DT>::V val;
@@ -570,8 +572,8 @@ struct FusedLds {
     alignas(16) typename SR<DT>::Acc sums[kFusedUnitRows * group_size<DT>()];
     // lane group h's entries from h * (len + 1), its ends from h * (len + 8):
     // the eight lane groups read from different banks
-    alignas(16) uint16_t end[kFusedUnitNnz + 8 * 8];
-    FusedEntry<DT> e[kFusedUnitNnz + 8];
+    alignas(16) uint16_t end[kUnitNnz<DT> + 8 * 8];
+    FusedEntry<DT> e[kUnitNnz<DT> + 8];
     FusedEntry<DT> none[kFusedSteps];  // past the last step: the slab's zero row
     int64_t y[group_size<DT>()];  // where the vectors' Y begin
 };
@@ -586,14 +588,16 @@ constexpr uint32_t kNoEnd = 0xffff;
 // out together, one run of consecutive rows per vector. A piece of a split row
 // adds its sums to Y with atomics.
 //
-// 590 us for the seven groups of 217 vectors on R-MAT 2^18 (7.6M entries: 53M
-// gathered lines, 90 G lines/s, 55 % of them from L2): 330 of it is what a unit
-// takes without the gathers (90 of that the stores of Y, in lines that units
-// share), and lines that all come from L2 would save 65. Two vectors per lane
-// (512-byte gathers, three times the slab per group) took 1066 us beside the
-// other vectors' walk; eight entries of one row per step, the lane groups' sums
-// added at every row's end, twice the instructions; the next unit's entries
-// loaded ahead gave nothing (661 against 652 us).
+// 527 us for the seven groups of 217 vectors on R-MAT 2^18 (7.6M entries: 53M
+// gathered lines, 100 G lines/s, 55 % of them from L2). With units of 512
+// entries it took 587: 330 of that is what the units took without the gathers
+// (90 of it the stores of Y, in lines that units share), and lines that all come
+// from L2 would have saved 65. Longer units store longer runs of rows, but hold
+// more LDS: 256 entries 725 us, 640 538, 768 527 (12 waves per CU), 1024 602.
+// Two vectors per lane (512-byte gathers, three times the slab per group) took
+// 1066 us beside the other vectors' walk; eight entries of one row per step, the
+// lane groups' sums added at every row's end, twice the instructions; the next
+// unit's entries loaded ahead gave nothing (602 against 588 us).
 template <int DT, bool BUF>
 __device__ __forceinline__ void batch_fused_unit(const BatchDev& a, int g, int32_t unit, FusedLds<DT>& L) {
     using S = SR<DT>;
@@ -621,7 +625,7 @@ __device__ __forceinline__ void batch_fused_unit(const BatchDev& a, int g, int32
     if (lane < GS) L.y[lane] = lane < nvec ? (int64_t)a.gvec[g * GS + lane] * a.m : 0;
     // A streams through once per group: non-temporal, so that L2 keeps the
     // slab rows the gathers re-read
-    constexpr int kPer = kFusedUnitNnz / kWave;
+    constexpr int kPer = kUnitNnz<DT> / kWave;
     FusedEntry<DT> in[kPer];
 #pragma unroll
     for (int p = 0; p < kPer; ++p) {
@@ -635,10 +639,10 @@ __device__ __forceinline__ void batch_fused_unit(const BatchDev& a, int g, int32
     for (int e = 0; e < E; ++e) z.v[e] = S::zero();
     for (int i = lane; i < nrows * 8; i += kWave) *(SlotVals<Acc>*)(L.sums + i * E) = z;
     // lane group h takes the entries from h * len on; inv finds i / len for
-    // i < 512
+    // i < 1024
     const int len = ((cnt + 7) / 8 + 2 * kFusedSteps - 1) / (2 * kFusedSteps) * (2 * kFusedSteps);
-    const uint32_t inv = len > 0 ? (65536u + len - 1) / len : 0;
-    auto group_of = [&](int i) { return (int)(((uint32_t)i * inv) >> 16); };
+    const uint32_t inv = len > 0 ? ((1u << 20) + len - 1) / len : 0;
+    auto group_of = [&](int i) { return (int)(((uint32_t)i * inv) >> 20); };
     // of row r, the lane's piece of its sums
     auto sums_at = [&](int r) { return r * 8 * 16 + ((r & 7) << 4); };
 #pragma unroll
@@ -758,11 +762,11 @@ __global__ __launch_bounds__(kBlock) void k_batch_fused(BatchDev a) {
 // of 2 % on R-MAT 2^18 (4.7M segments of 1.8 entries on average, of 13 in the
 // first block; 310 MB of Y), 190 when the vectors came in the batch's order and
 // the last long one ran on alone. 55 of it is zeroing and storing Y; 16 are adds
-// to one row by several lanes. In the batch's order, four lanes to a segment and a wave to a long one
-// took 219 us (where all segments are short it is 5 % faster), 512 threads
-// 252; 128 KB of Y per workgroup 182. Atomics into Y took 760 us, and 54 us
-// for zeroing Y before: the chip does 21 G scattered atomics/s, from one XCD or
-// all.
+// to one row by several lanes. In the batch's order, four lanes to a segment
+// and a wave to a long one took 219 us (where all segments are short it is 5 %
+// faster), 512 threads 252; 128 KB of Y per workgroup 182. Atomics into Y took
+// 760 us, and 54 us for zeroing Y before: the chip does 21 G scattered
+// atomics/s, from one XCD or all.
 constexpr int kRowsBytes = 65536;
 constexpr int kRowsThreads = 1024;
 constexpr int kRowsSteps = 4;

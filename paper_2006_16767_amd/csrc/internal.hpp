@@ -268,8 +268,8 @@ struct BatchLaunch {
     int32_t row_lanes;
     int32_t persistent_grid;
     // work units of A for the fused row-major groups (null: no fusion): at
-    // most kFusedUnitNnz entries of at most kFusedUnitRows whole rows, or a
-    // piece of a row longer than kFusedUnitNnz
+    // most fused_unit_nnz entries of at most kFusedUnitRows whole rows, or a
+    // piece of a longer row
     const int32_t* units;  // 4 ints per unit
     int32_t nunits;
     const int32_t* split_rows;
@@ -279,7 +279,8 @@ struct BatchLaunch {
     int32_t nblk;
     int32_t* fused_per_cu;  // resident workgroups of the walk per CU, 0 = not asked yet (kept by the handle)
 };
-constexpr int kFusedUnitNnz = 512;
+// entries of a work unit (the walk's LDS per wave is 12 KB with 4-byte values)
+constexpr int fused_unit_nnz(int value_bytes) { return value_bytes == 8 ? 512 : 768; }
 constexpr int kFusedUnitRows = 32;
 size_t batch_ws_size(int32_t m, int32_t n, int dtype, int32_t B, int64_t cap_nnz_x, int64_t tiles_mat,
                      bool by_rows, size_t* zero_from, size_t* zero_bytes);

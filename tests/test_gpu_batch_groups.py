@@ -1,6 +1,6 @@
 """run_batch at the edges of its groups (32 vectors of 4-byte values, 16 of
 8-byte ones), slab tiles (256 columns), row blocks (64 KB of Y), work units
-(512 entries, 32 rows) and column segments, against the oracle."""
+(768 entries, 512 of 8-byte values, 32 rows) and column segments, against the oracle."""
 import numpy as np
 import pytest
 
