@@ -500,7 +500,7 @@ static spx_status launch_bucket_t(const CscArgs& A, int32_t nnz_x, const int32_t
 // frontier reaches are labelled and appended from LDS, with no product in
 // memory and no second launch: 8 to 10 us for 4.9 of the walk, the gap and
 // 5.5 to 6.5 of the update; a search of the R-MAT graph of 2^20 vertices, with
-// three such levels, 199 -> 193 us on one machine.
+// four such levels, 199 -> 193 us on one machine.
 template <int G>
 __global__ __launch_bounds__(kAccThreads) void k_bfs_walk(int32_t m, int logR, int32_t nnz_x,
                                                           const int32_t* __restrict__ x_idx,
