@@ -25,9 +25,14 @@
 // lanes read the second half of a column first, so that the two reads of a
 // wave use all banks.
 //
-// A segment's part in a slab holds at most kSlabCols entries (a segment's
-// indices are distinct), so a lane's running sum is a chain of at most
-// kSlabCols / 16 additions; the 16 lanes' sums are added as a tree.
+// A lane's running sum takes at most kFoldRounds additions: then the 16 lanes'
+// sums are added as a tree and go to the segment's sum in LDS, where a slab
+// (slab_cols(W) distinct indices) adds at most slab_cols(W) / (16 kFoldRounds)
+// of them. In one chain a row that fills a slab would take 256 or 512
+// additions, 1.5e-5 or 3.1e-5 of sum |a x| at worst in FP32; so it is 72 or 76,
+// 4.5e-6 (4096 and 8192 entries). Rows of that length take 3 to 13 % longer for
+// it (200000 x 4096 with 411 full rows, FP32: B = 8 63.6 us against 58.4, B = 64
+// 340 against 329), rows below 1024 entries the same time.
 #include <algorithm>
 #include <utility>
 
@@ -42,6 +47,7 @@ constexpr int kSlabLanes = 16;                            // lanes per segment: 
 constexpr int kSlabGroups = kSlabThreads / kSlabLanes;    // segments in flight per workgroup
 constexpr int kSlabU = 4;                                 // entries per lane and step
 constexpr int kSlabStep = kSlabLanes * kSlabU;
+constexpr int kSlabFold = kFoldRounds / kSlabU;           // steps between folds
 constexpr int kSlabBytes = 128 * 1024;                    // of the CU's 160 KiB
 constexpr int kSlabMaxSegs = 512;                         // segments per workgroup
 
@@ -242,41 +248,45 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab_gather(int32_t nseg, int3
         for (int r = 0; r < rounds; ++r) {
             int ke, kf;
             advance(ke, kf);
-            T acc[W][E];
-#pragma unroll
-            for (int w = 0; w < W; ++w)
-#pragma unroll
-                for (int e = 0; e < E; ++e) acc[w][e] = (T)0;
             int k = ka;
-            bool more;
+            bool more, first = blk == 0;
             do {
-                more = __any(k + kSlabStep < kb);  // uniform over the wave
-                // entries past the end read the zero column with value 0
-                SlabVec<T> p[kSlabU][W];
-                T a[kSlabU];
+                T acc[W][E];
 #pragma unroll
-                for (int u = 0; u < kSlabU; ++u) {
-                    const bool on = k + g + u * kSlabLanes < kb;
-                    slab_read<T, W>(slab, slab_at<W>(on ? c[u] - c0 : width, par16), p[u]);
-                    a[u] = on ? v[u] : (T)0;
+                for (int w = 0; w < W; ++w)
+#pragma unroll
+                    for (int e = 0; e < E; ++e) acc[w][e] = (T)0;
+                int left = kSlabFold;
+                do {
+                    more = __any(k + kSlabStep < kb);  // uniform over the wave
+                    // entries past the end read the zero column with value 0
+                    SlabVec<T> p[kSlabU][W];
+                    T a[kSlabU];
+#pragma unroll
+                    for (int u = 0; u < kSlabU; ++u) {
+                        const bool on = k + g + u * kSlabLanes < kb;
+                        slab_read<T, W>(slab, slab_at<W>(on ? c[u] - c0 : width, par16), p[u]);
+                        a[u] = on ? v[u] : (T)0;
+                    }
+                    fetch(more ? k + kSlabStep : kc, c, v);
+#pragma unroll
+                    for (int u = 0; u < kSlabU; ++u)
+#pragma unroll
+                        for (int w = 0; w < W; ++w)
+#pragma unroll
+                            for (int e = 0; e < E; ++e) acc[w][e] = fma_t(a[u], p[u][w].v[e], acc[w][e]);
+                    k += kSlabStep;
+                } while (more && --left);
+                T f[E / 2];
+                slab_fold<T, W>(acc, f);
+                const int s = r * kSlabGroups + s0;
+                if (g < 2 * W && s < ns) {
+                    T* o = sums + s * kRow + slab_fold_row<T, W>(lane);
+#pragma unroll
+                    for (int i = 0; i < E / 2; ++i) o[i] = first ? f[i] : o[i] + f[i];
                 }
-                fetch(more ? k + kSlabStep : kc, c, v);
-#pragma unroll
-                for (int u = 0; u < kSlabU; ++u)
-#pragma unroll
-                    for (int w = 0; w < W; ++w)
-#pragma unroll
-                        for (int e = 0; e < E; ++e) acc[w][e] = fma_t(a[u], p[u][w].v[e], acc[w][e]);
-                k += kSlabStep;
+                first = false;
             } while (more);
-            T f[E / 2];
-            slab_fold<T, W>(acc, f);
-            const int s = r * kSlabGroups + s0;
-            if (g < 2 * W && s < ns) {
-                T* o = sums + s * kRow + slab_fold_row<T, W>(lane);
-#pragma unroll
-                for (int i = 0; i < E / 2; ++i) o[i] = blk > 0 ? o[i] + f[i] : f[i];
-            }
             ka = kc;
             kb = kd;
             kc = ke;
