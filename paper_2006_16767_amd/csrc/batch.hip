@@ -684,7 +684,8 @@ __device__ __forceinline__ void batch_fused_unit(const BatchDev& a, int g, int32
         }
     };
     static_assert(kFusedSteps == 4, "two words of ends per step");
-    fetch(A, mine);
+    // a unit of empty rows has no entry in LDS to fetch
+    fetch(A, len > 0 ? mine : L.none);
     for (int t0 = 0; t0 < len; t0 += 2 * kFusedSteps) {
         fetch(B, mine + t0 + kFusedSteps);
         const uint4 end = *(const uint4*)(ends + t0);
