@@ -209,9 +209,9 @@ struct spx_matrix {
     DiaMat dia;
     Csr5Mat c5;
     // where each column (row) enters each row (column) block of the LDS slabs
-    // of dX (dvals); allocated on first use
-    int32_t* slab_part = nullptr;
-    int32_t* dots_part = nullptr;
+    // of dX (dvals); built on first use
+    PartTable slab_part, dots_part;
+    size_t grad_ws_refused = SIZE_MAX;  // bytes for the B-minor kernels that could not be had ahead
     bool cols_ascend = false;  // the column indices ascend within every row (F32 and F64 handles only)
     // column-sorted copy of the renumbered CSR for the balanced SpMV with
     // 2048-item tiles (kept with the renumbered copy when n <= 2^21)
@@ -499,8 +499,8 @@ extern "C" spx_status spx_matrix_destroy(spx_matrix* H) {
                     H->part[0][0], H->part[0][1], H->part[1][0], H->part[1][1], H->dev_sel, H->bws,
                     H->units, H->split_rows, H->segs, H->bfs_front[0], H->bfs_front[1], H->bfs_y, H->drv_count,
                     H->bfs_bits[0], H->bfs_bits[1], H->pr_W, H->pr_r, H->pr_y, H->pr_xidx, H->pr_xval,
-                    H->pr_xd[0], H->pr_xd[1], H->pr_p, H->pr_bad, H->cnt_dev, H->slab_part,
-                    H->dots_part, H->perm_blocks.at, H->perm_blocks.from};
+                    H->pr_xd[0], H->pr_xd[1], H->pr_p, H->pr_bad, H->cnt_dev, H->slab_part.at,
+                    H->dots_part.at, H->perm_blocks.at, H->perm_blocks.from};
     for (void* p : ptrs)
         if (p) hipFree(p);
     sell_free(&H->sell);
@@ -1852,68 +1852,111 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
 }
 
 // ------------------------------------------------------------------ backward
+// A call that is being captured can neither allocate nor build a table that
+// an eager call could read before the graph has run.
+static spx_status is_captured(hipStream_t s, bool* yes) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    SPX_HIP(hipStreamIsCapturing(s, &c));
+    *yes = c != hipStreamCaptureStatusNone;
+    return SPX_OK;
+}
+
+// The B-minor kernels' workspace, for a call that does not use it: a captured
+// call for which no table of bounds has been built falls back on those kernels
+// and cannot allocate. Where the memory is not there it is left out.
+static spx_status keep_grad_ws(spx_matrix* H, int32_t B, hipStream_t s) {
+    const size_t bytes = grad_ws_bytes(H->csr.m, H->csr.n, B, H->csr.dtype);
+    if (bytes <= H->ws_bytes || bytes >= H->grad_ws_refused) return SPX_OK;
+    bool captured = false;
+    SPX_TRY(is_captured(s, &captured));
+    if (captured) return SPX_OK;
+    if (ensure_ws(H, bytes) != SPX_OK) {
+        (void)hipGetLastError();
+        H->grad_ws_refused = bytes;
+    }
+    return SPX_OK;
+}
+
 extern "C" spx_status spmv_csr_batch(spx_matrix* H, int32_t B, const void* X, void* Y, void* stream) {
     if (!H || (B > 0 && (!X || !Y))) return fail(SPX_ERR_ARG, "null argument");
     if (B < 0) return fail(SPX_ERR_SHAPE, "B must be >= 0");
     const spx_csr& A = H->csr;
     if (A.dtype != SPX_F32 && A.dtype != SPX_F64)
         return fail(SPX_ERR_DTYPE, "the fused batch SpMV supports F32 and F64");
-    if (slab_gather_fits(A.m, A.n, A.nnz, B, A.dtype, nullptr))
-        return slab_gather(A.m, A.n, A.nnz, B, A.dtype, nullptr, A.row_ptr, nullptr, A.col_idx, A.vals, X, Y,
-                           (hipStream_t)stream);
+    hipStream_t s = (hipStream_t)stream;
+    if (slab_gather_fits(A.m, A.n, A.nnz, B, A.dtype, nullptr)) {
+        SPX_TRY(keep_grad_ws(H, B, s));
+        return slab_gather(A.m, A.n, A.nnz, B, A.dtype, nullptr, A.row_ptr, nullptr, A.col_idx, A.vals, X, Y, s);
+    }
     SPX_TRY(ensure_ws(H, grad_ws_bytes(A.m, A.n, B, A.dtype)));
     Arena ws(H->ws, H->ws_bytes);
-    return launch_spmv_batch(A.row_ptr, A.col_idx, A.vals, A.m, A.n, A.dtype, B, X, Y, ws, (hipStream_t)stream);
+    return launch_spmv_batch(A.row_ptr, A.col_idx, A.vals, A.m, A.n, A.dtype, B, X, Y, ws, s);
 }
 
-// A table of block bounds, built on first use (the pattern of A is fixed).
-static spx_status ensure_part(int32_t** part, int32_t nseg, const SlabBlocks& b, const int32_t* seg_ptr,
-                              const int32_t* idx, hipStream_t s) {
-    if (*part || b.nblk == 1) return SPX_OK;
+// A table of block bounds, built on first use (the pattern of A is fixed),
+// but not by a call that is being captured: the graph may run long after the
+// next eager call. *have = false: there is none, nor will there be where its
+// memory was refused.
+static spx_status ensure_part(PartTable* t, int32_t nseg, const SlabBlocks& b, const int32_t* seg_ptr,
+                              const int32_t* idx, hipStream_t s, bool* have) {
+    *have = t->at || b.nblk == 1;
+    if (*have || t->refused) return SPX_OK;
+    bool captured = false;
+    SPX_TRY(is_captured(s, &captured));
+    if (captured) return SPX_OK;
     int32_t* p = nullptr;
-    if (hipMalloc((void**)&p, (size_t)b.nblk * nseg * 4) != hipSuccess)
-        return fail(SPX_ERR_ALLOC, "block bounds: allocation failed");
+    if (hipMalloc((void**)&p, (size_t)b.nblk * nseg * 4) != hipSuccess) {
+        (void)hipGetLastError();
+        t->refused = true;
+        return SPX_OK;
+    }
     const spx_status st = slab_part_build(nseg, b, seg_ptr, idx, p, s);
     if (st != SPX_OK) {
         hipFree(p);
         return st;
     }
-    *part = p;
+    t->at = p;
+    *have = true;
     return SPX_OK;
 }
 
 // dX = G A over the CSC copy (its rows ascend within a column, so G's rows
 // of length m can pass through LDS in blocks)
-static bool dx_in_slabs(const spx_matrix* H, int32_t B) {
+static spx_status dx_in_slabs(spx_matrix* H, int32_t B, hipStream_t s, bool* yes) {
     const spx_csr& A = H->csr;
     const SlabBlocks b = slab_blocks(A.m);
-    return slab_gather_fits(A.n, A.m, A.nnz, B, A.dtype, &b);
+    *yes = slab_gather_fits(A.n, A.m, A.nnz, B, A.dtype, &b);
+    return *yes ? ensure_part(&H->slab_part, A.n, b, H->col_ptr, H->row_idx, s, yes) : SPX_OK;
 }
 
 static spx_status run_dx(spx_matrix* H, int32_t B, const void* G, void* dX, hipStream_t s) {
     const spx_csr& A = H->csr;
-    if (dx_in_slabs(H, B)) {
+    bool slabs = false;
+    SPX_TRY(dx_in_slabs(H, B, s, &slabs));
+    if (slabs) {
         const SlabBlocks b = slab_blocks(A.m);
-        SPX_TRY(ensure_part(&H->slab_part, A.n, b, H->col_ptr, H->row_idx, s));
-        return slab_gather(A.n, A.m, A.nnz, B, A.dtype, &b, H->col_ptr, H->slab_part, H->row_idx, H->vals_csc, G, dX,
-                           s);
+        SPX_TRY(keep_grad_ws(H, B, s));
+        return slab_gather(A.n, A.m, A.nnz, B, A.dtype, &b, H->col_ptr, H->slab_part.at, H->row_idx, H->vals_csc, G,
+                           dX, s);
     }
     SPX_TRY(ensure_ws(H, grad_ws_bytes(A.m, A.n, B, A.dtype)));
     Arena ws(H->ws, H->ws_bytes);
     return launch_dx(H->col_ptr, H->row_idx, H->vals_csc, A.m, A.n, A.dtype, B, G, dX, ws, s);
 }
 
-static bool dvals_in_slabs(const spx_matrix* H, int32_t B) {
+static spx_status dvals_in_slabs(spx_matrix* H, int32_t B, hipStream_t s, bool* yes) {
     const spx_csr& A = H->csr;
-    return H->cols_ascend && slab_dots_fits(A.m, A.n, A.nnz, B, A.dtype);
+    *yes = H->cols_ascend && slab_dots_fits(A.m, A.n, A.nnz, B, A.dtype);
+    return *yes ? ensure_part(&H->dots_part, A.m, dots_blocks(A.n), A.row_ptr, A.col_idx, s, yes) : SPX_OK;
 }
 
 static spx_status run_dvals(spx_matrix* H, int32_t B, const void* G, const void* X, void* dvals, hipStream_t s) {
     const spx_csr& A = H->csr;
-    if (dvals_in_slabs(H, B)) {
-        const SlabBlocks b = dots_blocks(A.n);
-        SPX_TRY(ensure_part(&H->dots_part, A.m, b, A.row_ptr, A.col_idx, s));
-        return slab_dots(A.m, A.n, A.nnz, B, A.dtype, A.row_ptr, H->dots_part, A.col_idx, G, X, dvals, s);
+    bool slabs = false;
+    SPX_TRY(dvals_in_slabs(H, B, s, &slabs));
+    if (slabs) {
+        SPX_TRY(keep_grad_ws(H, B, s));
+        return slab_dots(A.m, A.n, A.nnz, B, A.dtype, A.row_ptr, H->dots_part.at, A.col_idx, G, X, dvals, s);
     }
     SPX_TRY(ensure_ws(H, grad_ws_bytes(A.m, A.n, B, A.dtype)));
     Arena ws(H->ws, H->ws_bytes);
@@ -1945,7 +1988,10 @@ extern "C" spx_status spx_backward(spx_matrix* H, int32_t B, const void* G, cons
     const int dt = A.dtype;
     if (dt != SPX_F32 && dt != SPX_F64) return fail(SPX_ERR_DTYPE, "backward supports F32 and F64");
     hipStream_t s = (hipStream_t)stream;
-    if ((dX && dx_in_slabs(H, B)) || (dvals && dvals_in_slabs(H, B))) {
+    bool dx_slabs = false, dvals_slabs = false;
+    if (dX) SPX_TRY(dx_in_slabs(H, B, s, &dx_slabs));
+    if (dvals) SPX_TRY(dvals_in_slabs(H, B, s, &dvals_slabs));
+    if (dx_slabs || dvals_slabs) {
         // a gradient that does not go through LDS makes its own B-minor copies
         if (dX) SPX_TRY(run_dx(H, B, G, dX, s));
         return dvals ? run_dvals(H, B, G, X, dvals, s) : SPX_OK;

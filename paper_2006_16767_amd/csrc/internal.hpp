@@ -361,6 +361,10 @@ struct SlabBlocks {
     int32_t nblk = 1;
     int32_t cb = 0;
 };
+struct PartTable {
+    int32_t* at = nullptr;
+    bool refused = false;  // there was no memory for it
+};
 SlabBlocks slab_blocks(int32_t N);  // of slab_gather
 SlabBlocks dots_blocks(int32_t n);  // of slab_dots
 spx_status slab_part_build(int32_t nseg, const SlabBlocks& b, const int32_t* seg_ptr, const int32_t* idx,

@@ -1,0 +1,131 @@
+"""What the library's host code does around its kernels where something fails
+or the stream is being captured: which kernels it launches, what it allocates
+and when it waits. Runs without a GPU, on a stand-in for the HIP runtime
+(hip_stub.cpp) that only writes these calls down; every scenario in a process
+of its own."""
+import ctypes as C
+import importlib.util
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB_PY = os.path.join(os.path.dirname(HERE), "paper_2006_16767_amd", "_lib.py")
+ALLOCATION_REFUSED, ALLOCATION_ALLOWED = 1, 2  # during a capture
+
+
+class Stub:
+    def __init__(self, path):
+        # before libspx, so that its references bind to the stand-in
+        self.so = C.CDLL(path, mode=C.RTLD_GLOBAL)
+        self.so.stub_log.restype = C.c_char_p
+        self.so.stub_fail_sizes.argtypes = [C.c_size_t, C.c_size_t]
+        self.so.stub_total.argtypes = [C.c_uint64]
+        spec = importlib.util.spec_from_file_location("spx_lib", LIB_PY)
+        self.L = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(self.L)
+        self.lib = self.L.load()
+        self.keep = []
+
+    def array(self, kind, values):
+        a = (kind * max(1, len(values)))(*values)
+        self.keep.append(a)
+        return C.addressof(a)
+
+    def zeros(self, bytes_):
+        a = (C.c_char * bytes_)()
+        self.keep.append(a)
+        return C.addressof(a)
+
+    def matrix(self, m, n, per_row, dtype=None):
+        """per_row entries in the first columns of each row; device memory is
+        host memory, so the arrays serve as they are."""
+        L = self.L
+        nnz = m * per_row
+        csr = L.Csr(m, n, nnz, L.F32 if dtype is None else dtype, self.array(C.c_int32, range(0, nnz + 1, per_row)),
+                    self.array(C.c_int32, list(range(per_row)) * m), self.zeros(4 * nnz))
+        h = C.c_void_p()
+        assert self.lib.spx_matrix_create(C.byref(csr), L.NO_RENUMBER | L.FORMAT_CSR, None, C.byref(h)) == 0
+        return h
+
+    def calls(self, f, *args):
+        """The status of f(*args) and what the library asked of the runtime."""
+        self.so.stub_clear_log()
+        rc = f(*args)
+        return rc, self.so.stub_log().decode().split("\n")[:-1]
+
+
+def kernels(log):
+    return [line for line in log if line.startswith("launch")]
+
+
+def has(log, name):
+    return any(name in line for line in log)
+
+
+def block_bounds_under_capture(s, mode):
+    """The first backward of a handle is a captured one: no table of bounds is
+    built (it would be filled when the graph runs), the kernels that need none
+    are launched, in the workspace that the forward left; the next eager call
+    builds the tables and reads them."""
+    m, n, B = 8192, 600, 64
+    H = s.matrix(m, n, 200)
+    X, G, Y, dX, dv = (s.zeros(4 * k) for k in (B * n, B * m, B * m, B * n, m * 200))
+    rc, log = s.calls(s.lib.spmv_csr_batch, H, B, X, Y, None)
+    assert rc == 0 and has(log, "k_slab_gather")
+    s.so.stub_capturing(mode)
+    for call, args in ((s.lib.spx_backward, (G, X, dX, dv)), (s.lib.spmv_csr_transpose, (G, dX)),
+                       (s.lib.dvals_pattern, (G, X, dv)), (s.lib.spmv_csr_batch, (X, Y))):
+        rc, log = s.calls(call, H, B, *args, None)
+        assert rc == 0, s.lib.spx_last_error()
+        assert kernels(log) == log and not has(log, "k_slab_part") and not has(log, "k_slab_dots"), log
+        assert has(log, "k_seg_gather") or has(log, "k_sddmm") or call is s.lib.spmv_csr_batch
+    s.so.stub_capturing(0)
+    rc, log = s.calls(s.lib.spx_backward, H, B, G, X, dX, dv, None)
+    assert rc == 0 and sum("k_slab_part" in line for line in log) == 2
+    assert has(log, "k_slab_gather") and has(log, "k_slab_dots")
+    s.so.stub_capturing(mode)
+    rc, log = s.calls(s.lib.spx_backward, H, B, G, X, dX, dv, None)
+    assert rc == 0 and kernels(log) == log and has(log, "k_slab_gather") and has(log, "k_slab_dots")
+
+
+def block_bounds_without_memory(s):
+    """No memory for the tables of bounds: the kernels that need none, and
+    the tables are not tried again."""
+    m, n, B = 8192, 600, 64
+    H = s.matrix(m, n, 200)
+    X, G, dX, dv = (s.zeros(4 * k) for k in (B * n, B * m, B * n, m * 200))
+    s.so.stub_fail_sizes(2 * n * 4, 2 * m * 4)
+    rc, log = s.calls(s.lib.spx_backward, H, B, G, X, dX, dv, None)
+    assert rc == 0 and sum("malloc-failed" in line for line in log) == 2
+    assert has(log, "k_seg_gather") and has(log, "k_sddmm")
+    rc, log = s.calls(s.lib.spx_backward, H, B, G, X, dX, dv, None)
+    assert rc == 0 and kernels(log) == log and has(log, "k_seg_gather") and has(log, "k_sddmm")
+
+
+SCENARIOS = {
+    "block_bounds_captured_no_allocation": lambda s: block_bounds_under_capture(s, ALLOCATION_REFUSED),
+    "block_bounds_captured_allocation": lambda s: block_bounds_under_capture(s, ALLOCATION_ALLOWED),
+    "block_bounds_without_memory": block_bounds_without_memory,
+}
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    path = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", os.path.join(HERE, "hip_stub.cpp"), "-o", path],
+                   check=True)
+    return path
+
+
+@pytest.mark.parametrize("name", SCENARIOS)
+def test_host_calls(name, stub):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), name, stub], capture_output=True, text=True,
+                       timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    SCENARIOS[sys.argv[1]](Stub(sys.argv[2]))
