@@ -1779,7 +1779,17 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
     a.stage = PR_INIT;
     SPX_TRY(launch_pagerank(a, s));
     SPX_TRY(fill_u32((uint32_t*)H->drv_count, 0u, 64, s));
+    // A select that is still to store its total when the call returns early
+    // would store it into the word that the next call waits on.
+    struct Settle {
+        hipStream_t s;
+        bool counting = false;
+        ~Settle() {
+            if (counting) (void)hipStreamSynchronize(s);
+        }
+    } settle{s};
     auto enqueue_select = [&](int32_t round, bool list) -> spx_status {
+        settle.counting = true;
         a.stage = PR_SELECT;
         a.list = list;
         a.round = round;
@@ -1809,6 +1819,7 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
         int32_t nx = 0;
         int64_t ns = 0;  // column lengths of supp(x)
         SPX_TRY(read_driver_count(H, round, s, &nx, &ns));
+        settle.counting = false;
         spx_plan p{};
         if (spec) {
             // an empty x gave y = 0: nothing to count and nothing to fold

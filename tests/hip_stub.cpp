@@ -20,7 +20,8 @@ struct Counters { void* count; void* clear; uint32_t* done; volatile uint64_t* h
 std::map<const void*, std::string> g_names;
 Config g_config;
 std::string g_log;
-std::string g_fail_launch;       // a kernel whose next launch fails
+std::string g_fail_launch;       // a kernel whose launch fails once,
+int g_fail_skip = 0;             // after this many that do not
 int g_capturing = 0;             // 1: allocation is refused, 2: allowed
 size_t g_fail_from = SIZE_MAX, g_fail_to = 0;  // allocations of these sizes fail
 int g_error = kOk;
@@ -65,7 +66,7 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* lds, void** strea
 int hipLaunchKernel(const void* f, Dim3, Dim3, void** args, size_t, void*) {
     const std::string& name = g_names[f];
     log("launch " + name);
-    if (!g_fail_launch.empty() && name.find(g_fail_launch) != std::string::npos) {
+    if (!g_fail_launch.empty() && name.find(g_fail_launch) != std::string::npos && g_fail_skip-- == 0) {
         g_fail_launch.clear();
         return g_error = kLaunchFailure;
     }
@@ -127,6 +128,9 @@ void stub_fail_sizes(size_t from, size_t to) {
     g_fail_from = from;
     g_fail_to = to;
 }
-void stub_fail_launch(const char* kernel) { g_fail_launch = kernel; }
+void stub_fail_launch(const char* kernel, int skip) {
+    g_fail_launch = kernel;
+    g_fail_skip = skip;
+}
 void stub_total(uint64_t v) { g_totals.push_back(v); }
 }

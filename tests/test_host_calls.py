@@ -105,7 +105,32 @@ def block_bounds_without_memory(s):
     assert rc == 0 and kernels(log) == log and has(log, "k_seg_gather") and has(log, "k_sddmm")
 
 
+def ranking_that_fails_with_a_count_to_come(s):
+    """The product queued behind a round's select fails: the call waits for
+    the select, whose total would else reach the word that the next call
+    waits on."""
+    m = 64
+    H = s.matrix(m, m, 16)
+    rank = s.zeros(4 * m)
+    plan = s.L.Plan(s.L.PAT_SPMV, s.L.DIST_BALANCED, s.L.WB_NONE, 0, 0, 0)
+    iters = C.c_int32()
+    args = lambda products: (H, 0.85, 1e-6, products, C.byref(plan), rank, None, C.byref(iters), None, 0, None)
+    assert s.calls(s.lib.spx_pagerank, *args(0))[0] == 0  # the column sums
+    s.so.stub_total(80 << 32 | 5)
+    s.so.stub_total(80 << 32 | 5)
+    s.so.stub_fail_launch(b"k_csr_merge", 1)
+    rc, log = s.calls(s.lib.spx_pagerank, *args(5))
+    assert rc == -7 and sum("k_pr_select" in line for line in log) == 2
+    select = max(i for i, line in enumerate(log) if "k_pr_select" in line)
+    assert has(log[select:], "k_csr_merge") and has(log[select:], "sync"), log
+    # and a ranking that ends by itself does not wait for the last product
+    s.so.stub_total(0)
+    rc, log = s.calls(s.lib.spx_pagerank, *args(5))
+    assert rc == 0 and iters.value == 0 and kernels(log) == log
+
+
 SCENARIOS = {
+    "ranking_that_fails_with_a_count_to_come": ranking_that_fails_with_a_count_to_come,
     "block_bounds_captured_no_allocation": lambda s: block_bounds_under_capture(s, ALLOCATION_REFUSED),
     "block_bounds_captured_allocation": lambda s: block_bounds_under_capture(s, ALLOCATION_ALLOWED),
     "block_bounds_without_memory": block_bounds_without_memory,
