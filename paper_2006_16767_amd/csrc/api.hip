@@ -270,7 +270,9 @@ struct spx_matrix {
     uint32_t* pr_bad = nullptr;
     bool pr_W_valid = false;
     int32_t fused_per_cu = 0;  // batched path: resident workgroups of the groups' walk per CU
-    PermBlocks perm_blocks;    // perm by blocks, for the refresh of vals_csc (built by the first one)
+    PermBlocks perm_blocks;    // perm by blocks, for the refresh of vals_csc (built by the second one)
+    bool refreshed = false;            // there has been a refresh,
+    bool perm_blocks_refused = false;  // and there was no memory for perm_blocks
     // profiling
     int profiling = 0;
     double host_ms[2] = {0, 0};
@@ -818,19 +820,33 @@ extern "C" spx_status spx_matrix_csc(const spx_matrix* H, spx_csc* out) {
     return SPX_OK;
 }
 
-// vals_csc from vals. The blocked form of the permutation is built by the
-// first refresh that finds it worth while, unless that one is being captured
-// or the memory for it is not there.
+// A call that is being captured can neither allocate nor build a table that
+// an eager call could read before the graph has run.
+static spx_status is_captured(hipStream_t s, bool* yes) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    SPX_HIP(hipStreamIsCapturing(s, &c));
+    *yes = c != hipStreamCaptureStatusNone;
+    return SPX_OK;
+}
+
+// vals_csc from vals. The blocked form of the permutation takes 290 us and 6
+// bytes per entry and saves 10 us a refresh (3.4M entries of a 16384 x 4096
+// matrix), so a handle that is refreshed once does not pay for it: it is built
+// by the second refresh, unless that one is being captured.
 static spx_status refresh_csc(spx_matrix* H, int vs, hipStream_t s) {
     const spx_csr& A = H->csr;
-    if (!H->perm_blocks.at && perm_blocks_pay(A.nnz, A.n, vs)) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        SPX_HIP(hipStreamIsCapturing(s, &cap));
-        if (cap == hipStreamCaptureStatusNone) {
+    if (!H->perm_blocks.at && !H->perm_blocks_refused && perm_blocks_pay(A.nnz, A.n, vs)) {
+        bool captured = false;
+        SPX_TRY(is_captured(s, &captured));
+        if (!captured && H->refreshed) {
             const spx_status st = perm_blocks_build(H->perm, A.nnz, vs, &H->perm_blocks, s);
             if (st != SPX_OK && st != SPX_ERR_ALLOC) return st;
-            if (st == SPX_ERR_ALLOC) (void)hipGetLastError();
+            if (st == SPX_ERR_ALLOC) {
+                (void)hipGetLastError();
+                H->perm_blocks_refused = true;
+            }
         }
+        if (!captured) H->refreshed = true;
     }
     if (H->perm_blocks.at) return gather_blocks(A.vals, H->perm_blocks, H->vals_csc, A.nnz, vs, s);
     return gather_perm(A.vals, H->perm, H->vals_csc, A.nnz, vs, s);
@@ -1863,15 +1879,6 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
 }
 
 // ------------------------------------------------------------------ backward
-// A call that is being captured can neither allocate nor build a table that
-// an eager call could read before the graph has run.
-static spx_status is_captured(hipStream_t s, bool* yes) {
-    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    SPX_HIP(hipStreamIsCapturing(s, &c));
-    *yes = c != hipStreamCaptureStatusNone;
-    return SPX_OK;
-}
-
 // The B-minor kernels' workspace, for a call that does not use it: a captured
 // call for which no table of bounds has been built falls back on those kernels
 // and cannot allocate. Where the memory is not there it is left out.

@@ -105,6 +105,33 @@ def block_bounds_without_memory(s):
     assert rc == 0 and kernels(log) == log and has(log, "k_seg_gather") and has(log, "k_sddmm")
 
 
+def refresh(s):
+    """The first refresh is a launch. The second one orders the permutation by
+    blocks (it allocates and waits), unless it is being captured; from then on
+    a refresh is a launch again."""
+    H = s.matrix(1 << 14, 300, 64)  # 64 blocks of 16384 entries
+    rc, log = s.calls(s.lib.spx_matrix_values_updated, H, None)
+    assert rc == 0 and len(log) == 1 and has(log, "k_gather_perm"), log
+    s.so.stub_capturing(ALLOCATION_ALLOWED)
+    rc, log = s.calls(s.lib.spx_matrix_values_updated, H, None)
+    assert rc == 0 and len(log) == 1 and has(log, "k_gather_perm"), log
+    s.so.stub_capturing(0)
+    rc, log = s.calls(s.lib.spx_matrix_values_updated, H, None)
+    assert rc == 0 and has(log, "k_perm_keys") and has(log, "sync") and has(log[-1:], "k_gather_blocks"), log
+    rc, log = s.calls(s.lib.spx_matrix_values_updated, H, None)
+    assert rc == 0 and len(log) == 1 and has(log, "k_gather_blocks"), log
+
+
+def refresh_without_memory(s):
+    H = s.matrix(1 << 14, 300, 64)
+    assert s.calls(s.lib.spx_matrix_values_updated, H, None)[0] == 0
+    s.so.stub_fail_sizes(2 << 20, 2 << 20)  # the 16-bit half of the ordered permutation
+    rc, log = s.calls(s.lib.spx_matrix_values_updated, H, None)
+    assert rc == 0 and has(log, "malloc-failed") and has(log[-1:], "k_gather_perm"), log
+    rc, log = s.calls(s.lib.spx_matrix_values_updated, H, None)
+    assert rc == 0 and len(log) == 1 and has(log, "k_gather_perm"), log
+
+
 def ranking_that_fails_with_a_count_to_come(s):
     """The product queued behind a round's select fails: the call waits for
     the select, whose total would else reach the word that the next call
@@ -130,6 +157,8 @@ def ranking_that_fails_with_a_count_to_come(s):
 
 
 SCENARIOS = {
+    "refresh": refresh,
+    "refresh_without_memory": refresh_without_memory,
     "ranking_that_fails_with_a_count_to_come": ranking_that_fails_with_a_count_to_come,
     "block_bounds_captured_no_allocation": lambda s: block_bounds_under_capture(s, ALLOCATION_REFUSED),
     "block_bounds_captured_allocation": lambda s: block_bounds_under_capture(s, ALLOCATION_ALLOWED),
