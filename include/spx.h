@@ -412,7 +412,10 @@ spx_status spx_run_times(spx_matrix *H, double *out, int32_t cap, int32_t *count
  * column-major, a block of rows of Y at a time in LDS, or with device
  * atomics for BOOL and where A has too few entries for that. The calls
  * are kernels on the given stream; nothing synchronizes except the first
- * call on a handle and a workspace reallocation.
+ * call on a handle and a workspace reallocation. The handle keeps the
+ * workspace, and for the row blocks a table of where each column enters
+ * each block: 4 bytes per column and block of 64 KB of Y, at most 32 per
+ * entry of A (without the memory for it, device atomics).
  * total_nnz_x (host) is an upper bound of vec_ptr[B] used to size the
  * workspace. Vector indices must be unique within a vector; they may
  * come in any order.

@@ -242,6 +242,7 @@ struct spx_matrix {
     int32_t nunits = 0;
     int32_t* segs = nullptr;  // the columns' segments in blocks of rows, for run_batch
     int32_t nblk = 0;
+    bool segs_refused = false;  // there was no memory for them
     int32_t* split_rows = nullptr;
     int32_t nsplit = 0;
     // breadth-first search buffers (allocated on first use)
@@ -1463,16 +1464,20 @@ extern "C" spx_status run_batch(spx_matrix* H, int32_t B, int64_t total_nnz_x, c
     SPX_TRY(cached_part(H, A, 0, &bal, s, &part));
     const int64_t tiles_mat = ceil_div((int64_t)A.m + A.nnz, 2048);
     if (!H->units && A.dtype != SPX_BOOL && A.m > 0) SPX_TRY(build_units(H, s));
-    if (!H->segs) {
-        H->nblk = batch_row_blocks(A.m, A.n, A.nnz, A.dtype);
-        if (H->nblk) {
-            if (hipMalloc((void**)&H->segs, ((size_t)A.n * H->nblk + 1) * 4) != hipSuccess) {
-                (void)hipGetLastError();  // without the table, by atomics
-                H->segs = nullptr;
-                H->nblk = 0;
-            } else {
-                SPX_TRY(batch_build_segs(A, H->col_ptr, H->row_idx, H->nblk, H->segs, s));
+    if (!H->segs && !H->segs_refused) {
+        const int32_t nblk = batch_row_blocks(A.m, A.n, A.nnz, A.dtype);
+        int32_t* segs = nullptr;
+        if (nblk && hipMalloc((void**)&segs, ((size_t)A.n * nblk + 1) * 4) != hipSuccess) {
+            (void)hipGetLastError();  // without the table, by atomics
+            H->segs_refused = true;
+        } else if (nblk) {
+            const spx_status st = batch_build_segs(A, H->col_ptr, H->row_idx, nblk, segs, s);
+            if (st != SPX_OK) {
+                hipFree(segs);
+                return st;
             }
+            H->segs = segs;
+            H->nblk = nblk;
         }
     }
     // capacity-bounded workspace, zeroed at allocation (the per-vector

@@ -105,6 +105,27 @@ def block_bounds_without_memory(s):
     assert rc == 0 and kernels(log) == log and has(log, "k_seg_gather") and has(log, "k_sddmm")
 
 
+def batch_table(s, without_memory):
+    """run_batch's table of column segments: where its memory is refused the
+    products go by atomics and it is not tried again; where its build fails
+    the next call builds it."""
+    m, n, B = 40000, 64, 2  # three blocks of 16384 rows
+    H = s.matrix(m, n, 8)
+    args = (H, B, 6, s.array(C.c_int32, [0, 3, 6]), s.array(C.c_int32, [0, 1, 2] * 2), s.zeros(24), s.zeros(4 * B * m),
+            None)
+    if without_memory:
+        s.so.stub_fail_sizes(4 * (3 * n + 1), 4 * (3 * n + 1))
+        rc, log = s.calls(s.lib.run_batch, *args)
+        assert rc == 0 and has(log, "malloc-failed") and has(log, "k_batch_phase"), log
+        rc, log = s.calls(s.lib.run_batch, *args)
+        assert rc == 0 and kernels(log) == log and has(log, "k_batch_phase"), log
+    else:
+        s.so.stub_fail_launch(b"k_segs", 0)
+        assert s.calls(s.lib.run_batch, *args)[0] == -7
+        rc, log = s.calls(s.lib.run_batch, *args)
+        assert rc == 0 and has(log, "k_segs") and has(log, "k_batch_rows"), log
+
+
 def refresh(s):
     """The first refresh is a launch. The second one orders the permutation by
     blocks (it allocates and waits), unless it is being captured; from then on
@@ -157,6 +178,8 @@ def ranking_that_fails_with_a_count_to_come(s):
 
 
 SCENARIOS = {
+    "batch_table_without_memory": lambda s: batch_table(s, True),
+    "batch_table_not_built": lambda s: batch_table(s, False),
     "refresh": refresh,
     "refresh_without_memory": refresh_without_memory,
     "ranking_that_fails_with_a_count_to_come": ranking_that_fails_with_a_count_to_come,
