@@ -1900,6 +1900,20 @@ static spx_status keep_grad_ws(spx_matrix* H, int32_t B, hipStream_t s) {
     return SPX_OK;
 }
 
+// Whether arrays of a_elems and b_elems values (of the handle's type) share memory.
+static bool rows_overlap(const spx_matrix* H, int64_t a_elems, const void* a, int64_t b_elems, const void* b) {
+    const size_t es = value_size(H->csr.dtype);
+    const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+    return pa < pb + (size_t)b_elems * es && pb < pa + (size_t)a_elems * es;
+}
+
+// The slab kernels read their operands while they write. A result that shares
+// memory with one (a product in place) is left to the B-minor kernels, which
+// copy the operands first.
+static bool dx_in_place(const spx_matrix* H, int32_t B, const void* G, const void* dX) {
+    return rows_overlap(H, (int64_t)B * H->csr.m, G, (int64_t)B * H->csr.n, dX);
+}
+
 extern "C" spx_status spmv_csr_batch(spx_matrix* H, int32_t B, const void* X, void* Y, void* stream) {
     if (!H || (B > 0 && (!X || !Y))) return fail(SPX_ERR_ARG, "null argument");
     if (B < 0) return fail(SPX_ERR_SHAPE, "B must be >= 0");
@@ -1907,7 +1921,8 @@ extern "C" spx_status spmv_csr_batch(spx_matrix* H, int32_t B, const void* X, vo
     if (A.dtype != SPX_F32 && A.dtype != SPX_F64)
         return fail(SPX_ERR_DTYPE, "the fused batch SpMV supports F32 and F64");
     hipStream_t s = (hipStream_t)stream;
-    if (slab_gather_fits(A.m, A.n, A.nnz, B, A.dtype, nullptr)) {
+    if (slab_gather_fits(A.m, A.n, A.nnz, B, A.dtype, nullptr) &&
+        !rows_overlap(H, (int64_t)B * A.n, X, (int64_t)B * A.m, Y)) {
         SPX_TRY(keep_grad_ws(H, B, s));
         return slab_gather(A.m, A.n, A.nnz, B, A.dtype, nullptr, A.row_ptr, nullptr, A.col_idx, A.vals, X, Y, s);
     }
@@ -1945,17 +1960,17 @@ static spx_status ensure_part(PartTable* t, int32_t nseg, const SlabBlocks& b, c
 
 // dX = G A over the CSC copy (its rows ascend within a column, so G's rows
 // of length m can pass through LDS in blocks)
-static spx_status dx_in_slabs(spx_matrix* H, int32_t B, hipStream_t s, bool* yes) {
+static spx_status dx_in_slabs(spx_matrix* H, int32_t B, const void* G, const void* dX, hipStream_t s, bool* yes) {
     const spx_csr& A = H->csr;
     const SlabBlocks b = slab_blocks(A.m);
-    *yes = slab_gather_fits(A.n, A.m, A.nnz, B, A.dtype, &b);
+    *yes = slab_gather_fits(A.n, A.m, A.nnz, B, A.dtype, &b) && !dx_in_place(H, B, G, dX);
     return *yes ? ensure_part(&H->slab_part, A.n, b, H->col_ptr, H->row_idx, s, yes) : SPX_OK;
 }
 
 static spx_status run_dx(spx_matrix* H, int32_t B, const void* G, void* dX, hipStream_t s) {
     const spx_csr& A = H->csr;
     bool slabs = false;
-    SPX_TRY(dx_in_slabs(H, B, s, &slabs));
+    SPX_TRY(dx_in_slabs(H, B, G, dX, s, &slabs));
     if (slabs) {
         const SlabBlocks b = slab_blocks(A.m);
         SPX_TRY(keep_grad_ws(H, B, s));
@@ -1967,16 +1982,18 @@ static spx_status run_dx(spx_matrix* H, int32_t B, const void* G, void* dX, hipS
     return launch_dx(H->col_ptr, H->row_idx, H->vals_csc, A.m, A.n, A.dtype, B, G, dX, ws, s);
 }
 
-static spx_status dvals_in_slabs(spx_matrix* H, int32_t B, hipStream_t s, bool* yes) {
+static spx_status dvals_in_slabs(spx_matrix* H, int32_t B, const void* G, const void* X, const void* dvals,
+                                 hipStream_t s, bool* yes) {
     const spx_csr& A = H->csr;
-    *yes = H->cols_ascend && slab_dots_fits(A.m, A.n, A.nnz, B, A.dtype);
+    *yes = H->cols_ascend && slab_dots_fits(A.m, A.n, A.nnz, B, A.dtype) &&
+           !rows_overlap(H, (int64_t)B * A.m, G, A.nnz, dvals) && !rows_overlap(H, (int64_t)B * A.n, X, A.nnz, dvals);
     return *yes ? ensure_part(&H->dots_part, A.m, dots_blocks(A.n), A.row_ptr, A.col_idx, s, yes) : SPX_OK;
 }
 
 static spx_status run_dvals(spx_matrix* H, int32_t B, const void* G, const void* X, void* dvals, hipStream_t s) {
     const spx_csr& A = H->csr;
     bool slabs = false;
-    SPX_TRY(dvals_in_slabs(H, B, s, &slabs));
+    SPX_TRY(dvals_in_slabs(H, B, G, X, dvals, s, &slabs));
     if (slabs) {
         SPX_TRY(keep_grad_ws(H, B, s));
         return slab_dots(A.m, A.n, A.nnz, B, A.dtype, A.row_ptr, H->dots_part.at, A.col_idx, G, X, dvals, s);
@@ -2012,9 +2029,10 @@ extern "C" spx_status spx_backward(spx_matrix* H, int32_t B, const void* G, cons
     if (dt != SPX_F32 && dt != SPX_F64) return fail(SPX_ERR_DTYPE, "backward supports F32 and F64");
     hipStream_t s = (hipStream_t)stream;
     bool dx_slabs = false, dvals_slabs = false;
-    if (dX) SPX_TRY(dx_in_slabs(H, B, s, &dx_slabs));
-    if (dvals) SPX_TRY(dvals_in_slabs(H, B, s, &dvals_slabs));
-    if (dx_slabs || dvals_slabs) {
+    if (dX) SPX_TRY(dx_in_slabs(H, B, G, dX, s, &dx_slabs));
+    if (dvals) SPX_TRY(dvals_in_slabs(H, B, G, X, dvals, s, &dvals_slabs));
+    // (dX over G: both gradients from one copy of G, made before dX)
+    if (dx_slabs || (dvals_slabs && !(dX && dx_in_place(H, B, G, dX)))) {
         // a gradient that does not go through LDS makes its own B-minor copies
         if (dX) SPX_TRY(run_dx(H, B, G, dX, s));
         return dvals ? run_dvals(H, B, G, X, dvals, s) : SPX_OK;

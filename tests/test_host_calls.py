@@ -105,6 +105,36 @@ def block_bounds_without_memory(s):
     assert rc == 0 and kernels(log) == log and has(log, "k_seg_gather") and has(log, "k_sddmm")
 
 
+def layer_products_in_place(s):
+    """A result that shares memory with an operand (a square layer in place,
+    gradients over G or X): the kernels that copy the operand first, and with
+    dX over G both gradients from the one copy of G."""
+    n, B = 2048, 64
+    H = s.matrix(n, n, 200)
+    X, G, dX, dv = (s.zeros(4 * k) for k in (B * n, B * n, B * n, 200 * n))
+
+    def ran(f, *args):
+        rc, log = s.calls(f, H, B, *args, None)
+        assert rc == 0, s.lib.spx_last_error()
+        return [line for line in kernels(log) if "k_slab_part" not in line]
+
+    # apart, through the slabs
+    assert all("k_slab" in k for k in ran(s.lib.spmv_csr_batch, X, G) + ran(s.lib.spmv_csr_transpose, G, dX) +
+               ran(s.lib.dvals_pattern, G, X, dv) + ran(s.lib.spx_backward, G, X, dX, dv))
+    last = 4 * (B * n - 1)
+    for f, args in ((s.lib.spmv_csr_batch, (X, X)), (s.lib.spmv_csr_batch, (X, X + last)),
+                    (s.lib.spmv_csr_transpose, (G, G)), (s.lib.spmv_csr_transpose, (G + last, G)),
+                    (s.lib.dvals_pattern, (dv, X, dv)), (s.lib.dvals_pattern, (G, dv + 4, dv)),
+                    (s.lib.spx_backward, (G, None, G, None)), (s.lib.spx_backward, (G, X, G, dv))):
+        log = ran(f, *args)
+        assert has(log[:1], "k_transpose") and not has(log, "k_slab"), (f.__name__, log)
+    # one copy of G, made before dX
+    assert sum("k_transpose" in k for k in log) == 2 and has(log[1:2], "k_seg_gather"), log
+    # a gradient that is apart goes through the slabs
+    log = ran(s.lib.spx_backward, dv, X, dX, dv)
+    assert has(log[:1], "k_slab_gather") and has(log[1:], "k_transpose") and has(log[-1:], "k_sddmm"), log
+
+
 def batch_table(s, without_memory):
     """run_batch's table of column segments: where its memory is refused the
     products go by atomics and it is not tried again; where its build fails
@@ -178,6 +208,7 @@ def ranking_that_fails_with_a_count_to_come(s):
 
 
 SCENARIOS = {
+    "layer_products_in_place": layer_products_in_place,
     "batch_table_without_memory": lambda s: batch_table(s, True),
     "batch_table_not_built": lambda s: batch_table(s, False),
     "refresh": refresh,
