@@ -10,7 +10,7 @@
 // at a random place. Gathering it from L2 (a B-minor copy, a row of B values
 // per entry) moves 4 B bytes per entry through the L2 and the address path:
 // 860 MB for the 16384 x 4096 layer at 5 % and B = 64, 57 us at 15 TB/s. Here
-// a workgroup holds a slab of the operand in LDS, kSlabCols columns of a few
+// a workgroup holds a slab of the operand in LDS, slab_cols(W) columns of a few
 // batch rows (32 bytes a column: 8 FP32 or 4 FP64 batch rows, one or two
 // 16-byte LDS reads per entry), built from the B-major operand itself (no
 // B-minor copy), and streams the segments' indices and values past it. The
@@ -518,8 +518,7 @@ spx_status slab_part_build(int32_t nseg, const SlabBlocks& b, const int32_t* seg
 }
 
 // Mean entries a segment must have per slab: below it the segment's share of
-// a workgroup is its bounds, its fold and idle lanes, and the gather from L2
-// is the faster one.
+// a workgroup is its bounds, its fold and idle lanes.
 constexpr double kSlabMinEntries = 8.0;
 
 // 16-byte columns for few batch rows, and for operands of up to twice the
@@ -534,11 +533,60 @@ static int slab_width(int32_t N, int32_t B) {
 // the entries' arrays are addressed by 32-bit byte offsets
 static bool slab_addresses(int32_t nnz, int dtype) { return (int64_t)nnz * (dtype == SPX_F64 ? 8 : 4) < (int64_t(1) << 31); }
 
+// Segments per workgroup and batch rows per workgroup of the gather.
+struct SlabTiling {
+    int32_t st, nchunk;
+};
+static SlabTiling slab_tiling(int32_t nseg, int32_t B, int NB, int cus) {
+    SlabTiling t;
+    t.nchunk = (int32_t)ceil_div(B, NB);
+    // about a workgroup per CU (the slab fills its LDS), and enough segments
+    // in each for its 64 groups
+    const int64_t want = std::max<int64_t>(1, cus / t.nchunk);
+    t.st = (int32_t)std::min<int64_t>(kSlabMaxSegs, std::max<int64_t>(kSlabGroups, ceil_div(nseg, want)));
+    return t;
+}
+
+// Whether the gather through slabs of cb columns is the faster one, by what
+// the two take in us on a chip of 256 CUs. The slab kernel works by
+// workgroups, one per CU: for each slab a fill, then rounds of 64 segments that
+// cost at least a step of 64 entries each, again for every 4 to 8 FP32 (2 to 4
+// FP64) batch rows. The gather from L2 (k_seg_gather behind a transpose) has a
+// wave per segment and 64 batch rows, whatever the batch: its entries at the
+// chip's rate, or one segment's chain where there are few; past 8 MB the
+// B-minor copy no longer lies in the L2s. The constants are a fit to 2368
+// products (forward with 256 to 8192 columns, dX over 1 to 64 slabs, 8 to 512
+// entries per segment and slab, B = 1 to 256, both types). The rule takes the
+// slower kernel by more than 6 % in 12 of them (24 % at most), the mean alone
+// (from 8 entries on) took it in 529. L2 gather against slabs: 300000 x 4096
+// with 8 entries a row, FP32, 74 against 184 us at B = 64 and 65 against 31 at
+// B = 8; 100000 x 4096 at B = 64, FP32, 40 / 73 us with 16 entries a row, 98 /
+// 79 with 64; FP64 100 / 155 with 32, 363 / 225 with 128; dX of 262144 x 4096
+// (64 slabs) at B = 1, FP32, 48 / 140 us with 8 entries a row, 193 / 163 with 32.
+static bool slab_gather_pays(int32_t nseg, int32_t N, int32_t nnz, int32_t B, int es, int W, int32_t nblk, int32_t cb) {
+    constexpr int kCus = 256;
+    const SlabTiling t = slab_tiling(nseg, B, W * 16 / es, kCus);
+    const double grid = (double)ceil_div(nseg, t.st) * t.nchunk;
+    const double rounds = (double)ceil_div(std::min(t.st, nseg), kSlabGroups);
+    const double len = (double)nnz / nseg;
+    const double steps = std::max(1.0, len / nblk / kSlabStep + 0.25);
+    const double fill = 0.88 + 0.95 * W * cb / slab_cols(2);
+    const double round = 0.2 + (0.06 * (4 + es) + 0.2 * W) * steps;
+    const double slab_us = 4.5 + std::max(1.0, grid / kCus) * nblk * (fill + rounds * round);
+    const double in_mb = (double)N * B * es * 1e-6;
+    const double far = std::min(1.0, std::max(0.0, (in_mb - 8.0) / 24.0));
+    const double rate_us = nseg * (0.08 + 0.013 * (es / 4) * len * (1.0 + 0.28 * far)) * 1e-3;
+    const double l2_us = 10.4 + 0.5 * in_mb + (double)ceil_div(B, kWave) * std::max(rate_us, 0.11 * len);
+    return slab_us < l2_us;
+}
+
 bool slab_gather_fits(int32_t nseg, int32_t N, int32_t nnz, int32_t B, int dtype, const SlabBlocks* blocks) {
     if (nseg <= 0 || N <= 0 || B <= 0 || !slab_addresses(nnz, dtype)) return false;
-    if (!blocks && (dtype == SPX_F64 ? slab_width<double>(N, B) : slab_width<float>(N, B)) == 0) return false;
-    const int32_t nblk = blocks ? blocks->nblk : 1;
-    return (double)nnz >= kSlabMinEntries * (double)nseg * nblk;
+    const int es = dtype == SPX_F64 ? 8 : 4;
+    const int32_t nblk = blocks ? blocks->nblk : 1, cb = blocks ? blocks->cb : N;
+    const int W = es == 8 ? slab_width<double>(cb, B) : slab_width<float>(cb, B);
+    return W > 0 && (double)nnz >= kSlabMinEntries * (double)nseg * nblk &&
+           slab_gather_pays(nseg, N, nnz, B, es, W, nblk, cb);
 }
 
 // lanes that hold an entry's batch rows
@@ -566,14 +614,9 @@ template <typename T, int W>
 static spx_status slab_gather_w(int32_t nseg, int32_t N, int32_t nnz, int32_t B, const SlabBlocks& b, const int32_t* seg_ptr,
                                 const int32_t* part, const int32_t* idx, const T* vals, const T* in, T* out,
                                 hipStream_t s) {
-    constexpr int NB = W * SlabVec<T>::E;
-    const int32_t nchunk = (int32_t)ceil_div(B, NB);
     int cus = 0;
     SPX_TRY(slab_cus(&cus));
-    // about a workgroup per CU (the slab fills its LDS), and enough segments
-    // in each for its 64 groups
-    const int64_t want = std::max<int64_t>(1, cus / nchunk);
-    const int32_t st = (int32_t)std::min<int64_t>(kSlabMaxSegs, std::max<int64_t>(kSlabGroups, ceil_div(nseg, want)));
+    const auto [st, nchunk] = slab_tiling(nseg, B, W * SlabVec<T>::E, cus);
     const int64_t grid = ceil_div(nseg, st) * nchunk;
     if (grid > 0x7fffffff) return fail(SPX_ERR_SHAPE, "batch gather: too many batch rows");
     const size_t lds = slab_gather_lds<T, W>(b.cb, st);
@@ -590,8 +633,7 @@ static spx_status slab_gather_t(int32_t nseg, int32_t N, int32_t nnz, int32_t B,
                                 const int32_t* part, const int32_t* idx, const void* vals, const void* in, void* out,
                                 hipStream_t s) {
     const SlabBlocks b = blocks ? *blocks : SlabBlocks{1, N};
-    const int W = b.cb <= slab_cols(2) && B > SlabVec<T>::E ? 2 : 1;
-    if (W == 2)
+    if (slab_width<T>(b.cb, B) == 2)
         return slab_gather_w<T, 2>(nseg, N, nnz, B, b, seg_ptr, part, idx, (const T*)vals, (const T*)in, (T*)out, s);
     return slab_gather_w<T, 1>(nseg, N, nnz, B, b, seg_ptr, part, idx, (const T*)vals, (const T*)in, (T*)out, s);
 }

@@ -135,6 +135,29 @@ def layer_products_in_place(s):
     assert has(log[:1], "k_slab_gather") and has(log[1:], "k_transpose") and has(log[-1:], "k_sddmm"), log
 
 
+def layer_kernel_by_size(s):
+    """Forward and dX go to the faster kernel, where one is much the faster
+    on the GPU: few entries per segment and slab, many batch rows, 8-byte
+    values and many slabs belong to the gather from L2."""
+    L2, SLAB = "k_seg_gather", "k_slab_gather"
+    for m, n, per_row, dtype, want in (
+            (300000, 4096, 8, s.L.F32, {("fwd", 8): SLAB, ("fwd", 64): L2, ("fwd", 256): L2}),
+            (100000, 1024, 16, s.L.F64, {("fwd", 4): SLAB, ("fwd", 64): L2}),
+            (100000, 1024, 128, s.L.F64, {("fwd", 64): SLAB}),
+            (16384, 8192, 8, s.L.F32, {("fwd", 8): SLAB, ("fwd", 64): L2}),
+            (2000, 1024, 8, s.L.F32, {("fwd", 1): SLAB, ("fwd", 64): SLAB, ("fwd", 256): SLAB}),
+            (16384, 4096, 205, s.L.F32, {("fwd", 64): SLAB, ("dX", 64): SLAB}),
+            (65536, 1000, 2, s.L.F32, {("dX", 1): L2, ("dX", 64): L2}),
+            (65536, 1000, 31, s.L.F32, {("dX", 1): SLAB, ("dX", 64): SLAB}),
+            (65536, 16384, 32, s.L.F64, {("dX", 1): SLAB, ("dX", 64): L2})):
+        H = s.matrix(m, n, per_row, dtype)
+        for (what, B), kernel in want.items():
+            f = s.lib.spmv_csr_batch if what == "fwd" else s.lib.spmv_csr_transpose
+            # (nothing reads or writes the operands here)
+            rc, log = s.calls(f, H, B, 1 << 50, 1 << 51, None)
+            assert rc == 0 and has(log, kernel) and not has(log, L2 if kernel == SLAB else SLAB), (m, n, per_row, B, log)
+
+
 def batch_table(s, without_memory):
     """run_batch's table of column segments: where its memory is refused the
     products go by atomics and it is not tried again; where its build fails
@@ -208,6 +231,7 @@ def ranking_that_fails_with_a_count_to_come(s):
 
 
 SCENARIOS = {
+    "layer_kernel_by_size": layer_kernel_by_size,
     "layer_products_in_place": layer_products_in_place,
     "batch_table_without_memory": lambda s: batch_table(s, True),
     "batch_table_not_built": lambda s: batch_table(s, False),
