@@ -595,11 +595,31 @@ static int dots_lanes(int32_t B, int dtype) {
     return B <= E ? 1 : B <= 4 * E ? 4 : 16;
 }
 
+// Segments (rows) per workgroup of the gradient of the values.
+static int32_t dots_rows(int32_t m, int32_t nblk, int cus) {
+    return (int32_t)std::max<int64_t>(kSlabGroups, ceil_div(m, std::max(1, cus / nblk)));
+}
+
+// With more batch rows than a slab holds a workgroup passes over its entries
+// again, adding to what it stored, and there are no more workgroups for it: it
+// takes half a chip of them and 16 entries per row and block to beat the
+// gather from L2, which spreads every batch over the chip (FP32 at B = 256,
+// gather against slabs in us: 2000 x 256 with 256 entries a row, 32 workgroups,
+// 61 / 86; 2000 x 1024 with 32, 64 workgroups, 17 / 24; 16384 x 1024 with 16, 8
+// to a block, 33 / 36; 16384 x 1024 with 32, 46 / 37; 2000 x 4096 with 128, 43 /
+// 26. FP64 at B = 64: 2000 x 256 with 256, 37 / 57; 100000 x 256 with 16, 80 /
+// 37). With the batch in one slab the slabs were the faster ones in all of
+// 1110 products measured.
 bool slab_dots_fits(int32_t m, int32_t n, int32_t nnz, int32_t B, int dtype) {
     if (m <= 0 || n <= 0 || B <= 0 || !slab_addresses(nnz, dtype)) return false;
-    const int64_t nblk = ceil_div(n, kDotsBytes / (16 * dots_lanes(B, dtype)));
+    constexpr int kCus = 256;
+    const int lanes = dots_lanes(B, dtype);
+    const int32_t nblk = (int32_t)ceil_div(n, kDotsBytes / (16 * lanes));
+    const bool again = B > lanes * (dtype == SPX_F64 ? 2 : 4);
+    if (again && ceil_div(m, dots_rows(m, nblk, kCus)) * nblk < kCus / 2) return false;
     // and the table of bounds stays below the index array
-    return (double)nnz >= kSlabMinEntries * (double)m * nblk && nnz >= (int64_t)m * ceil_div(n, kDotsGrain);
+    return (double)nnz >= (again ? 2 : 1) * kSlabMinEntries * (double)m * nblk &&
+           nnz >= (int64_t)m * ceil_div(n, kDotsGrain);
 }
 
 static spx_status slab_cus(int* cus) {
@@ -652,7 +672,7 @@ static spx_status slab_dots_l(int32_t m, int32_t n, int32_t nnz, int32_t B, cons
     int cus = 0;
     SPX_TRY(slab_cus(&cus));
     const int32_t nblk = (int32_t)ceil_div(n, dots_cols<LPE>());
-    const int32_t st = (int32_t)std::max<int64_t>(kSlabGroups, ceil_div(m, std::max(1, cus / nblk)));
+    const int32_t st = dots_rows(m, nblk, cus);
     const int64_t grid = ceil_div(m, st) * nblk;
     if (grid > 0x7fffffff) return fail(SPX_ERR_SHAPE, "dvals: too many blocks");
     const size_t lds = (size_t)std::min(n, dots_cols<LPE>()) * 16 * LPE;

@@ -158,6 +158,25 @@ def layer_kernel_by_size(s):
             assert rc == 0 and has(log, kernel) and not has(log, L2 if kernel == SLAB else SLAB), (m, n, per_row, B, log)
 
 
+def values_gradient_by_size(s):
+    """The gradient of the values, likewise: with more batch rows than a slab
+    holds it takes workgroups for half the chip and 16 entries per row and
+    block of columns."""
+    for m, n, per_row, dtype, slabs, gather in (
+            (2000, 256, 256, s.L.F32, (1, 64), (65, 256)),   # 32 workgroups
+            (2000, 256, 256, s.L.F64, (1, 32), (33, 64)),
+            (16384, 1024, 16, s.L.F32, (64,), (256,)),       # 8 entries per row and block
+            (16384, 1024, 32, s.L.F32, (64, 256), ()),
+            (100000, 256, 16, s.L.F64, (32, 64, 256), ()),
+            (2000, 4096, 128, s.L.F32, (64, 256), ())):
+        H = s.matrix(m, n, per_row, dtype)
+        s.calls(s.lib.dvals_pattern, H, 1, 1 << 50, 1 << 51, 1 << 52, None)
+        for B in slabs + gather:
+            rc, log = s.calls(s.lib.dvals_pattern, H, B, 1 << 50, 1 << 51, 1 << 52, None)
+            assert rc == 0 and has(log, "k_slab_dots") == (B in slabs) and has(log, "k_sddmm") == (B in gather), \
+                (m, n, per_row, B, log)
+
+
 def batch_table(s, without_memory):
     """run_batch's table of column segments: where its memory is refused the
     products go by atomics and it is not tried again; where its build fails
@@ -231,6 +250,7 @@ def ranking_that_fails_with_a_count_to_come(s):
 
 
 SCENARIOS = {
+    "values_gradient_by_size": values_gradient_by_size,
     "layer_kernel_by_size": layer_kernel_by_size,
     "layer_products_in_place": layer_products_in_place,
     "batch_table_without_memory": lambda s: batch_table(s, True),
