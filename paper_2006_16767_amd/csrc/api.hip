@@ -850,7 +850,9 @@ static spx_status refresh_csc(spx_matrix* H, int vs, hipStream_t s) {
         if (!captured) H->refreshed = true;
     }
     if (H->perm_blocks.at) return gather_blocks(A.vals, H->perm_blocks, H->vals_csc, A.nnz, vs, s);
-    return gather_perm(A.vals, H->perm, H->vals_csc, A.nnz, vs, s);
+    // by ranges of columns where a line per row fits an XCD's L2 or few rows
+    // hold most entries (then the handle renumbers)
+    return gather_perm(A.vals, H->perm, H->vals_csc, A.nnz, vs, s, A.m <= 32768 || H->gorder);
 }
 
 extern "C" spx_status spx_matrix_values_updated(spx_matrix* H, void* stream) {

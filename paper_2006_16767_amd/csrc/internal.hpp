@@ -79,9 +79,9 @@ spx_status radix_sort_pairs(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
 
 // row id of every CSR position
 spx_status expand_rows(const int32_t* row_ptr, int32_t m, int32_t* rows_out, hipStream_t s);
-// out[p] = in[perm[p]] for element size esize (4 or 8)
+// out[p] = in[perm[p]] for element size esize (4 or 8); by_range: see prim.hip
 spx_status gather_perm(const void* in, const int32_t* perm, void* out, int64_t n, int esize,
-                       hipStream_t s);
+                       hipStream_t s, bool by_range = true);
 // A permutation grouped by the block of its source (prim.hip).
 struct PermBlocks {
     int32_t* at = nullptr;

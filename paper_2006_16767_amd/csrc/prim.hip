@@ -346,24 +346,32 @@ spx_status expand_rows(const int32_t* row_ptr, int32_t m, int32_t* rows_out, hip
     return SPX_OK;
 }
 
-// out[p] = in[perm[p]]. A workgroup takes kGatherTile consecutive positions
-// (its loads of a phase all in flight) and every XCD one contiguous range of
-// them: where the permutation transposes a matrix, a range of positions is a
-// range of columns and reads the same eighth of every row, which stays in the
-// XCD's L2 (3.3M entries of a 16384 x 4096 matrix: 23 us against 28 us when
-// the ranges went round the XCDs and every L2 saw all of in).
-constexpr int kGatherPer = 8;
+// out[p] = in[perm[p]], kGatherPer positions per thread, their loads in
+// flight together. by_range: every XCD takes one contiguous range of positions.
+// Where the permutation transposes a matrix, a range of positions is a range of
+// columns and reads the same eighth of every row; that stays in the XCD's L2
+// (4 MB) where a line per row fits there, or where a few rows hold most
+// entries. Otherwise neighbouring positions read neighbouring parts of the same
+// lines on different XCDs at the same time, and meet in the Infinity Cache.
+// 4-byte values, in us, by ranges and round the XCDs: 16384 x 4096 with 3.4M
+// entries 19 / 26, R-MAT 2^20 with 16M 146 / 173; uniform 300000 x 300000 with
+// 4.8M 78 / 75, 200000 x 50000 with 12.8M 235 / 217 (with 8-byte values 253 /
+// 232). Eight positions per thread, past the caches, left too few workgroups
+// for 1M entries (R-MAT 2^16: 7.5 against 6.2 by ranges) and the values in
+// memory on the way to the next pass (16384 x 4096: 23 against 19).
+constexpr int kGatherPer = 2;
 constexpr int kGatherTile = kBlock * kGatherPer;
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_gather_perm(const T* __restrict__ in,
                                                         const int32_t* __restrict__ perm,
-                                                        T* __restrict__ out, int64_t n) {
-    const int64_t base = xcd_tile(blockIdx.x, gridDim.x) * kGatherTile + threadIdx.x;
+                                                        T* __restrict__ out, int64_t n, bool by_range) {
+    const int64_t tile = by_range ? xcd_tile(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+    const int64_t base = tile * kGatherTile + threadIdx.x;
     int32_t q[kGatherPer];
     T v[kGatherPer];
 #pragma unroll
-    for (int u = 0; u < kGatherPer; ++u) q[u] = base + u * kBlock < n ? __builtin_nontemporal_load(perm + base + u * kBlock) : 0;
+    for (int u = 0; u < kGatherPer; ++u) q[u] = base + u * kBlock < n ? perm[base + u * kBlock] : 0;
 #pragma unroll
     for (int u = 0; u < kGatherPer; ++u)
         if (base + u * kBlock < n) v[u] = in[q[u]];
@@ -373,13 +381,13 @@ __global__ __launch_bounds__(kBlock) void k_gather_perm(const T* __restrict__ in
 }
 
 spx_status gather_perm(const void* in, const int32_t* perm, void* out, int64_t n, int esize,
-                       hipStream_t s) {
+                       hipStream_t s, bool by_range) {
     if (n <= 0) return SPX_OK;
     const unsigned grid = (unsigned)ceil_div(n, kGatherTile);
     if (esize == 4)
-        k_gather_perm<uint32_t><<<grid, kBlock, 0, s>>>((const uint32_t*)in, perm, (uint32_t*)out, n);
+        k_gather_perm<uint32_t><<<grid, kBlock, 0, s>>>((const uint32_t*)in, perm, (uint32_t*)out, n, by_range);
     else if (esize == 8)
-        k_gather_perm<uint64_t><<<grid, kBlock, 0, s>>>((const uint64_t*)in, perm, (uint64_t*)out, n);
+        k_gather_perm<uint64_t><<<grid, kBlock, 0, s>>>((const uint64_t*)in, perm, (uint64_t*)out, n, by_range);
     else
         return fail(SPX_ERR_DTYPE, "gather_perm: element size must be 4 or 8");
     SPX_HIP(hipGetLastError());
