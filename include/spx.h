@@ -302,7 +302,7 @@ spx_status spx_matrix_csc(const spx_matrix *H, spx_csc *out);
  * CSR5 and DIA copies) from the borrowed CSR values (gathers through the permutations);
  * call after the caller changed A's values in place. The second call on a
  * handle that is not BOOL, with at most 65536 / value size columns and at least
- * 2^22 / value size entries synchronizes the stream and allocates: it orders
+ * 6291456 / value size entries synchronizes the stream and allocates: it orders
  * the permutation by blocks (22 bytes per entry while it does, 6 that the
  * handle keeps). It does not while the stream is being captured, and without
  * the memory every call gathers as the first one did. */

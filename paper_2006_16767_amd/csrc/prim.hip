@@ -400,7 +400,7 @@ spx_status gather_perm(const void* in, const int32_t* perm, void* out, int64_t n
 // with few columns (a block holds rows, a run a column's entries in them): a
 // store touches a line per run, where the gather above reads a line per entry.
 // The blocks of neighbouring runs go to one XCD, whose L2 joins them to lines.
-// 3.4M entries of a 16384 x 4096 matrix (runs of four): 13 against 23 us.
+// 3.4M entries of a 16384 x 4096 matrix (runs of four): 13 against 19 us.
 constexpr int kPermBytes = 65536;
 constexpr int kPermThreads = 1024;
 
@@ -452,14 +452,16 @@ __global__ __launch_bounds__(kBlock) void k_perm_from(int64_t n, int mask, const
 }
 
 // runs: the runs of positions that a block's readers make (the columns of a
-// transposed matrix). From one entry per run on (16384 x 16384 with 13.4M
-// entries: 73 against 86 us; 65536 x 16384 with 21.5M: 110 against 237;
-// longer lists of columns, as graphs have, would store a line per entry), and
-// from 64 blocks on (1.7M entries of 16384 x 1024, 102 blocks: 7 against 14 us;
-// 0.8M, 51 blocks: 13.6 against 14.2, which does not pay for the lists).
+// transposed matrix). From one entry per run on (whole refreshes, 4-byte values,
+// gather against blocks in us: 65536 x 16384 with 4.2M entries 70 / 43, 16384 x
+// 4096 with 3.4M 36 / 29, 1000000 x 100 with 3M 46 / 19; 16384 x 16384 with 13M
+// 123 / 127; longer lists of columns, as graphs have, would store a line per
+// entry), and from 96 blocks on, which are its workgroups (16384 x 1024 with
+// 1.67M entries, 102 blocks, 19.5 / 15.3; 4096 x 4096, 100 blocks, 18.2 / 18.2;
+// 8192 x 8192, 75 blocks, 14.0 / 16.4; 16384 x 1024, 64 blocks, 13.6 / 20.2).
 bool perm_blocks_pay(int64_t n, int64_t runs, int esize) {
     const int64_t E = kPermBytes / esize;
-    return runs <= E && n >= 64 * E && n < ((int64_t)1 << 31);
+    return runs <= E && n >= 96 * E && n < ((int64_t)1 << 31);
 }
 
 // at and from of k_gather_blocks, for a permutation of [0, n). Synchronizes.

@@ -199,10 +199,15 @@ def batch_table(s, without_memory):
 
 
 def refresh(s):
-    """The first refresh is a launch. The second one orders the permutation by
+    """Below 96 blocks of 16384 entries every refresh is a launch. From there
+    on the first one is. The second one orders the permutation by
     blocks (it allocates and waits), unless it is being captured; from then on
     a refresh is a launch again."""
-    H = s.matrix(1 << 14, 300, 64)  # 64 blocks of 16384 entries
+    H = s.matrix(1 << 14, 300, 95)
+    for _ in range(3):
+        rc, log = s.calls(s.lib.spx_matrix_values_updated, H, None)
+        assert rc == 0 and len(log) == 1 and has(log, "k_gather_perm"), log
+    H = s.matrix(1 << 14, 300, 96)
     rc, log = s.calls(s.lib.spx_matrix_values_updated, H, None)
     assert rc == 0 and len(log) == 1 and has(log, "k_gather_perm"), log
     s.so.stub_capturing(ALLOCATION_ALLOWED)
@@ -216,9 +221,9 @@ def refresh(s):
 
 
 def refresh_without_memory(s):
-    H = s.matrix(1 << 14, 300, 64)
+    H = s.matrix(1 << 14, 300, 96)
     assert s.calls(s.lib.spx_matrix_values_updated, H, None)[0] == 0
-    s.so.stub_fail_sizes(2 << 20, 2 << 20)  # the 16-bit half of the ordered permutation
+    s.so.stub_fail_sizes(3 << 20, 3 << 20)  # the 16-bit half of the ordered permutation
     rc, log = s.calls(s.lib.spx_matrix_values_updated, H, None)
     assert rc == 0 and has(log, "malloc-failed") and has(log[-1:], "k_gather_perm"), log
     rc, log = s.calls(s.lib.spx_matrix_values_updated, H, None)
