@@ -211,6 +211,7 @@ struct spx_matrix {
     // where each column (row) enters each row (column) block of the LDS slabs
     // of dX (dvals); built on first use
     PartTable slab_part, dots_part;
+    int32_t slab_rows = 0;              // batch rows up to which they take every layer product
     size_t grad_ws_refused = SIZE_MAX;  // bytes for the B-minor kernels that could not be had ahead
     bool cols_ascend = false;  // the column indices ascend within every row (F32 and F64 handles only)
     // column-sorted copy of the renumbered CSR for the balanced SpMV with
@@ -1886,12 +1887,27 @@ extern "C" spx_status spx_pagerank(spx_matrix* H, double damping, double eps, in
 }
 
 // ------------------------------------------------------------------ backward
-// The B-minor kernels' workspace, for a call that does not use it: a captured
-// call for which no table of bounds has been built falls back on those kernels
-// and cannot allocate. Where the memory is not there it is left out.
+// Whether the slab kernels take every layer product of up to B rows (none of
+// those needs the workspace). Answers are kept, up to 1024 rows.
+static bool slabs_to(spx_matrix* H, int32_t B) {
+    const spx_csr& A = H->csr;
+    const SlabBlocks b = slab_blocks(A.m);
+    while (H->slab_rows < std::min(B, 1024)) {
+        const int32_t k = H->slab_rows + 1;
+        if (!H->cols_ascend || !slab_gather_fits(A.m, A.n, A.nnz, k, A.dtype, nullptr) ||
+            !slab_gather_fits(A.n, A.m, A.nnz, k, A.dtype, &b) || !slab_dots_fits(A.m, A.n, A.nnz, k, A.dtype))
+            return false;
+        H->slab_rows = k;
+    }
+    return B <= H->slab_rows;
+}
+
+// The B-minor kernels' workspace, ahead of another product of up to B rows that
+// may be captured and then cannot allocate. Where the memory is not there it
+// is left out.
 static spx_status keep_grad_ws(spx_matrix* H, int32_t B, hipStream_t s) {
     const size_t bytes = grad_ws_bytes(H->csr.m, H->csr.n, B, H->csr.dtype);
-    if (bytes <= H->ws_bytes || bytes >= H->grad_ws_refused) return SPX_OK;
+    if (bytes <= H->ws_bytes || bytes >= H->grad_ws_refused || slabs_to(H, B)) return SPX_OK;
     bool captured = false;
     SPX_TRY(is_captured(s, &captured));
     if (captured) return SPX_OK;
@@ -1935,12 +1951,11 @@ extern "C" spx_status spmv_csr_batch(spx_matrix* H, int32_t B, const void* X, vo
 
 // A table of block bounds, built on first use (the pattern of A is fixed),
 // but not by a call that is being captured: the graph may run long after the
-// next eager call. *have = false: there is none, nor will there be where its
-// memory was refused.
+// next eager call. Without one, also where its memory was refused, the kernels
+// search for the bounds.
 static spx_status ensure_part(PartTable* t, int32_t nseg, const SlabBlocks& b, const int32_t* seg_ptr,
-                              const int32_t* idx, hipStream_t s, bool* have) {
-    *have = t->at || b.nblk == 1;
-    if (*have || t->refused) return SPX_OK;
+                              const int32_t* idx, hipStream_t s) {
+    if (t->at || t->refused || b.nblk == 1) return SPX_OK;
     bool captured = false;
     SPX_TRY(is_captured(s, &captured));
     if (captured) return SPX_OK;
@@ -1956,25 +1971,22 @@ static spx_status ensure_part(PartTable* t, int32_t nseg, const SlabBlocks& b, c
         return st;
     }
     t->at = p;
-    *have = true;
     return SPX_OK;
 }
 
 // dX = G A over the CSC copy (its rows ascend within a column, so G's rows
 // of length m can pass through LDS in blocks)
-static spx_status dx_in_slabs(spx_matrix* H, int32_t B, const void* G, const void* dX, hipStream_t s, bool* yes) {
+static bool dx_in_slabs(const spx_matrix* H, int32_t B, const void* G, const void* dX) {
     const spx_csr& A = H->csr;
     const SlabBlocks b = slab_blocks(A.m);
-    *yes = slab_gather_fits(A.n, A.m, A.nnz, B, A.dtype, &b) && !dx_in_place(H, B, G, dX);
-    return *yes ? ensure_part(&H->slab_part, A.n, b, H->col_ptr, H->row_idx, s, yes) : SPX_OK;
+    return slab_gather_fits(A.n, A.m, A.nnz, B, A.dtype, &b) && !dx_in_place(H, B, G, dX);
 }
 
 static spx_status run_dx(spx_matrix* H, int32_t B, const void* G, void* dX, hipStream_t s) {
     const spx_csr& A = H->csr;
-    bool slabs = false;
-    SPX_TRY(dx_in_slabs(H, B, G, dX, s, &slabs));
-    if (slabs) {
+    if (dx_in_slabs(H, B, G, dX)) {
         const SlabBlocks b = slab_blocks(A.m);
+        SPX_TRY(ensure_part(&H->slab_part, A.n, b, H->col_ptr, H->row_idx, s));
         SPX_TRY(keep_grad_ws(H, B, s));
         return slab_gather(A.n, A.m, A.nnz, B, A.dtype, &b, H->col_ptr, H->slab_part.at, H->row_idx, H->vals_csc, G,
                            dX, s);
@@ -1984,19 +1996,16 @@ static spx_status run_dx(spx_matrix* H, int32_t B, const void* G, void* dX, hipS
     return launch_dx(H->col_ptr, H->row_idx, H->vals_csc, A.m, A.n, A.dtype, B, G, dX, ws, s);
 }
 
-static spx_status dvals_in_slabs(spx_matrix* H, int32_t B, const void* G, const void* X, const void* dvals,
-                                 hipStream_t s, bool* yes) {
+static bool dvals_in_slabs(const spx_matrix* H, int32_t B, const void* G, const void* X, const void* dvals) {
     const spx_csr& A = H->csr;
-    *yes = H->cols_ascend && slab_dots_fits(A.m, A.n, A.nnz, B, A.dtype) &&
+    return H->cols_ascend && slab_dots_fits(A.m, A.n, A.nnz, B, A.dtype) &&
            !rows_overlap(H, (int64_t)B * A.m, G, A.nnz, dvals) && !rows_overlap(H, (int64_t)B * A.n, X, A.nnz, dvals);
-    return *yes ? ensure_part(&H->dots_part, A.m, dots_blocks(A.n), A.row_ptr, A.col_idx, s, yes) : SPX_OK;
 }
 
 static spx_status run_dvals(spx_matrix* H, int32_t B, const void* G, const void* X, void* dvals, hipStream_t s) {
     const spx_csr& A = H->csr;
-    bool slabs = false;
-    SPX_TRY(dvals_in_slabs(H, B, G, X, dvals, s, &slabs));
-    if (slabs) {
+    if (dvals_in_slabs(H, B, G, X, dvals)) {
+        SPX_TRY(ensure_part(&H->dots_part, A.m, dots_blocks(A.n), A.row_ptr, A.col_idx, s));
         SPX_TRY(keep_grad_ws(H, B, s));
         return slab_dots(A.m, A.n, A.nnz, B, A.dtype, A.row_ptr, H->dots_part.at, A.col_idx, G, X, dvals, s);
     }
@@ -2030,11 +2039,9 @@ extern "C" spx_status spx_backward(spx_matrix* H, int32_t B, const void* G, cons
     const int dt = A.dtype;
     if (dt != SPX_F32 && dt != SPX_F64) return fail(SPX_ERR_DTYPE, "backward supports F32 and F64");
     hipStream_t s = (hipStream_t)stream;
-    bool dx_slabs = false, dvals_slabs = false;
-    if (dX) SPX_TRY(dx_in_slabs(H, B, G, dX, s, &dx_slabs));
-    if (dvals) SPX_TRY(dvals_in_slabs(H, B, G, X, dvals, s, &dvals_slabs));
     // (dX over G: both gradients from one copy of G, made before dX)
-    if (dx_slabs || (dvals_slabs && !(dX && dx_in_place(H, B, G, dX)))) {
+    if ((dX && dx_in_slabs(H, B, G, dX)) ||
+        (dvals && dvals_in_slabs(H, B, G, X, dvals) && !(dX && dx_in_place(H, B, G, dX)))) {
         // a gradient that does not go through LDS makes its own B-minor copies
         if (dX) SPX_TRY(run_dx(H, B, G, dX, s));
         return dvals ? run_dvals(H, B, G, X, dvals, s) : SPX_OK;

@@ -355,7 +355,8 @@ spx_status launch_dvals(const int32_t* row_ptr, const int32_t* col_idx, int32_t 
 // The same products with the dense operand held in LDS, a slab of its
 // columns at a time (slab.hip). SlabBlocks cuts an operand's N columns into
 // nblk blocks of cb for segments whose indices ascend; part (nblk * nseg
-// entries, slab_part_build) holds where each segment enters each block.
+// entries, slab_part_build) holds where each segment enters each block (null:
+// the kernels search for it).
 // slab_gather with blocks null: one slab of all columns, any index order.
 struct SlabBlocks {
     int32_t nblk = 1;

@@ -174,6 +174,19 @@ __device__ __forceinline__ int slab_fold_row(int lane) {
     return W == 2 ? (lane & 1) * E + ((lane >> 1) & 1) * (E / 2) : (lane & 1) * (E / 2);
 }
 
+// The first entry of a segment (of [lo, hi)) whose index is at or past c; its
+// indices ascend.
+__device__ __forceinline__ int first_from(const int32_t* __restrict__ idx, int lo, int hi, int c) {
+    while (lo < hi) {
+        const int mid = lo + (hi - lo) / 2;
+        if (idx[mid] < c)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    return lo;
+}
+
 // LDS of a gather workgroup: the slab and its zero column, then the sums of
 // the segments, NB + 1 values apart.
 template <typename T, int W>
@@ -184,8 +197,9 @@ static size_t slab_gather_lds(int32_t cb, int32_t segs) {
 // Workgroup = (segments [tile * st, + st), batch rows [chunk * NB, + NB)).
 // The operand's N columns come as nblk slabs of cb; with nblk > 1 the
 // segments' indices ascend and part[blk * nseg + j] is the first entry of
-// segment j at or past column blk * cb (blk < nblk).
-template <typename T, int W>
+// segment j at or past column blk * cb (blk < nblk); without the table (PART =
+// false) it is searched for.
+template <typename T, int W, bool PART>
 __global__ __launch_bounds__(kSlabThreads) void k_slab_gather(int32_t nseg, int32_t N, int32_t nnz, int32_t B,
                                                               int32_t st, int32_t nchunk, int32_t nblk, int32_t cb,
                                                               const int32_t* __restrict__ seg_ptr,
@@ -217,8 +231,15 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab_gather(int32_t nseg, int3
         k0 = k1 = 0;
         if (pblk < nblk && s < ns) {
             const int64_t j = j0 + s;
-            k0 = pblk > 0 ? part[(int64_t)pblk * nseg + j] : seg_ptr[j];
-            k1 = pblk + 1 < nblk ? part[(int64_t)(pblk + 1) * nseg + j] : seg_ptr[j + 1];
+            if constexpr (PART) {
+                k0 = pblk > 0 ? part[(int64_t)pblk * nseg + j] : seg_ptr[j];
+                k1 = pblk + 1 < nblk ? part[(int64_t)(pblk + 1) * nseg + j] : seg_ptr[j + 1];
+            } else {
+                k0 = seg_ptr[j];
+                k1 = seg_ptr[j + 1];
+                if (pblk > 0) k0 = first_from(idx, k0, k1, pblk * cb);
+                if (pblk + 1 < nblk) k1 = first_from(idx, k0, k1, (pblk + 1) * cb);
+            }
         }
         if (++pr == rounds) {
             pr = 0;
@@ -313,7 +334,8 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab_gather(int32_t nseg, int3
 // pieces are permuted by its number (dots_at), so that neither the slab's
 // writes (a wave writes one piece of 64 columns) nor its reads (LPE = 16: the
 // 256 bytes of 4 columns) meet on banks. part[i * m + r] is the first entry
-// of row r at or past column i * kDotsGrain (columns ascend within a row).
+// of row r at or past column i * kDotsGrain (columns ascend within a row); PART
+// as above.
 constexpr int kDotsBytes = 128 * 1024;
 constexpr int kDotsGrain = 512;
 
@@ -379,7 +401,7 @@ __device__ __forceinline__ T dots_step(const char* slab, int at, int mine, const
     return dots_fold<LPE, T>(v);
 }
 
-template <typename T, int LPE>
+template <typename T, int LPE, bool PART>
 __global__ __launch_bounds__(kSlabThreads) void k_slab_dots(int32_t m, int32_t n, int32_t nnz, int32_t B, int32_t st,
                                                             int32_t nblk, const int32_t* __restrict__ row_ptr,
                                                             const int32_t* __restrict__ part,
@@ -431,9 +453,16 @@ __global__ __launch_bounds__(kSlabThreads) void k_slab_dots(int32_t m, int32_t n
             for (int e = 0; e < E; ++e) gv[e] = (T)0;
             if (s < ns) {
                 const int64_t j = j0 + s;
-                const int32_t p = blk * grains;
-                k0 = blk > 0 ? part[p * (int64_t)m + j] : row_ptr[j];
-                k1 = blk + 1 < nblk ? part[(p + grains) * (int64_t)m + j] : row_ptr[j + 1];
+                if constexpr (PART) {
+                    const int32_t p = blk * grains;
+                    k0 = blk > 0 ? part[p * (int64_t)m + j] : row_ptr[j];
+                    k1 = blk + 1 < nblk ? part[(p + grains) * (int64_t)m + j] : row_ptr[j + 1];
+                } else {
+                    k0 = row_ptr[j];
+                    k1 = row_ptr[j + 1];
+                    if (blk > 0) k0 = first_from(col_idx, k0, k1, c0);
+                    if (blk + 1 < nblk) k1 = first_from(col_idx, k0, k1, c0 + cols);
+                }
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
                     const int b = b0 + (g % LPE) * E + e;
@@ -483,15 +512,7 @@ __global__ __launch_bounds__(kBlock) void k_slab_part(int32_t nseg, int32_t nblk
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= (int64_t)nseg * nblk) return;
     const int32_t blk = (int32_t)(i / nseg), j = (int32_t)(i % nseg);
-    int lo = seg_ptr[j], hi = seg_ptr[j + 1];
-    while (lo < hi) {
-        const int mid = lo + (hi - lo) / 2;
-        if (idx[mid] < blk * cb)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    part[i] = lo;
+    part[i] = first_from(idx, seg_ptr[j], seg_ptr[j + 1], blk * cb);
 }
 
 // ------------------------------------------------------------------ host
@@ -640,10 +661,10 @@ static spx_status slab_gather_w(int32_t nseg, int32_t N, int32_t nnz, int32_t B,
     const int64_t grid = ceil_div(nseg, st) * nchunk;
     if (grid > 0x7fffffff) return fail(SPX_ERR_SHAPE, "batch gather: too many batch rows");
     const size_t lds = slab_gather_lds<T, W>(b.cb, st);
-    SPX_HIP(hipFuncSetAttribute((const void*)k_slab_gather<T, W>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds));
-    k_slab_gather<T, W><<<(unsigned)grid, kSlabThreads, lds, s>>>(nseg, N, nnz, B, st, nchunk, b.nblk, b.cb, seg_ptr, part,
-                                                                  idx, vals, in, out);
+    const auto kernel = part || b.nblk == 1 ? k_slab_gather<T, W, true> : k_slab_gather<T, W, false>;
+    SPX_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    kernel<<<(unsigned)grid, kSlabThreads, lds, s>>>(nseg, N, nnz, B, st, nchunk, b.nblk, b.cb, seg_ptr, part, idx,
+                                                     vals, in, out);
     SPX_HIP(hipGetLastError());
     return SPX_OK;
 }
@@ -676,11 +697,11 @@ static spx_status slab_dots_l(int32_t m, int32_t n, int32_t nnz, int32_t B, cons
     const int64_t grid = ceil_div(m, st) * nblk;
     if (grid > 0x7fffffff) return fail(SPX_ERR_SHAPE, "dvals: too many blocks");
     const size_t lds = (size_t)std::min(n, dots_cols<LPE>()) * 16 * LPE;
-    SPX_HIP(hipFuncSetAttribute((const void*)k_slab_dots<T, LPE>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kDotsBytes));
+    const auto kernel = part || nblk == 1 ? k_slab_dots<T, LPE, true> : k_slab_dots<T, LPE, false>;
+    SPX_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kDotsBytes));
     // the permuted pieces of the last columns stay within their column
-    k_slab_dots<T, LPE><<<(unsigned)grid, kSlabThreads, lds, s>>>(m, n, nnz, B, st, nblk, row_ptr, part, col_idx,
-                                                                  (const T*)G, (const T*)X, (T*)dvals);
+    kernel<<<(unsigned)grid, kSlabThreads, lds, s>>>(m, n, nnz, B, st, nblk, row_ptr, part, col_idx, (const T*)G,
+                                                     (const T*)X, (T*)dvals);
     SPX_HIP(hipGetLastError());
     return SPX_OK;
 }

@@ -14,6 +14,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PY = os.path.join(os.path.dirname(HERE), "paper_2006_16767_amd", "_lib.py")
 ALLOCATION_REFUSED, ALLOCATION_ALLOWED = 1, 2  # during a capture
+TABLE = "Lb1E"  # in the name of a slab kernel that reads a table of bounds
 
 
 class Stub:
@@ -67,42 +68,63 @@ def has(log, name):
 
 def block_bounds_under_capture(s, mode):
     """The first backward of a handle is a captured one: no table of bounds is
-    built (it would be filled when the graph runs), the kernels that need none
-    are launched, in the workspace that the forward left; the next eager call
-    builds the tables and reads them."""
+    built (it would be filled when the graph runs) and nothing is allocated;
+    the kernels search for the bounds. The next eager call builds the tables
+    and reads them, and so does a call captured after it."""
     m, n, B = 8192, 600, 64
     H = s.matrix(m, n, 200)
     X, G, Y, dX, dv = (s.zeros(4 * k) for k in (B * n, B * m, B * m, B * n, m * 200))
     rc, log = s.calls(s.lib.spmv_csr_batch, H, B, X, Y, None)
-    assert rc == 0 and has(log, "k_slab_gather")
+    assert rc == 0 and kernels(log) == log and has(log, "k_slab_gather")
     s.so.stub_capturing(mode)
     for call, args in ((s.lib.spx_backward, (G, X, dX, dv)), (s.lib.spmv_csr_transpose, (G, dX)),
                        (s.lib.dvals_pattern, (G, X, dv)), (s.lib.spmv_csr_batch, (X, Y))):
         rc, log = s.calls(call, H, B, *args, None)
         assert rc == 0, s.lib.spx_last_error()
-        assert kernels(log) == log and not has(log, "k_slab_part") and not has(log, "k_slab_dots"), log
-        assert has(log, "k_seg_gather") or has(log, "k_sddmm") or call is s.lib.spmv_csr_batch
+        assert kernels(log) == log and not has(log, "k_slab_part") and has(log, "k_slab_"), log
+        assert call is s.lib.spmv_csr_batch or not any(TABLE in line for line in log), log
     s.so.stub_capturing(0)
     rc, log = s.calls(s.lib.spx_backward, H, B, G, X, dX, dv, None)
     assert rc == 0 and sum("k_slab_part" in line for line in log) == 2
-    assert has(log, "k_slab_gather") and has(log, "k_slab_dots")
+    assert sum(TABLE in line for line in log) == 2, log
     s.so.stub_capturing(mode)
     rc, log = s.calls(s.lib.spx_backward, H, B, G, X, dX, dv, None)
-    assert rc == 0 and kernels(log) == log and has(log, "k_slab_gather") and has(log, "k_slab_dots")
+    assert rc == 0 and kernels(log) == log and sum(TABLE in line for line in log) == 2, log
+
+
+def workspace_for_a_captured_call(s):
+    """A forward through the slabs keeps the workspace where the backward, or a
+    smaller batch, needs it: a call captured next cannot allocate. Where the
+    slabs take them all it allocates nothing."""
+    for m, n, per_row, B, keeps in ((16384, 4096, 205, 64, False), (65536, 4096, 64, 8, False), (65536, 1000, 2, 8, False),
+                                    (100000, 4096, 8, 8, True), (16384, 4096, 8, 4, True)):
+        H = s.matrix(m, n, per_row)
+        rc, log = s.calls(s.lib.spmv_csr_batch, H, B, 1 << 50, 1 << 51, None)
+        if not has(log, "k_slab_gather"):  # its own workspace
+            assert has(log, "malloc")
+            continue
+        assert rc == 0 and has(log, "malloc") == keeps, (m, n, per_row, log)
+        s.so.stub_capturing(ALLOCATION_REFUSED)
+        for b in range(1, B + 1):
+            for f, args in ((s.lib.spmv_csr_batch, ()), (s.lib.spmv_csr_transpose, ()), (s.lib.dvals_pattern, (1 << 52,)),
+                            (s.lib.spx_backward, (1 << 52, 1 << 53))):
+                assert s.calls(f, H, b, 1 << 50, 1 << 51, *args, None)[0] == 0, (m, n, per_row, b, f.__name__)
+        s.so.stub_capturing(0)
 
 
 def block_bounds_without_memory(s):
-    """No memory for the tables of bounds: the kernels that need none, and
-    the tables are not tried again."""
+    """No memory for the tables of bounds: the kernels search for them, and the
+    tables are not tried again."""
     m, n, B = 8192, 600, 64
     H = s.matrix(m, n, 200)
     X, G, dX, dv = (s.zeros(4 * k) for k in (B * n, B * m, B * n, m * 200))
     s.so.stub_fail_sizes(2 * n * 4, 2 * m * 4)
     rc, log = s.calls(s.lib.spx_backward, H, B, G, X, dX, dv, None)
     assert rc == 0 and sum("malloc-failed" in line for line in log) == 2
-    assert has(log, "k_seg_gather") and has(log, "k_sddmm")
-    rc, log = s.calls(s.lib.spx_backward, H, B, G, X, dX, dv, None)
-    assert rc == 0 and kernels(log) == log and has(log, "k_seg_gather") and has(log, "k_sddmm")
+    for _ in range(2):
+        assert has(log, "k_slab_gather") and has(log, "k_slab_dots") and not any(TABLE in line for line in log), log
+        rc, log = s.calls(s.lib.spx_backward, H, B, G, X, dX, dv, None)
+        assert rc == 0 and kernels(log) == log
 
 
 def layer_products_in_place(s):
@@ -255,6 +277,7 @@ def ranking_that_fails_with_a_count_to_come(s):
 
 
 SCENARIOS = {
+    "workspace_for_a_captured_call": workspace_for_a_captured_call,
     "values_gradient_by_size": values_gradient_by_size,
     "layer_kernel_by_size": layer_kernel_by_size,
     "layer_products_in_place": layer_products_in_place,
