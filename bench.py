@@ -264,7 +264,7 @@ def extra_fwd_bwd(torch, spx, synth, flush, reps=10):
     t_f_sparse = med(lambda: M.run_dense_batch(X, Y))  # per-vector adaptive SpMSpV
     t_dx = med(lambda: M.transpose_matvec(G, dX))
     t_dv = med(lambda: M.dvals(G, X, dv))
-    t_bwd = med(lambda: M.backward(G, X))  # both gradients from one B-minor copy of G
+    t_bwd = med(lambda: M.backward(G, X))  # both gradients in one call
     B, m, n, nnz = 64, A.m, A.n, A.nnz
     nnz_x = [v.nnz for v in acts]
     xs = [(torch.as_tensor(v.idx, device="cuda"), torch.as_tensor(v.val, device="cuda")) for v in acts]
@@ -294,9 +294,9 @@ def extra_fwd_bwd(torch, spx, synth, flush, reps=10):
             "unique_scale": {"fwd_pct_hbm_peak": round(f_u, 2), "bwd_pct_hbm_peak": round(b_u, 2),
                              "bwd_over_fwd": round(b_u / f_u, 2)},
             "dx_pct_unique": round(pct(dx_u, t_dx), 2), "dvals_pct": round(pct(dv_b, t_dv), 2),
-            # the gathers' own roofs: every stored entry reads B-long rows of the
-            # B-minor copies (G^T for dX; G^T and X^T for dvals) from L2, and
-            # does 2 B FP32 flops
+            # the gathers' own roofs: every stored entry takes B values of G (for
+            # dX), or of G and X (for dvals), and does 2 B FP32 flops. Gathered
+            # from L2 they would be bound by its rate; from LDS they are not
             "l2_gather": {"dx_GB/s": round(nnz * B * 4 / (t_dx * 1e-3) / 1e9, 1),
                           "dvals_GB/s": round(nnz * B * 8 / (t_dv * 1e-3) / 1e9, 1),
                           "derived_peak_GB/s": L2_PEAK_GBS,

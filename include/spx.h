@@ -432,11 +432,14 @@ spx_status spx_batch_status(spx_matrix *H, int32_t *flags, void *stream);
 
 /* Y[b] = A X[b] for the B rows of a dense X (B x n -> Y B x m, device,
  * row-major): the row-major SpMV of Section 4.1 applied to all B vectors
- * in one pass over A (a wave per row, lane = batch entry, entries of x
- * gathered from a B-minor copy of X in the workspace). Reads A once where
- * B separate calls read it B times; meant for dense batches such as layer
- * activations. One wave walks a whole row, so rows far longer than the
- * average (hub rows) serialize. F32 and F64 only. */
+ * in one pass over A: X a few rows at a time in LDS, past which A is read
+ * once per 4 to 8 rows (n <= 8192 and rows of A long enough for it), or a
+ * wave per row of A with the entries of x gathered from a B-minor copy of X
+ * in the workspace. Meant for dense batches such as layer activations. 16
+ * lanes or a wave walk a whole row, so rows far longer than the average
+ * (hub rows) serialize. Y may share memory with X (A square): X is copied
+ * first. Allocates where the workspace is first needed, or needed larger
+ * (spx_backward). F32 and F64 only. */
 spx_status spmv_csr_batch(spx_matrix *H, int32_t B, const void *X, void *Y, void *stream);
 
 /* Sparse-output SpMSpV with a complement mask (the frontier form of the
@@ -478,9 +481,11 @@ spx_status spx_pack_mask(int32_t m, const uint8_t *rows, uint32_t *words, void *
  * labelled (1 + the largest level). If plans is given, plans[l] receives
  * the plan of expansion l for l < plans_cap; a masked pull is reported as
  * {SPX_PAT_CSR_SPMSPV, SPX_DIST_DIRECT, SPX_WB_NONE, lanes = -1}.
- * Synchronizes the stream once per level (the frontier size decides the
- * next call). The frontier lists and bitvectors, the product buffer and
- * a pinned counter belong to the handle (allocated on the first call). */
+ * Waits for every level (the frontier size decides the next call): the
+ * host polls a pinned word that the level's last workgroup stores the size
+ * to, and synchronizes the stream if it has not come within a second and
+ * at the end. The frontier lists and bitvectors, the product buffer and
+ * the counters belong to the handle (allocated on the first call). */
 #define SPX_BFS_PUSH_ONLY 1u
 spx_status spx_bfs(spx_matrix *H, int32_t source, int32_t *level, int32_t max_levels, const spx_plan *plan,
                    uint32_t flags, int32_t *n_levels, spx_plan *plans, int32_t plans_cap, void *stream);
@@ -501,10 +506,11 @@ spx_status spx_bfs(spx_matrix *H, int32_t source, int32_t *level, int32_t max_le
  * damping in [0, 1), eps >= 0, max_iters >= 0. rank (required) and
  * residual (optional): device arrays of n values of the handle's type,
  * written by the call. *n_iters = the number of products; plans[k]
- * receives the plan of product k for k < plans_cap. Synchronizes the
- * stream once per round. The column sums are computed on the first call
- * and again after spx_matrix_values_updated; the work buffers belong to
- * the handle. */
+ * receives the plan of product k for k < plans_cap. Waits for every round's
+ * count (polled in a pinned word, as in spx_bfs), not for the last product:
+ * rank and residual are ready in stream order. The column sums are computed
+ * on the first call and again after spx_matrix_values_updated (one
+ * synchronization); the work buffers belong to the handle. */
 spx_status spx_pagerank(spx_matrix *H, double damping, double eps, int32_t max_iters, const spx_plan *plan,
                         void *rank, void *residual, int32_t *n_iters, spx_plan *plans, int32_t plans_cap,
                         void *stream);
@@ -516,10 +522,17 @@ spx_status spx_pagerank(spx_matrix *H, double damping, double eps, int32_t max_i
  *                                           read as rows of A^T, a gather
  *                                           along columns, no atomics)
  *   dvals_k = sum_b G[b, row k] X[b, col k]  over the CSR pattern
- * Both read the matrix once for the whole batch. F32 and F64 only. The
- * handle's workspace holds B-minor copies of G (and X); dX is stored
- * B-major directly by the gather kernel (a workgroup's 16 columns turned
- * through LDS).
+ * F32 and F64 only. dX passes G through LDS, a block of rows of A at a time
+ * (A is read once per 4 to 8 rows of G), dvals X, a block of columns at a
+ * time (A is read once per 32 or 64 rows); dvals does where the columns
+ * ascend within every row of A. Where these are not the faster ones, and
+ * where a result shares memory with G or X, both read the matrix once for
+ * 64 rows and gather from B-minor copies of G (and X) in the workspace.
+ * The first call that needs it allocates the workspace ((m + n) * B values,
+ * also ahead of a product of up to B rows that might be captured), and the
+ * first dX and dvals through LDS a table of where each column (row) of A
+ * enters each block, at most half a byte (4 bytes) per entry of A. A call
+ * that is being captured builds no table: its kernels search for the bounds.
  * ------------------------------------------------------------------- */
 
 /* dX[b] = A^T G[b] for b < B: G is B x m, dX is B x n (device, row-major). */
@@ -531,10 +544,11 @@ spx_status dvals_pattern(spx_matrix *H, int32_t B, const void *G, const void *X,
                          void *stream);
 
 /* Both gradients of one backward pass: dX = G A (as spmv_csr_transpose)
- * and dvals (as dvals_pattern), computed from one B-minor copy of G, which
- * the two separate calls would each make. dX or dvals may be NULL to skip
- * it (not both); X may be NULL when dvals is. Same layouts and dtypes as
- * the separate calls. */
+ * and dvals (as dvals_pattern). Where neither goes through LDS they share
+ * one B-minor copy of G, which the separate calls would each make. dX or
+ * dvals may be NULL to skip it (not both); X may be NULL when dvals is.
+ * Same layouts and dtypes as the separate calls; dX may share memory with
+ * G (dvals is that of G as it was), but with X only when dvals is NULL. */
 spx_status spx_backward(spx_matrix *H, int32_t B, const void *G, const void *X, void *dX, void *dvals,
                         void *stream);
 

@@ -449,9 +449,9 @@ class Matrix:
 
 
     def backward(self, G, X=None, want_dx=True, want_dvals=True, stream=None):
-        """(dX, dvals) of one backward pass from one B-minor copy of G:
-        dX[b] = A^T G[b] (B x n) and dvals[k] = sum_b G[b, row k] X[b, col k];
-        either may be skipped (None is returned for it)."""
+        """(dX, dvals) of one backward pass: dX[b] = A^T G[b] (B x n) and
+        dvals[k] = sum_b G[b, row k] X[b, col k]; either may be skipped (None
+        is returned for it)."""
         torch = _torch()
         G2 = G.reshape(-1, self.m).contiguous()
         B = int(G2.shape[0])

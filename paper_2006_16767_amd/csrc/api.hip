@@ -1484,8 +1484,7 @@ extern "C" spx_status run_batch(spx_matrix* H, int32_t B, int64_t total_nnz_x, c
         }
     }
     // capacity-bounded workspace, zeroed at allocation (the per-vector
-    // bitvector and value slots and the group slabs are self-cleaning
-    // afterwards)
+    // bitvector and value slots are self-cleaning afterwards)
     if (B > H->bcap_B || total_nnz_x > H->bcap_nnz) {
         const int32_t nb = std::max(B, H->bcap_B);
         const int64_t nn = std::max(total_nnz_x, H->bcap_nnz);

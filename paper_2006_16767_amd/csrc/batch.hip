@@ -121,8 +121,7 @@ struct BatchDev {
     int32_t* heads;   // of the queues of work units, 128 bytes apart
     int32_t* stray;   // a flag per vector: k_batch_slabs met an entry outside its tile
     int32_t* gvec;    // slot -> vector, behind the groups' slots the other vectors for k_batch_rows
-    void* xt_all;     // ceil(B / gsize) slabs of (n + 1) x gsize values, row n zero
-    int32_t gsize;    // vectors per fused group and slots per slab row
+    void* xt_all;     // a slab of (n + 1) x group_size values per group, row n zero
 };
 
 __device__ __forceinline__ int dev_tree_eval(const DevTree& t, const double* f) {
@@ -1067,7 +1066,6 @@ static void batch_layout(int32_t m, int32_t n, int dtype, int32_t B, int64_t cap
     d->stray = (int32_t*)(base + off[13]);
     d->gvec = (int32_t*)(base + off[10]);
     d->xt_all = base + off[11];
-    d->gsize = (int32_t)gsize;
 }
 
 size_t batch_ws_size(int32_t m, int32_t n, int dtype, int32_t B, int64_t cap_nnz_x, int64_t tiles_mat,

@@ -279,7 +279,14 @@ struct BatchLaunch {
     int32_t nblk;
     int32_t* fused_per_cu;  // resident workgroups of the walk per CU, 0 = not asked yet (kept by the handle)
 };
-// entries of a work unit (the walk's LDS per wave is 12 KB with 4-byte values)
+// entries of a work unit (the walk's LDS per wave is 12 KB with 4-byte values).
+// 256 vectors of density 10 %, FP32, units of 512 / 640 / 768: R-MAT 2^18 861 /
+// 777 / 762 us, power-law rows 100000 x 50000 415 / 401 / 396, uniform 30000 x
+// 20000 with 64 a row 181 / 183 / 175, R-MAT 2^13 47 / 47 / 46; 16 vectors of
+// 30 % on R-MAT 2^16, where the units are few, 53 / 56 / 57. With 8-byte values
+// 512 / 640 / 768 take 1811 / 1618 / 1579 on R-MAT 2^18, but 58 / 61 / 64 on
+// 5000 power-law rows: what a longer unit gains on a large matrix it loses where
+// the units do not fill the chip.
 constexpr int fused_unit_nnz(int value_bytes) { return value_bytes == 8 ? 512 : 768; }
 constexpr int kFusedUnitRows = 32;
 size_t batch_ws_size(int32_t m, int32_t n, int dtype, int32_t B, int64_t cap_nnz_x, int64_t tiles_mat,

@@ -11,8 +11,8 @@ summaries read the rocpd databases rocprofv3 writes (`*_results.db`).
   python -m paper_2006_16767_amd.prof batch [--B 512] [--reps R]
       run_batch on the 512-vector R-MAT 2^18 (degree 32) batch.
   python -m paper_2006_16767_amd.prof fc [--reps R]
-      the pruned FC layer 16384 x 4096: fused forward, then dX and dvals
-      in one backward call.
+      a training pass of the pruned FC layer 16384 x 4096: values refresh,
+      fused forward, then dX and dvals in one backward call.
   python -m paper_2006_16767_amd.prof poisson [--k K] [--dtype f32|f64] [--reps R]
       run() on a dense x over the 7-point Poisson matrix on K^3 (128 by
       default; the format tree keeps the ELL copy for it).
@@ -232,10 +232,11 @@ def cmd_fc(args):
     G = torch.as_tensor(synth.cfg5_upstream(), device="cuda")
     Y = M.out_tensor(64)
     for _ in range(args.reps + 1):
+        M.values_updated()
         M.spmv_batch(X, Y)
-        M.backward(G, X)  # dX and dvals from one B-minor copy of G
+        M.backward(G, X)
     torch.cuda.synchronize()
-    print(f"[prof] FC layer 16384 x 4096: {args.reps + 1} forward + backward passes done", flush=True)
+    print(f"[prof] FC layer 16384 x 4096: {args.reps + 1} training passes done", flush=True)
 
 
 def cmd_bfs(args):
