@@ -102,8 +102,8 @@ __global__ __launch_bounds__(kBlock) void k_dia_fill(int32_t m, const int32_t* _
 // each offset, comes into one L2 once and not into several: a call, back to
 // back over rotating x, on Poisson 128^3 in FP32 takes 14.0 us (18.8 with the
 // workgroups round the XCDs; its 77 MB at the rate of a large copy: 14), on
-// 101^3 in FP64 12.7 (14.7). Non-temporal loads of the cells undo it (17.8 and
-// 20.3 for a kernel that starts alone, 14.5 and 14.3 without).
+// 101^3 in FP64 12.7 (14.7); the kernels in a trace 14.0 and 13.3. Non-temporal
+// loads of the cells undo it (17.8 and 20.3).
 template <int DT>
 __global__ __launch_bounds__(kBlock) void k_dia_spmv(int32_t m, int32_t n, int nd, const int32_t* __restrict__ offs,
                                                      int64_t words, const typename SR<DT>::V* __restrict__ dvals,

@@ -578,8 +578,8 @@ static SlabTiling slab_tiling(int32_t nseg, int32_t B, int NB, int cus) {
 // B-minor copy no longer lies in the L2s. The constants are a fit to 2368
 // products (forward with 256 to 8192 columns, dX over 1 to 64 slabs, 8 to 512
 // entries per segment and slab, B = 1 to 256, both types). The rule takes the
-// slower kernel by more than 6 % in 12 of them (24 % at most), the mean alone
-// (from 8 entries on) took it in 529. L2 gather against slabs: 300000 x 4096
+// slabs where they are more than 6 % slower in 25 of them (22 % at most); the
+// mean alone (from 8 entries on) did in 529. L2 gather against slabs: 300000 x 4096
 // with 8 entries a row, FP32, 74 against 184 us at B = 64 and 65 against 31 at
 // B = 8; 100000 x 4096 at B = 64, FP32, 40 / 73 us with 16 entries a row, 98 /
 // 79 with 64; FP64 100 / 155 with 32, 363 / 225 with 128; dX of 262144 x 4096
